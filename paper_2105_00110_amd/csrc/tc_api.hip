@@ -391,7 +391,7 @@ tc_status tc_graph_from_csr(const int64_t *row_ptr, const int32_t *col, int32_t 
     g->last_stream = s;
     tc_prof_mark(g, 0, s);
     tc_status st = assume_simple_sorted
-                       ? tc_build_from_pairs(g, nullptr, nullptr, 0, nullptr, nullptr, 1, s, d_rp,
+                       ? tc_build_from_pairs(g, nullptr, nullptr, nnz, nullptr, nullptr, 1, s, d_rp,
                                              d_col)
                        : tc_build_from_pairs(g, d_src, d_col, nnz, nullptr, nullptr, 1, s);
     if (st >= 0) st = finish_build(g, s);

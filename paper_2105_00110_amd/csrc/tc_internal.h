@@ -197,8 +197,8 @@ void tc_prof_mark(tc_graph *g, int idx, hipStream_t s);
 
 // Pipeline stages (tc_build.hip, tc_count.hip, tc_aggregate.hip).
 // Canonical edges from pairs (sorted and deduplicated), or, with simple_rp
-// given, from a simple sorted CSR (simple_rp / simple_col, device): the
-// entries above the diagonal, taken in order.
+// given, from a simple sorted CSR of P entries (simple_rp / simple_col,
+// device): the entries above the diagonal, taken in order.
 tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *d_dst,
                               int64_t P, const int64_t *d_pair_vtx_base,
                               const int64_t *d_pair_off, int32_t num_graphs, hipStream_t s,

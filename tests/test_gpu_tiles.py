@@ -1,0 +1,55 @@
+"""GPU parity at the edges of tiles, classes and dispatch rules.
+
+Each test takes one kernel (or one rule that picks a kernel) at the sizes
+where it can go wrong: a tile exactly full, one more, the first and last row
+of a class, long runs of empty rows.  Expected values come from the CPU
+oracle; all integers are equal and the quotient bit-identical.
+"""
+import numpy as np
+import pytest
+
+from oracle import native
+from paper_2105_00110_amd import graphgen as gg
+from tests.test_gpu_parity import _csr, _say, assert_parity
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _star(n, center, leaves):
+    leaves = np.asarray(leaves, np.int32)
+    return np.full(leaves.shape[0], center, np.int32), leaves, n
+
+
+CSR_TILE = 4096  # row ends plus entries per workgroup
+CSR_CASES = {
+    # n + entries at a tile, one short and one past it (upper triangle only)
+    "full_tile": lambda: _star(CSR_TILE - 100, 7, np.arange(8, 108)),
+    "one_short": lambda: _star(CSR_TILE - 100, 7, np.arange(8, 107)),
+    "one_past": lambda: _star(CSR_TILE - 100, 7, np.arange(8, 109)),
+    # a row over several tiles whose neighbours lie below and above it
+    "hub": lambda: _star(3 * CSR_TILE, 5000, np.setdiff1d(np.arange(3 * CSR_TILE), [5000])),
+    # whole tiles of empty rows before, between and after the edges
+    "empty_runs": lambda: (np.array([9000, 9000, 9001, 20000, 20000, 20001], np.int32),
+                           np.array([9001, 9002, 9002, 20001, 29000, 29000], np.int32), 40000),
+    "no_edges": lambda: (np.zeros(0, np.int32), np.zeros(0, np.int32), 2 * CSR_TILE),
+    "skewed": lambda: gg.rmat(13, 16, seed=8),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CSR_CASES))
+def test_simple_sorted_csr_tiles(tclib, name):
+    src, dst, n = CSR_CASES[name]()
+    ref = native.o2_paper(src, dst, n)
+    sym = _csr(np.concatenate([ref.eu, ref.ev]), np.concatenate([ref.ev, ref.eu]), n)
+    for form, (rp, col) in (("symmetric", sym), ("upper", _csr(ref.eu, ref.ev, n))):
+        _say("simple sorted CSR tiles", name, form, "n", n, "entries", col.shape[0])
+        g = tclib.Graph.from_csr(torch.as_tensor(rp).cuda(), torch.as_tensor(col).cuda(), n,
+                                 assume_simple_sorted=True)
+        st = g.compute()
+        res = g.results()
+        res["eu"], res["ev"] = g.edges()
+        res["status"], res["m"] = st, g.m
+        g.close()
+        assert_parity(res, ref)
