@@ -53,3 +53,30 @@ def test_simple_sorted_csr_tiles(tclib, name):
         res["status"], res["m"] = st, g.m
         g.close()
         assert_parity(res, ref)
+
+
+ID_TILE = 4096  # sorted ids per workgroup of the deduplication
+RELABEL_CASES = {
+    "one_id": lambda rng: np.full(2 * 70, 123456789, np.int64),
+    "full_tile": lambda rng: rng.permutation(ID_TILE).astype(np.int64) * 3,
+    "past_tile": lambda rng: rng.permutation(ID_TILE + 2).astype(np.int64) * 3,
+    "two_tiles_repeats": lambda rng: rng.integers(5, 9, 2 * ID_TILE),
+    # the whole range of an id, and all but one id in a single bucket
+    "extremes": lambda rng: np.concatenate([np.array([0, 2**63 - 1], np.int64),
+                                            rng.integers(0, 2**63 - 1, 998)]),
+    "clustered": lambda rng: np.concatenate([np.array([2**62], np.int64),
+                                             rng.integers(0, 5000, 9999)]),
+}
+
+
+@pytest.mark.parametrize("name", sorted(RELABEL_CASES))
+def test_relabel_tiles_and_ranges(tclib, name):
+    ids = RELABEL_CASES[name](np.random.default_rng(11))
+    src, dst = ids[::2].copy(), ids[1::2].copy()
+    _say("relabel tiles", name, "pairs", src.shape[0])
+    s32, d32, got, n = tclib.relabel(src, dst)
+    want = np.unique(ids)
+    assert n == want.shape[0]
+    np.testing.assert_array_equal(got, want)
+    np.testing.assert_array_equal(s32, np.searchsorted(want, src))
+    np.testing.assert_array_equal(d32, np.searchsorted(want, dst))
