@@ -213,6 +213,13 @@ tc_status tc_ensure_symmetric(tc_graph *g, hipStream_t s);
 // Frees lt_key / lt_val (no-op when gone).  tc_build.hip.
 void tc_release_transposition(tc_graph *g, hipStream_t s);
 tc_status tc_alg_numerator(const tc_graph *g, uint64_t *d_num, hipStream_t s);  // tc_algebraic.hip
+// The k <= TOPK_SELECT_MAX largest of tcv[n] (ties by smaller index) into host
+// arrays; *found is false, and nothing is written, when more than TOPK_CAP
+// values tie around the k-th.  Waits for the stream.  tc_topk.hip.
+constexpr uint32_t TOPK_CAP = 4096;
+constexpr int32_t TOPK_SELECT_MAX = 1024;
+tc_status tc_topk_select(const double *tcv, int32_t n, int32_t k, int32_t *h_verts, double *h_vals,
+                         bool *found, hipStream_t s);
 tc_status tc_work_stats(tc_graph *g, int64_t *stats, hipStream_t s);
 tc_status tc_mid_prepare(tc_graph *g, hipStream_t s);
 tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,

@@ -80,3 +80,37 @@ def test_relabel_tiles_and_ranges(tclib, name):
     np.testing.assert_array_equal(got, want)
     np.testing.assert_array_equal(s32, np.searchsorted(want, src))
     np.testing.assert_array_equal(d32, np.searchsorted(want, dst))
+
+
+def _rank(tcv, k):
+    """The oracle's ranking: value descending, then smaller id."""
+    order = np.lexsort((np.arange(tcv.shape[0]), -tcv))[:k]
+    return order.astype(np.int32), tcv[order]
+
+
+TOPK_GRAPHS = {
+    "rmat_s14": lambda: gg.rmat(14, 16, seed=5),
+    # many equal values: 1200 copies of K5 (6000 ties), and 500 (2500)
+    "ties_above_cap": lambda: gg.disjoint_cliques(1200, 5),
+    "ties_below_cap": lambda: gg.disjoint_cliques(500, 5),
+    "all_zero": lambda: (np.arange(0, 9999, dtype=np.int32), np.arange(1, 10000, dtype=np.int32),
+                         10000),
+    "one_vertex_more": lambda: gg.ba(4097, 4, seed=3),
+    "tiny": lambda: gg.clique(3),
+}
+
+
+@pytest.mark.parametrize("name", sorted(TOPK_GRAPHS))
+def test_top_k_selection(tclib, name):
+    src, dst, n = TOPK_GRAPHS[name]()
+    ref = native.o2_paper(src, dst, n)
+    g = tclib.Graph.from_edges(src, dst, n)
+    g.compute()
+    for k in (1, 2, 10, 1000, 1024, 1025, n):  # selection up to 1024, sort above
+        k = min(k, n)
+        _say("top k", name, "k", k, "n", n)
+        verts, vals = g.top_k(k)
+        want_v, want = _rank(ref.tc, k)
+        np.testing.assert_array_equal(verts, want_v)
+        np.testing.assert_array_equal(vals.view(np.uint64), want.view(np.uint64))
+    g.close()
