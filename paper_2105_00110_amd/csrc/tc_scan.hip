@@ -1,9 +1,18 @@
-// Device-wide exclusive prefix sum (reduce-then-scan).
+// Device-wide exclusive prefix sum.
 //
-// Tiles of TILE = BLOCK*ITEMS elements: one kernel reduces every tile, the
-// tile totals are scanned recursively, and a second kernel rescans each
-// tile in LDS and adds its tile offset.  Loads and stores are coalesced
-// (striped through LDS); each thread scans ITEMS consecutive elements.
+// Up to ONE_MAX elements one workgroup scans everything: one launch.  Above,
+// reduce-then-scan over tiles of TILE = BLOCK*ITEMS elements: one kernel
+// reduces every tile, and a second one rescans each tile in LDS and adds the
+// sum of the tiles before it, which every workgroup takes from the tile sums
+// itself (a few KB out of the L2): two launches.  Only above PARTIAL_MAX tiles
+// are the tile sums scanned by a launch of their own first.  Loads and stores
+// are coalesced (striped through LDS); each thread scans ITEMS consecutive
+// elements.
+//
+// The graph build makes some twenty scans of mostly under a million elements,
+// so their launches cost more than their bytes: three launches and more for
+// each of them were 90 of the 206 launches and 0.40 ms of an R-MAT scale-20
+// call.
 #include "tc_internal.h"
 
 namespace {
@@ -12,6 +21,10 @@ constexpr int SCAN_BLOCK = 256;
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = SCAN_BLOCK * SCAN_ITEMS;
 constexpr int SCAN_WAVES = SCAN_BLOCK / TC_WAVE;
+constexpr int ONE_BLOCK = 1024;
+constexpr int ONE_ITEMS = 8;
+constexpr int64_t ONE_MAX = 2 * ONE_BLOCK * ONE_ITEMS;  // two rounds of one workgroup
+constexpr int64_t PARTIAL_MAX = 4096;
 
 template <typename T>
 __device__ T block_sum(T x, T *red) {
@@ -40,9 +53,47 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_tile_reduce(const T *__restrict_
     if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
-// Exclusive scan of one tile; tile_off (may be null) holds scanned tile
-// offsets.  The block that owns the last element writes the grand total.
+// Exclusive scan by one workgroup, ONE_BLOCK * ONE_ITEMS elements a round.
 template <typename T>
+__global__ __launch_bounds__(ONE_BLOCK) void k_scan_one(const T *in, T *out, int64_t n, T *total) {
+    constexpr int W = ONE_BLOCK / TC_WAVE;
+    __shared__ T wsum[W];
+    const int tid = threadIdx.x, w = tid / TC_WAVE;
+    T carry = 0;
+    for (int64_t base = 0; base < n; base += ONE_BLOCK * ONE_ITEMS) {
+        const int64_t i0 = base + (int64_t)tid * ONE_ITEMS;
+        T v[ONE_ITEMS], run = 0;
+#pragma unroll
+        for (int k = 0; k < ONE_ITEMS; ++k) v[k] = i0 + k < n ? in[i0 + k] : (T)0;
+#pragma unroll
+        for (int k = 0; k < ONE_ITEMS; ++k) {
+            const T x = v[k];
+            v[k] = run;
+            run += x;
+        }
+        const T incl = tc_wave_incl_scan(run);
+        if (__lane_id() == TC_WAVE - 1) wsum[w] = incl;
+        __syncthreads();
+        T before = carry + incl - run, all = 0;
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            const T x = wsum[q];
+            before += q < w ? x : (T)0;
+            all += x;
+        }
+#pragma unroll
+        for (int k = 0; k < ONE_ITEMS; ++k)
+            if (i0 + k < n) out[i0 + k] = v[k] + before;
+        carry += all;
+        __syncthreads();
+    }
+    if (total != nullptr && tid == 0) *total = carry;
+}
+
+// Exclusive scan of one tile.  tile_off holds the tile sums (SUMMED false:
+// the workgroup adds those before its own) or their exclusive scan (SUMMED
+// true).  The block that owns the last element writes the grand total.
+template <typename T, bool SUMMED>
 __global__ __launch_bounds__(SCAN_BLOCK) void k_tile_scan(const T *in, T *out, int64_t n,
                                                           const T *__restrict__ tile_off,
                                                           T *total) {
@@ -70,8 +121,14 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_tile_scan(const T *in, T *out, i
     __syncthreads();
     T before = incl - run;
     for (int i = 0; i < w; ++i) before += wsum[i];
-    T off = tile_off ? tile_off[blockIdx.x] : (T)0;
-    before += off;
+    if constexpr (SUMMED) {
+        before += tile_off[blockIdx.x];
+    } else {
+        T acc = 0;
+        for (unsigned i = tid; i < blockIdx.x; i += SCAN_BLOCK) acc += tile_off[i];
+        __shared__ T red[SCAN_WAVES];
+        before += block_sum(acc, red);
+    }
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; ++k) buf[tid * SCAN_ITEMS + k] = v[k] + before;
     if (total != nullptr && tid == SCAN_BLOCK - 1 && base + SCAN_TILE >= n) {
@@ -99,20 +156,24 @@ tc_status scan_impl(const T *in, T *out, int64_t n, T *total, hipStream_t s) {
         }
         return TC_OK;
     }
-    int64_t tiles = tc_div_up(n, SCAN_TILE);
-    if (tiles == 1) {
-        k_tile_scan<T><<<1, SCAN_BLOCK, 0, s>>>(in, out, n, nullptr, total);
+    if (n <= ONE_MAX) {
+        k_scan_one<T><<<1, ONE_BLOCK, 0, s>>>(in, out, n, total);
         TC_LAUNCHED();
         return TC_OK;
     }
+    int64_t tiles = tc_div_up(n, SCAN_TILE);
     if (tiles > 0x7FFFFFFF) return TC_ERR_UNSUPPORTED;
     tc_scratch tmp(s);
     T *partial = nullptr;
     TC_TRY(tmp.get(&partial, tiles));
     k_tile_reduce<T><<<(unsigned)tiles, SCAN_BLOCK, 0, s>>>(in, n, partial);
     TC_LAUNCHED();
-    TC_TRY(scan_impl<T>(partial, partial, tiles, (T *)nullptr, s));
-    k_tile_scan<T><<<(unsigned)tiles, SCAN_BLOCK, 0, s>>>(in, out, n, partial, total);
+    if (tiles <= PARTIAL_MAX) {
+        k_tile_scan<T, false><<<(unsigned)tiles, SCAN_BLOCK, 0, s>>>(in, out, n, partial, total);
+    } else {
+        TC_TRY(scan_impl<T>(partial, partial, tiles, (T *)nullptr, s));
+        k_tile_scan<T, true><<<(unsigned)tiles, SCAN_BLOCK, 0, s>>>(in, out, n, partial, total);
+    }
     TC_LAUNCHED();
     return TC_OK;
 }

@@ -3,10 +3,16 @@
 // Per digit pass (reduce-then-scan form):
 //   k_radix_hist    each tile of TILE keys counts its 256 digits in LDS and
 //                   writes them digit-major: counts[d * tiles + tile];
-//   tc_scan_u32     exclusive scan of the counts gives, for every (digit,
-//                   tile), the first output position of that tile's keys
-//                   with that digit (smaller digits first, then earlier
-//                   tiles: this is what makes the pass stable);
+//   k_radix_rows    one workgroup per digit scans the digit's counts over
+//                   the tiles and keeps their total; with the totals of the
+//                   smaller digits this gives, for every (digit, tile), the
+//                   first output position of that tile's keys with that
+//                   digit (smaller digits first, then earlier tiles: this
+//                   is what makes the pass stable).  Up to FEW_TILES tiles
+//                   there is no such launch: the counts are written
+//                   tile-major and every workgroup of the scatter sums the
+//                   few rows before its own (a general scan of the counts
+//                   took two to five launches);
 //   k_radix_scatter every wavefront ranks its keys with 8 ballots per item
 //                   (lanes holding the same digit form a 64-bit peer mask;
 //                   the rank is the popcount of lower peers plus the
@@ -37,12 +43,16 @@ constexpr int sort_items() {
 // thread (tiles of 2048) instead.
 constexpr int64_t SORT_BIG_TILES_MIN = (int64_t)1 << 22;
 constexpr int SORT_SMALL_ITEMS = 8;
+// Up to this many tiles the scatter sums the tile counts itself: at 128 tiles
+// (2^18 keys) that is 128 KB out of the L2 per workgroup, about the time of
+// the launch that it saves.
+constexpr int64_t FEW_TILES = 128;
 
 static_assert(SORT_BLOCK == RADIX, "one digit per thread in the scatter's digit scans");
 
 struct NoVal {};
 
-template <typename K, int SORT_ITEMS>
+template <typename K, int SORT_ITEMS, bool FEW>
 __global__ __launch_bounds__(SORT_BLOCK) void k_radix_hist(const K *__restrict__ keys, int64_t n,
                                                            int shift, uint32_t *__restrict__ counts,
                                                            int64_t tiles) {
@@ -62,15 +72,72 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_radix_hist(const K *__restrict__
         uint32_t c = 0;
 #pragma unroll
         for (int q = 0; q < SORT_WAVES; ++q) c += hist[q][d];
-        counts[(int64_t)d * tiles + blockIdx.x] = c;
+        if constexpr (FEW) counts[(int64_t)blockIdx.x * RADIX + d] = c;
+        else counts[(int64_t)d * tiles + blockIdx.x] = c;
     }
 }
 
-template <typename K, typename V, bool HAS_VAL, int SORT_ITEMS>
+// Exclusive scan of one digit's counts over the tiles, in place; tot[digit] =
+// their sum.  Bound by the round trip of a round (4 KB a workgroup), so a
+// thread takes four counts at a time.
+constexpr int ROWS_BLOCK = 1024;
+constexpr int ROWS_ITEMS = 4;
+
+__global__ __launch_bounds__(ROWS_BLOCK) void k_radix_rows(uint32_t *__restrict__ counts,
+                                                           int64_t tiles,
+                                                           uint32_t *__restrict__ tot) {
+    constexpr int W = ROWS_BLOCK / TC_WAVE;
+    __shared__ uint32_t wsum[W];
+    uint32_t *row = counts + (int64_t)blockIdx.x * tiles;
+    const int tid = threadIdx.x, w = tid / TC_WAVE;
+    uint32_t carry = 0;
+    for (int64_t base = 0; base < tiles; base += ROWS_BLOCK * ROWS_ITEMS) {
+        const int64_t i0 = base + (int64_t)tid * ROWS_ITEMS;
+        uint32_t v[ROWS_ITEMS], run = 0;
+#pragma unroll
+        for (int k = 0; k < ROWS_ITEMS; ++k) v[k] = i0 + k < tiles ? row[i0 + k] : 0u;
+#pragma unroll
+        for (int k = 0; k < ROWS_ITEMS; ++k) {
+            const uint32_t x = v[k];
+            v[k] = run;
+            run += x;
+        }
+        const uint32_t incl = tc_wave_incl_scan(run);
+        if (__lane_id() == TC_WAVE - 1) wsum[w] = incl;
+        __syncthreads();
+        uint32_t before = carry + incl - run, all = 0;
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            const uint32_t x = wsum[q];
+            before += q < w ? x : 0u;
+            all += x;
+        }
+#pragma unroll
+        for (int k = 0; k < ROWS_ITEMS; ++k)
+            if (i0 + k < tiles) row[i0 + k] = v[k] + before;
+        carry += all;
+        __syncthreads();
+    }
+    if (tid == 0) tot[blockIdx.x] = carry;
+}
+
+// Exclusive scan over the workgroup of one value per thread (digit).
+__device__ __forceinline__ uint32_t digit_scan(uint32_t x, uint32_t *wsum) {
+    const int w = threadIdx.x / TC_WAVE;
+    const uint32_t incl = tc_wave_incl_scan(x);
+    if (__lane_id() == TC_WAVE - 1) wsum[w] = incl;
+    __syncthreads();
+    uint32_t before = incl - x;
+    for (int q = 0; q < w; ++q) before += wsum[q];
+    __syncthreads();
+    return before;
+}
+
+template <typename K, typename V, bool HAS_VAL, int SORT_ITEMS, bool FEW>
 __global__ __launch_bounds__(SORT_BLOCK) void k_radix_scatter(
     const K *__restrict__ kin, const V *__restrict__ vin, K *__restrict__ kout,
-    V *__restrict__ vout, int64_t n, int shift, const uint32_t *__restrict__ offsets,
-    int64_t tiles, const uint32_t *__restrict__ vhi) {
+    V *__restrict__ vout, int64_t n, int shift, const uint32_t *__restrict__ counts,
+    int64_t tiles, const uint32_t *__restrict__ tot, const uint32_t *__restrict__ vhi) {
     constexpr int SORT_TILE = SORT_BLOCK * SORT_ITEMS;
     // The tile is first put in digit order in LDS, then written out by
     // consecutive threads to consecutive positions of each digit's run, so
@@ -140,8 +207,9 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_radix_scatter(
     }
     __syncthreads();
     // per digit: offsets of the waves, the tile total, and the global base
-    uint32_t tot = 0;
+    uint32_t tile_tot = 0;
     {
+        __shared__ uint32_t wsum[SORT_WAVES];
         const int d = threadIdx.x;  // SORT_BLOCK == RADIX
         uint32_t run = 0;
 #pragma unroll
@@ -150,18 +218,24 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_radix_scatter(
             wcnt[q][d] = run;
             run += c;
         }
-        tot = run;
-        gbase[d] = offsets[(int64_t)d * tiles + blockIdx.x];
-    }
-    // exclusive scan of the digit totals over the workgroup (one digit per thread)
-    {
-        const uint32_t incl = tc_wave_incl_scan(tot);
-        __shared__ uint32_t wsum[SORT_WAVES];
-        if (lane == TC_WAVE - 1) wsum[w] = incl;
-        __syncthreads();
-        uint32_t before = incl - tot;
-        for (int q = 0; q < w; ++q) before += wsum[q];
-        lbase[threadIdx.x] = before;
+        tile_tot = run;
+        // keys of this digit in all tiles, and in those before this one
+        uint32_t all = 0, before = 0;
+        if constexpr (FEW) {
+            const int nt = (int)tiles;
+#pragma unroll 16
+            for (int t = 0; t < nt; ++t) {
+                const uint32_t c = counts[t * RADIX + d];
+                all += c;
+                before += t < (int)blockIdx.x ? c : 0u;
+            }
+        } else {
+            all = tot[d];
+            before = counts[(int64_t)d * tiles + blockIdx.x];
+        }
+        gbase[d] = digit_scan(all, wsum) + before;
+        // start of the digit within the tile
+        lbase[d] = digit_scan(tile_tot, wsum);
     }
     __syncthreads();
     // place of each item in the tile's digit order
@@ -199,16 +273,41 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_radix_scatter(
     }
 }
 
-template <typename K, typename V, bool HAS_VAL, int ITEMS>
-tc_status radix_pass(const K *in, const V *vin, K *kout, V *vout, int64_t n, int shift,
-                     uint32_t *counts, int64_t tiles, const uint32_t *vhi, hipStream_t s) {
-    k_radix_hist<K, ITEMS><<<(unsigned)tiles, SORT_BLOCK, 0, s>>>(in, n, shift, counts, tiles);
+// counts: tiles * RADIX words, then the RADIX digit totals
+template <typename K, typename V, bool HAS_VAL, int ITEMS, bool FEW>
+tc_status radix_pass_form(const K *in, const V *vin, K *kout, V *vout, int64_t n, int shift,
+                          uint32_t *counts, int64_t tiles, const uint32_t *vhi, hipStream_t s) {
+    uint32_t *tot = counts + tiles * RADIX;
+    k_radix_hist<K, ITEMS, FEW><<<(unsigned)tiles, SORT_BLOCK, 0, s>>>(in, n, shift, counts, tiles);
     TC_LAUNCHED();
-    TC_TRY(tc_scan_u32(counts, counts, tiles * RADIX, nullptr, s));
-    k_radix_scatter<K, V, HAS_VAL, ITEMS><<<(unsigned)tiles, SORT_BLOCK, 0, s>>>(
-        in, vin, kout, vout, n, shift, counts, tiles, vhi);
+    if constexpr (!FEW) {
+        k_radix_rows<<<RADIX, ROWS_BLOCK, 0, s>>>(counts, tiles, tot);
+        TC_LAUNCHED();
+    }
+    k_radix_scatter<K, V, HAS_VAL, ITEMS, FEW><<<(unsigned)tiles, SORT_BLOCK, 0, s>>>(
+        in, vin, kout, vout, n, shift, counts, tiles, tot, vhi);
     TC_LAUNCHED();
     return TC_OK;
+}
+
+// One pass of n >= 1 elements; counts holds (tiles + 1) * RADIX words.
+template <typename K, typename V, bool HAS_VAL>
+tc_status radix_pass(const K *in, const V *vin, K *kout, V *vout, int64_t n, int shift,
+                     uint32_t *counts, int64_t tiles, const uint32_t *vhi, hipStream_t s) {
+    if (tiles <= FEW_TILES && n < SORT_BIG_TILES_MIN)
+        return radix_pass_form<K, V, HAS_VAL, SORT_SMALL_ITEMS, true>(in, vin, kout, vout, n, shift,
+                                                                     counts, tiles, vhi, s);
+    if (n < SORT_BIG_TILES_MIN)
+        return radix_pass_form<K, V, HAS_VAL, SORT_SMALL_ITEMS, false>(in, vin, kout, vout, n, shift,
+                                                                      counts, tiles, vhi, s);
+    return radix_pass_form<K, V, HAS_VAL, sort_items<K, V, HAS_VAL>(), false>(
+        in, vin, kout, vout, n, shift, counts, tiles, vhi, s);
+}
+
+template <typename K, typename V, bool HAS_VAL>
+int64_t sort_tiles(int64_t n) {
+    const int items = n >= SORT_BIG_TILES_MIN ? sort_items<K, V, HAS_VAL>() : SORT_SMALL_ITEMS;
+    return tc_div_up(n, (int64_t)SORT_BLOCK * items);
 }
 
 // src, when given, is read by the first pass in place of *keys (which then
@@ -224,24 +323,16 @@ tc_status radix_sort(K **keys, V **vals, K **tkeys, V **tvals, int64_t n, int bi
     if (n == 0 || (!fresh && (n <= 1 || bits == 0))) return TC_OK;
     if (fresh && bits == 0) bits = 1;  // keys below 2^0 are all zero: one pass keeps the order
     if (n >= (int64_t)0xFFFFFFFFll) return TC_ERR_UNSUPPORTED;
-    constexpr int ITEMS = sort_items<K, V, HAS_VAL>();
-    const bool big = n >= SORT_BIG_TILES_MIN;
-    int64_t tiles = tc_div_up(n, (int64_t)SORT_BLOCK * (big ? ITEMS : SORT_SMALL_ITEMS));
+    const int64_t tiles = sort_tiles<K, V, HAS_VAL>(n);
     tc_scratch tmp(s);
     uint32_t *counts = nullptr;
-    TC_TRY(tmp.get(&counts, tiles * RADIX));
+    TC_TRY(tmp.get(&counts, (tiles + 1) * RADIX));
     for (int shift = 0; shift < bits; shift += RB) {
         const K *in = (src && shift == 0) ? src : *keys;
         const V *vin = (HAS_VAL && !(iota && shift == 0)) ? *vals : nullptr;
         V *vout = HAS_VAL ? *tvals : nullptr;
         const uint32_t *vh = shift == 0 ? vhi : nullptr;
-        if (big)
-            TC_TRY((radix_pass<K, V, HAS_VAL, ITEMS>(in, vin, *tkeys, vout, n, shift, counts, tiles,
-                                                     vh, s)));
-        else
-            TC_TRY((radix_pass<K, V, HAS_VAL, SORT_SMALL_ITEMS>(in, vin, *tkeys, vout, n, shift,
-                                                                counts, tiles, vh, s)));
-        TC_LAUNCHED();
+        TC_TRY((radix_pass<K, V, HAS_VAL>(in, vin, *tkeys, vout, n, shift, counts, tiles, vh, s)));
         K *tk = *keys;
         *keys = *tkeys;
         *tkeys = tk;
@@ -286,17 +377,12 @@ tc_status tc_partition_u32_u32(const uint32_t *keys, const uint32_t *vals, uint3
     if (n < 0 || shift < 0 || shift > 24) return TC_ERR_INVALID_ARG;
     if (n == 0) return TC_OK;
     if (n >= (int64_t)0xFFFFFFFFll) return TC_ERR_UNSUPPORTED;
-    constexpr int ITEMS = sort_items<uint32_t, uint32_t, true>();
-    const bool big = n >= SORT_BIG_TILES_MIN;
-    const int64_t tiles = tc_div_up(n, (int64_t)SORT_BLOCK * (big ? ITEMS : SORT_SMALL_ITEMS));
+    const int64_t tiles = sort_tiles<uint32_t, uint32_t, true>(n);
     tc_scratch tmp(s);
     uint32_t *counts = nullptr;
-    TC_TRY(tmp.get(&counts, tiles * RADIX));
-    if (big)
-        return radix_pass<uint32_t, uint32_t, true, ITEMS>(keys, vals, keys_out, vals_out, n, shift,
-                                                           counts, tiles, nullptr, s);
-    return radix_pass<uint32_t, uint32_t, true, SORT_SMALL_ITEMS>(keys, vals, keys_out, vals_out, n,
-                                                                  shift, counts, tiles, nullptr, s);
+    TC_TRY(tmp.get(&counts, (tiles + 1) * RADIX));
+    return radix_pass<uint32_t, uint32_t, true>(keys, vals, keys_out, vals_out, n, shift, counts,
+                                                tiles, nullptr, s);
 }
 
 tc_status tc_sort_u32_u32(uint32_t **keys, uint32_t **vals, uint32_t **tmp_keys,

@@ -10,7 +10,7 @@ import pytest
 
 from oracle import native
 from paper_2105_00110_amd import graphgen as gg
-from tests.test_gpu_parity import _csr, _say, assert_parity
+from tests.test_gpu_parity import _csr, _say, assert_parity, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -114,3 +114,29 @@ def test_top_k_selection(tclib, name):
         np.testing.assert_array_equal(verts, want_v)
         np.testing.assert_array_equal(vals.view(np.uint64), want.view(np.uint64))
     g.close()
+
+
+# ids per sort: the last size whose tile counts the scatter sums itself, one
+# tile more, and both sides of the big tiles
+@pytest.mark.parametrize("count", [2048, 128 * 2048, 128 * 2048 + 2, (1 << 22) - 2, 1 << 22])
+def test_sort_tile_forms(tclib, count):
+    ids = np.random.default_rng(13).integers(0, 1 << 34, count)
+    src, dst = ids[::2].copy(), ids[1::2].copy()
+    _say("sort tile forms", count)
+    s32, d32, got, n = tclib.relabel(src, dst)
+    want = np.unique(ids)
+    assert n == want.shape[0]
+    np.testing.assert_array_equal(got, want)
+    np.testing.assert_array_equal(s32, np.searchsorted(want, src))
+    np.testing.assert_array_equal(d32, np.searchsorted(want, dst))
+
+
+# vertices per scan: one round and two of the single workgroup, then tiles
+@pytest.mark.parametrize("n", [8192, 8193, 16384, 16385, 5 * 4096 + 1])
+def test_scan_forms(tclib, n):
+    src, dst, _ = gg.er(n, 12.0 / n, seed=n)
+    # a triangle on the last vertices: their rows end every scan
+    src = np.concatenate([src, np.array([n - 1, n - 2, n - 3], np.int32)])
+    dst = np.concatenate([dst, np.array([n - 2, n - 3, n - 1], np.int32)])
+    _say("scan forms, n", n)
+    assert_parity(run_gpu(tclib, src, dst, n), native.o2_paper(src, dst, n))
