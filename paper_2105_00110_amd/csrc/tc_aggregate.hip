@@ -454,8 +454,7 @@ tc_status tc_aggregate(tc_graph *g, hipStream_t s) {
     k_big_write<<<grid_for(n), BK, 0, s>>>(n, g->row_ptr, pos, big);
     TC_LAUNCHED();
     uint32_t hbig = 0;
-    TC_HIP(hipMemcpyAsync(&hbig, tot, 4, hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{&hbig, tot, 1}}, s));
     const int64_t nbig = hbig;
 
     if (m > 0) {
@@ -516,8 +515,7 @@ static tc_status aggregate_rank_space(tc_graph *g, hipStream_t s) {
     TC_TRY(tc_scan_u32(cnt, off, n, tot, s));
     TC_TRY(support_to_edge_order(g, s));
     uint32_t hch = 0;
-    TC_HIP(hipMemcpyAsync(&hch, tot, 4, hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{&hch, tot, 1}}, s));
     const int64_t nchunk = hch;
     uint64_t *chunk = nullptr, *part = nullptr;
     TC_TRY(tmp.get(&chunk, nchunk > 0 ? nchunk : 1));

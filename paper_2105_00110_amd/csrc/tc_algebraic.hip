@@ -147,8 +147,7 @@ tc_status tc_alg_numerator(const tc_graph *g, uint64_t *d_num, hipStream_t s) {
     k_alg_big_write<<<grid_for(n), BK, 0, s>>>(n, f, pos, big);
     TC_LAUNCHED();
     uint32_t hbig = 0;
-    TC_HIP(hipMemcpyAsync(&hbig, tot, 4, hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{&hbig, tot, 1}}, s));
     const unsigned grid = grid_for((int64_t)n * GS);
     const unsigned bgrid = hbig < 65536 ? (hbig > 0 ? hbig : 1) : 65536;
     k_alg_rows<1><<<grid, BK, 0, s>>>(n, g->row_ptr, g->col, tv, nullptr, t, err);
@@ -164,7 +163,6 @@ tc_status tc_alg_numerator(const tc_graph *g, uint64_t *d_num, hipStream_t s) {
         TC_LAUNCHED();
     }
     uint32_t herr = 0;
-    TC_HIP(hipMemcpyAsync(&herr, err, 4, hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{&herr, err, 1}}, s));
     return herr ? TC_ERR_DEVICE : TC_OK;
 }

@@ -915,8 +915,7 @@ tc_status tc_orient(tc_graph *g, hipStream_t s) {
     TC_LAUNCHED();
     TC_TRY(compact_vertices(n, flags2, list_big, info + 2, s));
     uint32_t h_info[4] = {0, 0, 0, 0};
-    TC_HIP(hipMemcpyAsync(h_info, info, 16, hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{h_info, info, 4}}, s));
     const uint32_t h_max = h_info[0];
     const int64_t nmid = h_info[1], nblk = h_info[2];
     g->max_dplus = (int32_t)h_max;
@@ -993,9 +992,7 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
         TC_LAUNCHED();
         TC_TRY(tc_scan_u32(cnt, cnt, tiles, d_m, s));
         uint32_t h_m = 0, h_err = 0;
-        TC_HIP(hipMemcpyAsync(&h_err, g->err, 4, hipMemcpyDeviceToHost, s));
-        TC_HIP(hipMemcpyAsync(&h_m, d_m, 4, hipMemcpyDeviceToHost, s));
-        TC_HIP(hipStreamSynchronize(s));
+        TC_TRY(tc_read({{&h_err, g->err, 1}, {&h_m, d_m, 1}}, s));
         if (h_err) return TC_ERR_INVALID_ARG;
         m = h_m;
         TC_TRY(tc_graph_alloc(g, &g->eu, m, s));
@@ -1026,9 +1023,7 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
         TC_LAUNCHED();
         TC_TRY(tc_scan_u32(tcnt, tcnt, tiles, d_m, s));
         uint32_t h_m = 0, h_err = 0;
-        TC_HIP(hipMemcpyAsync(&h_err, g->err, 4, hipMemcpyDeviceToHost, s));
-        TC_HIP(hipMemcpyAsync(&h_m, d_m, 4, hipMemcpyDeviceToHost, s));
-        TC_HIP(hipStreamSynchronize(s));
+        TC_TRY(tc_read({{&h_err, g->err, 1}, {&h_m, d_m, 1}}, s));
         if (h_err) return TC_ERR_VERTEX_RANGE;
         m = h_m;
         TC_TRY(tc_graph_alloc(g, &g->eu, m, s));

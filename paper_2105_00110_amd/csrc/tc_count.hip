@@ -373,8 +373,7 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     TC_TRY(select_rows(g, light_max + 1, huge_min - 1, heavy, cnt + 1, s));
     TC_TRY(select_rows(g, huge_min, 0x7FFFFFFF, huge, cnt + 2, s));
     uint32_t hc[4] = {0, 0, 0, 0};
-    TC_HIP(hipMemcpyAsync(hc, cnt, 12, hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{hc, cnt, 3}}, s));
     const int64_t nl = hc[0], nh = hc[1], nz = hc[2];
     g->n_light = nl;
     g->n_heavy = nh;

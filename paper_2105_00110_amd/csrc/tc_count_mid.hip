@@ -1424,8 +1424,7 @@ static tc_status bit_rows_prepare(tc_graph *g, hipStream_t s) {
     TC_LAUNCHED();
     TC_TRY(tc_scan_i64(len, g->rowbase, n, g->rowbase + n, s));
     int64_t words = 0;
-    TC_HIP(hipMemcpyAsync(&words, g->rowbase + n, 8, hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{&words, g->rowbase + n, 2}}, s));
     g->bit_words = words;
     // 4 words of padding: the fold's row sums read up to 3 words past a
     // row's end
@@ -1507,8 +1506,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
     if (g->bit_words > 0)
         for (int i = 0; i < 2; ++i) TC_TRY(rows_count(g, rp[i], tots + NPLANS + i, items, s));
     uint32_t h_tots[NPLANS + 2] = {};
-    TC_HIP(hipMemcpyAsync(h_tots, tots, sizeof(h_tots), hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{h_tots, tots, NPLANS + 2}}, s));
     for (int i = 0; i < NPLANS; ++i) {
         pl[i].count = h_tots[i];
         TC_TRY(plan_write(g, pl[i], items, s));
@@ -1680,8 +1678,7 @@ tc_status tc_mid_bit_words(const tc_graph *g, int64_t *words, hipStream_t s) {
         TC_LAUNCHED();
     }
     unsigned long long h = 0;
-    TC_HIP(hipMemcpyAsync(&h, d, 8, hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{&h, d, 2}}, s));
     *words = (int64_t)h;
     return TC_OK;
 }

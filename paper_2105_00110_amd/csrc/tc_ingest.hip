@@ -322,6 +322,7 @@ tc_status tc_relabel_ids(const int64_t *src, const int64_t *dst, int64_t num_pai
     if (num_pairs == 0) return TC_OK;
     if (2 * num_pairs >= (int64_t)0xFFFFFFFFll) return TC_ERR_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
+    tc_call_scope scope(s);
     const bool host = mem_kind == TC_MEM_HOST;
     const int64_t P = num_pairs, N2 = 2 * num_pairs;
     tc_scratch tmp(s);
@@ -346,8 +347,7 @@ tc_status tc_relabel_ids(const int64_t *src, const int64_t *dst, int64_t num_pai
         d_src, d_dst, P, range);
     TC_LAUNCHED();
     long long h_range[2] = {0, 0};
-    TC_HIP(hipMemcpyAsync(h_range, range, sizeof(h_range), hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{h_range, range, 4}}, s));
     const int64_t base = h_range[0];
     if (base < 0) return TC_ERR_VERTEX_RANGE;
     const int bits = tc_bits_for((uint64_t)(h_range[1] - base));
@@ -363,8 +363,7 @@ tc_status tc_relabel_ids(const int64_t *src, const int64_t *dst, int64_t num_pai
     TC_LAUNCHED();
     TC_TRY(tc_scan_u32(cnt, cnt, tiles, tot, s));
     uint32_t hn = 0;
-    TC_HIP(hipMemcpyAsync(&hn, tot, 4, hipMemcpyDeviceToHost, s));
-    TC_HIP(hipStreamSynchronize(s));
+    TC_TRY(tc_read({{&hn, tot, 1}}, s));
     if (hn > (uint32_t)INT32_MAX) return TC_ERR_UNSUPPORTED;
     TC_TRY(tmp.get(&uniq, hn));
     k_ids_unique<true><<<(unsigned)tiles, BK, 0, s>>>(keys, N2, base, nullptr, cnt, uniq);

@@ -48,7 +48,27 @@ static inline int tc_bits_for(uint64_t max_value) {
 // device bytes the library holds past it fails with TC_ERR_BUDGET.
 // ---------------------------------------------------------------------------
 tc_status tc_dev_alloc(void **p, size_t bytes, hipStream_t s);
-void tc_dev_free(void *p, hipStream_t s);
+// idle: no work that uses the block is pending on any stream
+void tc_dev_free(void *p, hipStream_t s, bool idle = false);
+
+// Lives through an entry point: the blocks that the thread frees meanwhile on
+// this stream share one event (tc_api.hip).
+struct tc_call_scope {
+    explicit tc_call_scope(hipStream_t s);
+    ~tc_call_scope();
+    tc_call_scope(const tc_call_scope &) = delete;
+    tc_call_scope &operator=(const tc_call_scope &) = delete;
+};
+
+// Reads words (32-bit, at most 64 in all) from device memory to the host and
+// waits for the stream.
+constexpr int TC_READ_MAX = 3;
+struct tc_read_item {
+    void *dst = nullptr;
+    const void *src = nullptr;
+    int words = 0;
+};
+tc_status tc_read(const tc_read_item (&item)[TC_READ_MAX], hipStream_t s);
 
 template <typename T>
 static inline tc_status tc_alloc(T **p, int64_t count, hipStream_t s) {
