@@ -98,12 +98,13 @@ __global__ void k_tri_small(int32_t n, const int64_t *__restrict__ row_ptr,
     }
 }
 
-__global__ void k_tri_big(const int32_t *__restrict__ big, int64_t nbig,
+__global__ void k_tri_big(const int32_t *__restrict__ big, const uint32_t *__restrict__ nbig,
                           const int64_t *__restrict__ row_ptr, const uint32_t *__restrict__ sym2e,
                           const uint32_t *__restrict__ esup, uint8_t *__restrict__ flag,
                           uint64_t *__restrict__ tri, uint32_t *__restrict__ err) {
     __shared__ uint64_t red[16];
-    for (int64_t i = blockIdx.x; i < nbig; i += gridDim.x) {
+    const int64_t count = *nbig;
+    for (int64_t i = blockIdx.x; i < count; i += gridDim.x) {
         const int32_t v = big[i];
         const int64_t b = row_ptr[v], e = row_ptr[v + 1];
         uint64_t acc = 0;
@@ -120,29 +121,44 @@ __global__ void k_tri_big(const int32_t *__restrict__ big, int64_t nbig,
     }
 }
 
-// Σ tri over each graph's vertex range (block-level pre-reduction when the
-// block's vertices lie in one graph).
-__global__ void k_tri_sum(int32_t n, const uint64_t *__restrict__ tri,
-                          const int64_t *__restrict__ vtx_off, int32_t G,
-                          unsigned long long *__restrict__ sums) {
-    __shared__ uint64_t red[16];
-    const int64_t per_block = (int64_t)blockDim.x * 8;
-    for (int64_t base = (int64_t)blockIdx.x * per_block; base < n; base += (int64_t)gridDim.x * per_block) {
-        int64_t last = base + per_block - 1;
-        if (last >= n) last = n - 1;
-        const int32_t g0 = vtx_off ? graph_of(vtx_off, G, base) : 0;
-        const int32_t g1 = vtx_off ? graph_of(vtx_off, G, last) : 0;
-        if (g0 == g1) {
-            uint64_t acc = 0;
-            for (int64_t v = base + threadIdx.x; v <= last; v += blockDim.x) acc += tri[v];
-            acc = block_sum(acc, red);
-            if (threadIdx.x == 0 && acc) atomicAdd(&sums[g0], (unsigned long long)acc);
-        } else {
-            for (int64_t v = base + threadIdx.x; v <= last; v += blockDim.x) {
-                uint64_t t = tri[v];
-                if (t) atomicAdd(&sums[graph_of(vtx_off, G, v)], (unsigned long long)t);
-            }
+// Σ tri over each graph's vertex range.  A bounded grid, each workgroup a
+// contiguous slice: one graph takes one atomic per workgroup (a workgroup per
+// 2048 vertices put 8192 on one word at R-MAT scale 24); in a batch each
+// wavefront adds its 64 vertices' sums per graph (an atomic per vertex where
+// a workgroup crossed graphs took 216 us for 1.8 M vertices in 512 graphs;
+// 26 us so).
+constexpr unsigned TRI_SUM_BLOCKS = 1024;
+
+__global__ __launch_bounds__(BK) void k_tri_sum(int32_t n, const uint64_t *__restrict__ tri,
+                                                const int64_t *__restrict__ vtx_off, int32_t G,
+                                                unsigned long long *__restrict__ sums) {
+    __shared__ uint64_t red[BK / TC_WAVE];
+    const int64_t per = tc_div_up(tc_div_up(n, gridDim.x), BK) * BK;
+    const int64_t a = (int64_t)blockIdx.x * per;
+    const int64_t b = a + per < n ? a + per : n;
+    if (!vtx_off) {
+        uint64_t acc = 0;
+        for (int64_t v = a + threadIdx.x; v < b; v += BK) acc += tri[v];
+        acc = block_sum(acc, red);
+        if (threadIdx.x == 0 && acc) atomicAdd(&sums[0], (unsigned long long)acc);
+        return;
+    }
+    for (int64_t v0 = a; v0 < b; v0 += BK) {  // every lane of a wavefront takes part
+        const int64_t v = v0 + threadIdx.x;
+        const bool valid = v < b;
+        const int32_t g = valid ? graph_of(vtx_off, G, v) : G;
+        uint64_t x = valid ? tri[v] : 0;
+        // sum of the lanes of one graph, at its last lane
+        const int lane = __lane_id();
+#pragma unroll
+        for (int off = 1; off < TC_WAVE; off <<= 1) {
+            const uint64_t y = __shfl_up(x, off, TC_WAVE);
+            const int32_t h = __shfl_up(g, off, TC_WAVE);
+            if (lane >= off && h == g) x += y;
         }
+        const int32_t next = __shfl_down(g, 1, TC_WAVE);
+        if (valid && x && (lane == TC_WAVE - 1 || next != g))
+            atomicAdd(&sums[g], (unsigned long long)x);
     }
 }
 
@@ -188,13 +204,14 @@ __global__ void k_num_small(int32_t n, const int64_t *__restrict__ row_ptr,
     }
 }
 
-__global__ void k_num_big(const int32_t *__restrict__ big, int64_t nbig,
+__global__ void k_num_big(const int32_t *__restrict__ big, const uint32_t *__restrict__ nbig,
                           const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
                           const uint8_t *__restrict__ flag, const uint64_t *__restrict__ tri,
                           const uint64_t *__restrict__ triG, const int64_t *__restrict__ vtx_off,
                           int32_t G, uint64_t *__restrict__ num, double *__restrict__ tcv) {
     __shared__ uint64_t red[16];
-    for (int64_t i = blockIdx.x; i < nbig; i += gridDim.x) {
+    const int64_t count = *nbig;
+    for (int64_t i = blockIdx.x; i < count; i += gridDim.x) {
         const int32_t v = big[i];
         const int64_t b = row_ptr[v], e = row_ptr[v + 1];
         uint64_t acc = 0;
@@ -335,9 +352,10 @@ __global__ void k_rank_rows(int32_t n, RankArgs q) {
 // chunk[c] = (row << 32) | index of the chunk within its row
 template <int PASS>
 __global__ __launch_bounds__(256) void k_rank_chunks(const uint64_t *__restrict__ chunk,
-                                                     int64_t nchunk, RankArgs q,
-                                                     uint64_t *__restrict__ part) {
+                                                     const uint32_t *__restrict__ chunk_count,
+                                                     RankArgs q, uint64_t *__restrict__ part) {
     __shared__ uint64_t red[4];
+    const int64_t nchunk = *chunk_count;
     for (int64_t c = blockIdx.x; c < nchunk; c += gridDim.x) {
         const uint64_t w = chunk[c];
         const int64_t r = (int64_t)(w >> 32);
@@ -353,8 +371,10 @@ __global__ __launch_bounds__(256) void k_rank_chunks(const uint64_t *__restrict_
 
 // The first chunk of each row adds the row's partial sums and finishes it.
 template <int PASS>
-__global__ void k_rank_chunks_finish(const uint64_t *__restrict__ chunk, int64_t nchunk,
+__global__ void k_rank_chunks_finish(const uint64_t *__restrict__ chunk,
+                                     const uint32_t *__restrict__ chunk_count,
                                      const uint64_t *__restrict__ part, RankArgs q) {
+    const int64_t nchunk = *chunk_count;
     GRID_STRIDE(c, nchunk) {
         const uint64_t w = chunk[c];
         if ((uint32_t)w != 0) continue;
@@ -367,29 +387,40 @@ __global__ void k_rank_chunks_finish(const uint64_t *__restrict__ chunk, int64_t
     }
 }
 
-__global__ void k_rank_chunk_count(int32_t n, const int64_t *__restrict__ orp,
-                                   const int64_t *__restrict__ in_ptr, uint32_t *__restrict__ cnt) {
-    GRID_STRIDE(r, n) {
-        const int64_t len = rank_row_len(orp, in_ptr, r);
-        cnt[r] = len > RANK_SMALL ? (uint32_t)tc_div_up(len, RANK_CHUNK) : 0u;
+// Lists the chunks of the rows above RANK_SMALL entries, a row's chunks in
+// order and side by side, a tile's rows in order (neighbouring ranks gather
+// from the same rows); *count their number.
+constexpr int RC_TILE = 2048;
+constexpr int64_t CHUNK_GRID = 65536;
+
+__global__ __launch_bounds__(BK) void k_rank_chunk_list(int32_t n, const int64_t *__restrict__ orp,
+                                                        const int64_t *__restrict__ in_ptr,
+                                                        uint32_t *__restrict__ count,
+                                                        uint64_t *__restrict__ chunk) {
+    constexpr int PER = RC_TILE / BK;
+    __shared__ uint32_t lds[BK / TC_WAVE + 1];
+    const int64_t base = (int64_t)blockIdx.x * RC_TILE;
+    uint32_t c[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int64_t r = base + threadIdx.x * PER + k;
+        const int64_t len = r < n ? rank_row_len(orp, in_ptr, r) : 0;
+        c[k] = len > RANK_SMALL ? (uint32_t)tc_div_up(len, RANK_CHUNK) : 0u;
+        sum += c[k];
+    }
+    if (!__syncthreads_or(sum != 0)) return;
+    uint32_t at = tc_block_reserve<BK>(sum, count, lds);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int64_t r = base + threadIdx.x * PER + k;
+        for (uint32_t j = 0; j < c[k]; ++j) chunk[at++] = ((uint64_t)r << 32) | j;
     }
 }
 
-__global__ void k_rank_chunk_write(int32_t n, const uint32_t *__restrict__ cnt,
-                                   const uint32_t *__restrict__ off, uint64_t *__restrict__ chunk) {
-    GRID_STRIDE(r, n) {
-        const uint32_t c = cnt[r];
-        for (uint32_t j = 0; j < c; ++j) chunk[off[r] + j] = ((uint64_t)r << 32) | j;
-    }
-}
-
-__global__ void k_big_flags(int32_t n, const int64_t *__restrict__ row_ptr, uint32_t *__restrict__ f) {
-    GRID_STRIDE(v, n) f[v] = (row_ptr[v + 1] - row_ptr[v]) > BIG_DEG ? 1u : 0u;
-}
-
-__global__ void k_big_write(int32_t n, const int64_t *__restrict__ row_ptr,
-                            const uint32_t *__restrict__ pos, int32_t *__restrict__ out) {
-    GRID_STRIDE(v, n) if ((row_ptr[v + 1] - row_ptr[v]) > BIG_DEG) out[pos[v]] = (int32_t)v;
+__global__ void k_big_rows(int32_t n, const int64_t *__restrict__ row_ptr,
+                           uint32_t *__restrict__ count, int32_t *__restrict__ out) {
+    GRID_STRIDE(v, n)
+        if ((row_ptr[v + 1] - row_ptr[v]) > BIG_DEG) out[atomicAdd(count, 1u)] = (int32_t)v;
 }
 
 }  // namespace
@@ -443,19 +474,20 @@ tc_status tc_aggregate(tc_graph *g, hipStream_t s) {
     }
 
     tc_scratch tmp(s);
-    uint32_t *pos = nullptr, *tot = nullptr;
+    // rows above BIG_DEG: the largest degree says whether there are any, and
+    // then at most 2m / BIG_DEG, listed in any order
+    const bool any_big = g->max_degree > BIG_DEG;
+    const int64_t cap = any_big ? 2 * m / BIG_DEG + 1 : 0;
+    uint32_t *nbig = nullptr;
     int32_t *big = nullptr;
-    TC_TRY(tmp.get(&pos, nn));
-    TC_TRY(tmp.get(&tot, 1));
-    TC_TRY(tmp.get(&big, nn));
-    k_big_flags<<<grid_for(n), BK, 0, s>>>(n, g->row_ptr, pos);
-    TC_LAUNCHED();
-    TC_TRY(tc_scan_u32(pos, pos, n, tot, s));
-    k_big_write<<<grid_for(n), BK, 0, s>>>(n, g->row_ptr, pos, big);
-    TC_LAUNCHED();
-    uint32_t hbig = 0;
-    TC_TRY(tc_read({{&hbig, tot, 1}}, s));
-    const int64_t nbig = hbig;
+    if (any_big) {
+        TC_TRY(tmp.get(&nbig, 1));
+        TC_TRY(tmp.get(&big, cap));
+        TC_HIP(hipMemsetAsync(nbig, 0, 4, s));
+        k_big_rows<<<grid_for(n), BK, 0, s>>>(n, g->row_ptr, nbig, big);
+        TC_LAUNCHED();
+    }
+    const unsigned big_grid = (unsigned)(cap < 1024 ? cap : 1024);
 
     if (m > 0) {
         k_scatter_sup<<<grid_for(m), BK, 0, s>>>(m, g->o2e, g->osup, g->esup);
@@ -464,12 +496,13 @@ tc_status tc_aggregate(tc_graph *g, hipStream_t s) {
     const unsigned small_grid = grid_for((int64_t)n * GS);
     k_tri_small<<<small_grid, BK, 0, s>>>(n, g->row_ptr, g->sym2e, g->esup, g->flag, g->tri, g->err);
     TC_LAUNCHED();
-    if (nbig > 0) {
-        k_tri_big<<<(unsigned)(nbig < 65536 ? nbig : 65536), 1024, 0, s>>>(
+    if (any_big) {
+        k_tri_big<<<big_grid, 1024, 0, s>>>(
             big, nbig, g->row_ptr, g->sym2e, g->esup, g->flag, g->tri, g->err);
         TC_LAUNCHED();
     }
-    k_tri_sum<<<grid_for(n, BK * 8), BK, 0, s>>>(n, g->tri, voff, G, (unsigned long long *)g->triG);
+    k_tri_sum<<<grid_for(n) < TRI_SUM_BLOCKS ? grid_for(n) : TRI_SUM_BLOCKS, BK, 0, s>>>(
+        n, g->tri, voff, G, (unsigned long long *)g->triG);
     TC_LAUNCHED();
     k_tri_finish<<<grid_for(G), BK, 0, s>>>(G, g->triG, g->err);
     TC_LAUNCHED();
@@ -477,8 +510,8 @@ tc_status tc_aggregate(tc_graph *g, hipStream_t s) {
     k_num_small<<<small_grid, BK, 0, s>>>(n, g->row_ptr, g->col, g->flag, g->tri, g->triG, voff, G,
                                           g->num, g->tcv);
     TC_LAUNCHED();
-    if (nbig > 0) {
-        k_num_big<<<(unsigned)(nbig < 65536 ? nbig : 65536), 1024, 0, s>>>(
+    if (any_big) {
+        k_num_big<<<big_grid, 1024, 0, s>>>(
             big, nbig, g->row_ptr, g->col, g->flag, g->tri, g->triG, voff, G, g->num, g->tcv);
         TC_LAUNCHED();
     }
@@ -503,40 +536,40 @@ static tc_status aggregate_rank_space(tc_graph *g, hipStream_t s) {
         return TC_OK;
     }
     tc_scratch tmp(s);
-    uint32_t *cnt = nullptr, *off = nullptr, *tot = nullptr, *in_uw = nullptr;
-    uint64_t *tri_r = nullptr;
+    uint32_t *in_uw = nullptr, *chunks = nullptr;
+    uint64_t *tri_r = nullptr, *chunk = nullptr, *part = nullptr;
     TC_TRY(tmp.get(&in_uw, m > 0 ? m : 1));
-    TC_TRY(tmp.get(&cnt, nn));
-    TC_TRY(tmp.get(&off, nn));
-    TC_TRY(tmp.get(&tot, 1));
     TC_TRY(tmp.get(&tri_r, nn));
-    k_rank_chunk_count<<<grid_for(n), BK, 0, s>>>(n, g->orp, g->in_ptr, cnt);
-    TC_LAUNCHED();
-    TC_TRY(tc_scan_u32(cnt, off, n, tot, s));
-    TC_TRY(support_to_edge_order(g, s));
-    uint32_t hch = 0;
-    TC_TRY(tc_read({{&hch, tot, 1}}, s));
-    const int64_t nchunk = hch;
-    uint64_t *chunk = nullptr, *part = nullptr;
-    TC_TRY(tmp.get(&chunk, nchunk > 0 ? nchunk : 1));
-    TC_TRY(tmp.get(&part, nchunk > 0 ? nchunk : 1));
-    if (nchunk > 0) {
-        k_rank_chunk_write<<<grid_for(n), BK, 0, s>>>(n, cnt, off, chunk);
+    // a row's entries are its degree: none above RANK_SMALL, no chunks; else
+    // at most this many, the number itself staying on the device
+    const bool any_chunk = g->max_degree > RANK_SMALL;
+    const int64_t cap =
+        any_chunk ? 2 * m / RANK_CHUNK + 2 * m / (RANK_SMALL + 1) + 1 : 0;
+    if (any_chunk) {
+        TC_TRY(tmp.get(&chunks, 1));
+        TC_TRY(tmp.get(&chunk, cap));
+        TC_TRY(tmp.get(&part, cap));
+        TC_HIP(hipMemsetAsync(chunks, 0, 4, s));
+        k_rank_chunk_list<<<(unsigned)tc_div_up(n, RC_TILE), BK, 0, s>>>(n, g->orp, g->in_ptr, chunks,
+                                                                        chunk);
         TC_LAUNCHED();
     }
+    TC_TRY(support_to_edge_order(g, s));
     RankArgs q{g->orp, g->ocol, g->in_ptr, g->in_pair, g->osup, in_uw, g->perm, tri_r,
                g->tri, nullptr, voff, G, nullptr, nullptr, g->err};
     const unsigned small_grid = grid_for((int64_t)n * GS);
-    const unsigned chunk_grid = (unsigned)(nchunk < 1048576 ? (nchunk > 0 ? nchunk : 1) : 1048576);
+    const unsigned chunk_grid = (unsigned)(cap < CHUNK_GRID ? cap : CHUNK_GRID);
+    const unsigned finish_grid = grid_for(cap) < 1024 ? grid_for(cap) : 1024;
     k_rank_rows<1><<<small_grid, BK, 0, s>>>(n, q);
     TC_LAUNCHED();
-    if (nchunk > 0) {
-        k_rank_chunks<1><<<chunk_grid, 256, 0, s>>>(chunk, nchunk, q, part);
+    if (any_chunk) {
+        k_rank_chunks<1><<<chunk_grid, 256, 0, s>>>(chunk, chunks, q, part);
         TC_LAUNCHED();
-        k_rank_chunks_finish<1><<<grid_for(nchunk), BK, 0, s>>>(chunk, nchunk, part, q);
+        k_rank_chunks_finish<1><<<finish_grid, BK, 0, s>>>(chunk, chunks, part, q);
         TC_LAUNCHED();
     }
-    k_tri_sum<<<grid_for(n, BK * 8), BK, 0, s>>>(n, g->tri, voff, G, (unsigned long long *)g->triG);
+    k_tri_sum<<<grid_for(n) < TRI_SUM_BLOCKS ? grid_for(n) : TRI_SUM_BLOCKS, BK, 0, s>>>(
+        n, g->tri, voff, G, (unsigned long long *)g->triG);
     TC_LAUNCHED();
     k_tri_finish<<<grid_for(G), BK, 0, s>>>(G, g->triG, g->err);
     TC_LAUNCHED();
@@ -546,10 +579,10 @@ static tc_status aggregate_rank_space(tc_graph *g, hipStream_t s) {
     q.tcv = g->tcv;
     k_rank_rows<2><<<small_grid, BK, 0, s>>>(n, q);
     TC_LAUNCHED();
-    if (nchunk > 0) {
-        k_rank_chunks<2><<<chunk_grid, 256, 0, s>>>(chunk, nchunk, q, part);
+    if (any_chunk) {
+        k_rank_chunks<2><<<chunk_grid, 256, 0, s>>>(chunk, chunks, q, part);
         TC_LAUNCHED();
-        k_rank_chunks_finish<2><<<grid_for(nchunk), BK, 0, s>>>(chunk, nchunk, part, q);
+        k_rank_chunks_finish<2><<<finish_grid, BK, 0, s>>>(chunk, chunks, part, q);
         TC_LAUNCHED();
     }
     tc_prof_mark(g, 11, s);

@@ -292,6 +292,7 @@ namespace {
 
 struct ReadArgs {
     const uint32_t *src[TC_READ_MAX];
+    int64_t step[TC_READ_MAX];
     int words[TC_READ_MAX];
 };
 constexpr int READ_WORDS = 64;
@@ -301,7 +302,8 @@ __global__ void k_read_words(ReadArgs a, uint32_t *out) {
 #pragma unroll
     for (int i = 0; i < TC_READ_MAX; ++i) {
         const int j = (int)threadIdx.x - at;
-        if (j >= 0 && j < a.words[i]) out[threadIdx.x] = a.src[i][j];
+        if (j >= 0 && j < a.words[i])
+            out[threadIdx.x] = a.src[i][a.step[i] ? 2 * a.step[i] * (j >> 1) + (j & 1) : j];
         at += a.words[i];
     }
 }
@@ -316,6 +318,7 @@ tc_status tc_read(const tc_read_item (&item)[TC_READ_MAX], hipStream_t s) {
     int total = 0;
     for (int i = 0; i < TC_READ_MAX; ++i) {
         a.src[i] = static_cast<const uint32_t *>(item[i].src);
+        a.step[i] = item[i].step;
         a.words[i] = item[i].words;
         total += item[i].words;
     }
@@ -433,8 +436,7 @@ tc_status copy_out(void *dst, const void *src, size_t bytes, int32_t mem_kind, h
 void free_graph_arrays(tc_graph *g, hipStream_t s) {
     void *arrs[] = {g->eu,   g->ev,   g->row_ptr, g->col,  g->sym2e, g->rank, g->perm,
                     g->orp,  g->ocol, g->o2e,     g->osup, g->esup,  g->flag, g->tri,
-                    g->num,  g->tcv,  g->triG,    g->vtx_off, g->err, g->bin_rows,
-                    g->in_ptr, g->in_pair, g->rowbase, g->hitbits, g->orow,
+                    g->num,  g->tcv,  g->triG,    g->vtx_off, g->err, g->in_ptr, g->in_pair, g->rowbase, g->hitbits, g->orow,
                     g->run_us, g->lt_key, g->lt_val, g->ocol16, g->rowinfo};
     for (void *p : arrs) tc_dev_free(p, s, true);
 }

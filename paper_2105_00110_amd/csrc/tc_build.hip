@@ -337,12 +337,17 @@ struct GetHigh {
 
 __global__ void k_degree(int32_t n, const uint32_t *__restrict__ us, const uint32_t *__restrict__ ue,
                          const uint32_t *__restrict__ ls, const uint32_t *__restrict__ le,
-                         int64_t *__restrict__ deg64, uint32_t *__restrict__ deg32) {
+                         int64_t *__restrict__ deg64, uint32_t *__restrict__ deg32,
+                         uint32_t *__restrict__ dmax) {
+    __shared__ uint32_t lds[BK / TC_WAVE];
+    uint32_t mx = 0;
     GRID_STRIDE(x, n) {
         uint32_t d = (ue[x] - us[x]) + (le[x] - ls[x]);
         deg64[x] = d;
         deg32[x] = d;
+        mx = d > mx ? d : mx;
     }
+    tc_block_raise<BK>(mx, dmax, lds);
 }
 
 // Smaller neighbours: transposed entry j = (ev, e) sorted by ev.
@@ -370,10 +375,6 @@ __global__ void k_fill_upper(int64_t m, const int32_t *__restrict__ eu,
         col[p] = ev[e];
         sym2e[p] = (uint32_t)e;
     }
-}
-
-__global__ void k_iota(uint32_t *a, int64_t n) {
-    GRID_STRIDE(i, n) a[i] = (uint32_t)i;
 }
 
 __global__ void k_invert(const uint32_t *__restrict__ perm, int32_t n, int32_t *__restrict__ perm_out,
@@ -520,18 +521,46 @@ __global__ void k_place_by_larger(int64_t m, const uint32_t *__restrict__ lt_key
     }
 }
 
-// d+ by rank row, and its maximum.
-__global__ void k_dplus_by_rank(int32_t n, const uint32_t *__restrict__ cursor,
-                                const int32_t *__restrict__ rank, int64_t *__restrict__ dplus,
-                                uint32_t *__restrict__ dmax) {
-    uint32_t mx = 0;
-    GRID_STRIDE(x, n) {
-        const uint32_t d = cursor[x];
-        dplus[rank[x]] = d;
-        mx = d > mx ? d : mx;
+// d+ by rank row, its maximum (info[0]), and the vertices whose buckets a
+// wavefront (more than SEG_SMALL entries) or a workgroup (more than SEG_MID)
+// sorts: list_mid and list_big in any order, their counts in info[1] and
+// info[2].  Taken in rank order, so that the random accesses are 4-byte reads
+// and not 8-byte stores; a workgroup takes DL_TILE vertices and at most one
+// atomic per word (one per wavefront on info[0] took 180 us from a million
+// vertices on, and the lists ten more launches; 17 us so at 2^20).
+constexpr int SEG_MID = 1024;  // k_orient_mid's longest bucket
+constexpr int DL_TILE = 2048;
+
+__global__ __launch_bounds__(BK) void k_dplus_lists(int32_t n, const uint32_t *__restrict__ cursor,
+                                                    const int32_t *__restrict__ perm,
+                                                    int64_t *__restrict__ dplus,
+                                                    int32_t *__restrict__ list_mid,
+                                                    int32_t *__restrict__ list_big,
+                                                    uint32_t *__restrict__ info) {
+    constexpr int PER = DL_TILE / BK;
+    __shared__ uint32_t lds[BK / TC_WAVE + 1];
+    const int64_t base = (int64_t)blockIdx.x * DL_TILE;
+    uint32_t d[PER], mx = 0, nmid = 0, nbig = 0;
+    int32_t x[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int64_t r = base + k * BK + threadIdx.x;
+        x[k] = r < n ? perm[r] : -1;
+        d[k] = r < n ? cursor[x[k]] : 0u;
+        if (r < n) dplus[r] = d[k];
+        mx = d[k] > mx ? d[k] : mx;
+        nmid += d[k] > SEG_SMALL && d[k] <= SEG_MID ? 1u : 0u;
+        nbig += d[k] > SEG_MID ? 1u : 0u;
     }
-    mx = tc_wave_max(mx);
-    if (__lane_id() == 0 && mx) atomicMax(dmax, mx);
+    tc_block_raise<BK>(mx, &info[0], lds);
+    if (!__syncthreads_or(nmid | nbig)) return;
+    uint32_t pm = tc_block_reserve<BK>(nmid, &info[1], lds);
+    uint32_t pb = tc_block_reserve<BK>(nbig, &info[2], lds);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (d[k] > SEG_MID) list_big[pb++] = x[k];
+        else if (d[k] > SEG_SMALL) list_mid[pm++] = x[k];
+    }
 }
 
 // Buckets of 1..SEG_SMALL entries.  Every wavefront reads the sizes of 64
@@ -720,7 +749,6 @@ __global__ __launch_bounds__(256) void k_orient_block(
 // One wavefront per listed vertex with SEG_SMALL < entries <= SEG_MID: a
 // bitonic sort over an LDS buffer of the wavefront's own, so its rounds need
 // no workgroup barrier (a wavefront's LDS operations stay in order).
-constexpr int SEG_MID = 1024;
 
 // Bitonic compare-exchange of stage (k, J) on a lane's E consecutive
 // elements (global index base + i), for partners inside the lane (J < E).
@@ -825,32 +853,9 @@ __global__ __launch_bounds__(256) void k_orient_mid(
     }
 }
 
-__global__ void k_size_flags(int32_t n, const uint32_t *__restrict__ cursor, uint32_t lo,
-                             uint32_t hi, uint32_t *__restrict__ f) {
-    GRID_STRIDE(x, n) f[x] = (cursor[x] > lo && cursor[x] <= hi) ? 1u : 0u;
-}
-
-__global__ void k_compact_flags(int32_t n, const uint32_t *__restrict__ f,
-                                const uint32_t *__restrict__ pos, int32_t *__restrict__ out) {
-    GRID_STRIDE(x, n) if (f[x]) out[pos[x]] = (int32_t)x;
-}
-
 }  // namespace
 
 static tc_status orient_sorted(tc_graph *g, hipStream_t s);
-
-// Lists the vertices whose flag is set (flags in f, n entries); the count
-// goes to the device word *count (read back by the caller with others).
-static tc_status compact_vertices(int32_t n, uint32_t *f, int32_t *out, uint32_t *count,
-                                  hipStream_t s) {
-    tc_scratch tmp(s);
-    uint32_t *pos = nullptr;
-    TC_TRY(tmp.get(&pos, n));
-    TC_TRY(tc_scan_u32(f, pos, n, count, s));
-    k_compact_flags<<<grid_for(n), BK, 0, s>>>(n, f, pos, out);
-    TC_LAUNCHED();
-    return TC_OK;
-}
 
 void tc_release_transposition(tc_graph *g, hipStream_t s) {
     if (!g->lt_key) return;
@@ -879,15 +884,13 @@ tc_status tc_orient(tc_graph *g, hipStream_t s) {
     }
     tc_scratch tmp(s);
     int64_t *dplus = nullptr;
-    uint32_t *info = nullptr, *flags = nullptr, *flags2 = nullptr, *cursor = nullptr;
+    uint32_t *info = nullptr, *cursor = nullptr;
     uint64_t *tbuf = nullptr;
     int32_t *list_mid = nullptr, *list_big = nullptr;
     TC_TRY(tmp.get(&cursor, nn));
     TC_TRY(tmp.get(&tbuf, 2 * m));
     TC_TRY(tmp.get(&dplus, nn));
     TC_TRY(tmp.get(&info, 4));  // max d+, mid-list count, big-list count
-    TC_TRY(tmp.get(&flags, nn));
-    TC_TRY(tmp.get(&flags2, nn));
     TC_TRY(tmp.get(&list_mid, nn));
     TC_TRY(tmp.get(&list_big, nn));
     TC_HIP(hipMemsetAsync(info, 0, 16, s));
@@ -903,19 +906,12 @@ tc_status tc_orient(tc_graph *g, hipStream_t s) {
                                                      g->row_ptr, cursor, tbuf);
         TC_LAUNCHED();
     }
-    k_dplus_by_rank<<<grid_for(n) < 4096 ? grid_for(n) : 4096, BK, 0, s>>>(n, cursor, g->rank, dplus,
-                                                                          info);
+    // with the largest d+ and the lists, whose counts one read-back brings
+    k_dplus_lists<<<(unsigned)tc_div_up(n, DL_TILE), BK, 0, s>>>(n, cursor, g->perm, dplus, list_mid,
+                                                                list_big, info);
     TC_LAUNCHED();
-    // the buckets sorted by a wavefront and by a workgroup, listed now so that
-    // one read-back brings their counts with the largest d+
-    k_size_flags<<<grid_for(n), BK, 0, s>>>(n, cursor, SEG_SMALL, SEG_MID, flags);
-    TC_LAUNCHED();
-    TC_TRY(compact_vertices(n, flags, list_mid, info + 1, s));
-    k_size_flags<<<grid_for(n), BK, 0, s>>>(n, cursor, SEG_MID, 0xFFFFFFFFu, flags2);
-    TC_LAUNCHED();
-    TC_TRY(compact_vertices(n, flags2, list_big, info + 2, s));
     uint32_t h_info[4] = {0, 0, 0, 0};
-    TC_TRY(tc_read({{h_info, info, 4}}, s));
+    TC_TRY(tc_read({{h_info, info, 3}, {&g->max_degree, g->err + 1, 1}}, s));
     const uint32_t h_max = h_info[0];
     const int64_t nmid = h_info[1], nblk = h_info[2];
     g->max_dplus = (int32_t)h_max;
@@ -1073,7 +1069,8 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
         TC_LAUNCHED();
     }
     if (n > 0) {
-        k_degree<<<grid_for(n), BK, 0, s>>>(n, us, ue, ls, le, deg64, deg32);
+        k_degree<<<grid_for(n) < 1024 ? grid_for(n) : 1024, BK, 0, s>>>(n, us, ue, ls, le, deg64, deg32,
+                                                                        g->err + 1);
         TC_LAUNCHED();
         TC_TRY(tc_scan_i64(deg64, g->row_ptr, n, g->row_ptr + n, s));
     } else {
@@ -1090,10 +1087,10 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
         TC_TRY(tmp.get(&pv, nn));
         TC_TRY(tmp.get(&pv2, nn));
         TC_TRY(tmp.get(&dk2, nn));
-        k_iota<<<grid_for(n), BK, 0, s>>>(pv, n);
-        TC_LAUNCHED();
         // degrees are below n, so `bits` bits hold them
-        TC_TRY(tc_sort_u32_u32(&deg32, &pv, &dk2, &pv2, n, bits, s));
+        uint32_t *dk = nullptr;
+        TC_TRY(tmp.get(&dk, nn));
+        TC_TRY(tc_sort_u32_index(deg32, &dk, &pv, &dk2, &pv2, n, bits, s));
         k_invert<<<grid_for(n), BK, 0, s>>>(pv, n, g->perm, g->rank);
         TC_LAUNCHED();
     }

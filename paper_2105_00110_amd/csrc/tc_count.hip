@@ -100,7 +100,8 @@ __host__ __device__ __forceinline__ size_t light_wave_bytes(int dcap) {
 __global__ __launch_bounds__(1024) void k_count_light(const int64_t *__restrict__ orp,
                                                       const int32_t *__restrict__ ocol,
                                                       const int32_t *__restrict__ rows,
-                                                      int64_t nrows, int dcap,
+                                                      const uint32_t *__restrict__ row_count,
+                                                      int dcap,
                                                       uint32_t *__restrict__ osup,
                                                       unsigned long long *__restrict__ tri_total) {
     extern __shared__ uint4 lds4[];
@@ -113,6 +114,7 @@ __global__ __launch_bounds__(1024) void k_count_light(const int64_t *__restrict_
     uint16_t *pos = reinterpret_cast<uint16_t *>(base + 16 * (size_t)nbmax);
     uint32_t *lsup = reinterpret_cast<uint32_t *>(base + 24 * (size_t)nbmax);
     unsigned long long found = 0;
+    const int64_t nrows = *row_count;
     for (int64_t ri = (int64_t)blockIdx.x * wpb + wv; ri < nrows; ri += (int64_t)gridDim.x * wpb) {
         const int32_t r = rows[ri];
         const int64_t start = orp[r];
@@ -154,13 +156,13 @@ static inline size_t heavy_bytes(int dmax) {
 
 // One workgroup per heavy row (GLOBAL_LOOKUP: no table, binary search in
 // device memory, for rows whose table would not fit).  Wavefront wv takes
-// the row's u at indices wv, wv + wpb, wv + 2·wpb, ...; rows are taken from
-// the end of the list (highest rank, typically the most work) first.
+// the row's u at indices wv, wv + wpb, wv + 2·wpb, ...
 template <bool GLOBAL_LOOKUP>
 __global__ __launch_bounds__(1024) void k_count_heavy(const int64_t *__restrict__ orp,
                                                       const int32_t *__restrict__ ocol,
                                                       const int32_t *__restrict__ rows,
-                                                      int64_t nrows, int dmax,
+                                                      const uint32_t *__restrict__ row_count,
+                                                      int dmax,
                                                       uint32_t *__restrict__ osup,
                                                       unsigned long long *__restrict__ tri_total) {
     extern __shared__ uint4 lds4[];
@@ -173,8 +175,9 @@ __global__ __launch_bounds__(1024) void k_count_heavy(const int64_t *__restrict_
     uint16_t *pos = reinterpret_cast<uint16_t *>(base + 16 * (size_t)nbmax);
     uint32_t *lsup = reinterpret_cast<uint32_t *>(base + 24 * (size_t)nbmax);
     unsigned long long found = 0;
+    const int64_t nrows = *row_count;
     for (int64_t bi = blockIdx.x; bi < nrows; bi += gridDim.x) {
-        const int32_t r = rows[nrows - 1 - bi];
+        const int32_t r = rows[bi];
         const int64_t start = orp[r];
         const int d = (int)(orp[r + 1] - start);
         RowTable t{keys, pos, 0};
@@ -222,37 +225,43 @@ __global__ __launch_bounds__(1024) void k_count_heavy(const int64_t *__restrict_
     if (lane == 0 && found) atomicAdd(tri_total, found);
 }
 
-__global__ void k_bin_flags(int32_t n, const int64_t *__restrict__ orp, int lo, int hi,
-                            uint32_t *__restrict__ flags) {
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n;
-         r += (int64_t)gridDim.x * blockDim.x) {
-        int64_t d = orp[r + 1] - orp[r];
-        flags[r] = (d >= lo && d <= hi) ? 1u : 0u;
-    }
-}
+// The rows of each bin (2 <= d+ <= light_max, then below huge_min, then the
+// others), in any order; cnt[0..2] their numbers.  The count kernels read the
+// numbers on the device, so nothing waits for them (flags, a scan and a write
+// for each bin and a read-back were 13 launches and a wait).
+constexpr int BR_TILE = 2048;
 
-__global__ void k_bin_write(int32_t n, const int64_t *__restrict__ orp, int lo, int hi,
-                            const uint32_t *__restrict__ pos, int32_t *__restrict__ out) {
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n;
-         r += (int64_t)gridDim.x * blockDim.x) {
-        int64_t d = orp[r + 1] - orp[r];
-        if (d >= lo && d <= hi) out[pos[r]] = (int32_t)r;
+__global__ __launch_bounds__(BK) void k_bin_rows(int32_t n, const int64_t *__restrict__ orp,
+                                                 int light_max, int huge_min,
+                                                 int32_t *__restrict__ light,
+                                                 int32_t *__restrict__ heavy,
+                                                 int32_t *__restrict__ huge,
+                                                 uint32_t *__restrict__ cnt) {
+    constexpr int PER = BR_TILE / BK;
+    __shared__ uint32_t lds[BK / TC_WAVE + 1];
+    const int64_t base = (int64_t)blockIdx.x * BR_TILE;
+    int bin[PER];
+    uint32_t c[3] = {0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int64_t r = base + k * BK + threadIdx.x;
+        const int64_t d = r < n ? orp[r + 1] - orp[r] : 0;
+        bin[k] = d < 2 ? -1 : (d <= light_max ? 0 : (d < huge_min ? 1 : 2));
+#pragma unroll
+        for (int q = 0; q < 3; ++q) c[q] += bin[k] == q ? 1u : 0u;
     }
-}
-
-// Rows with lo <= d+ <= hi, in rank order; their count goes to the device
-// word *count (the caller reads the counts of all bins back at once).
-tc_status select_rows(const tc_graph *g, int lo, int hi, int32_t *out, uint32_t *count,
-                      hipStream_t s) {
-    tc_scratch tmp(s);
-    uint32_t *pos = nullptr;
-    TC_TRY(tmp.get(&pos, g->n));
-    k_bin_flags<<<grid_for(g->n), BK, 0, s>>>(g->n, g->orp, lo, hi, pos);
-    TC_LAUNCHED();
-    TC_TRY(tc_scan_u32(pos, pos, g->n, count, s));
-    k_bin_write<<<grid_for(g->n), BK, 0, s>>>(g->n, g->orp, lo, hi, pos, out);
-    TC_LAUNCHED();
-    return TC_OK;
+    uint32_t p0 = tc_block_reserve<BK>(c[0], &cnt[0], lds), p1 = 0, p2 = 0;
+    if (__syncthreads_or(c[1] | c[2])) {
+        p1 = tc_block_reserve<BK>(c[1], &cnt[1], lds);
+        p2 = tc_block_reserve<BK>(c[2], &cnt[2], lds);
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int32_t r = (int32_t)(base + k * BK + threadIdx.x);
+        if (bin[k] == 0) light[p0++] = r;
+        else if (bin[k] == 1) heavy[p1++] = r;
+        else if (bin[k] == 2) huge[p2++] = r;
+    }
 }
 
 }  // namespace
@@ -333,7 +342,6 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     unsigned long long *found = (unsigned long long *)(g->triG + g->num_graphs);
     TC_HIP(hipMemsetAsync(found, 0, sizeof(uint64_t), s));
     if (m == 0 || g->max_dplus < 2) {
-        g->n_light = g->n_heavy = g->n_huge = 0;
         g->light_max = t.light_max_dplus;
         g->huge_min = 0x7FFFFFFF;
         for (int k = 5; k <= 9; ++k) tc_prof_mark(g, k, s);
@@ -365,51 +373,51 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     tc_scratch tmp(s);
     int32_t *rows = nullptr, *heavy = nullptr, *huge = nullptr;
     uint32_t *cnt = nullptr;
+    // the longest row says which bins can hold rows at all
+    const bool any_heavy = g->max_dplus > light_max, any_huge = g->max_dplus >= huge_min;
     TC_TRY(tmp.get(&rows, g->n));
-    TC_TRY(tmp.get(&heavy, g->n));
-    TC_TRY(tmp.get(&huge, g->n));
-    TC_TRY(tmp.get(&cnt, 4));
-    TC_TRY(select_rows(g, 2, light_max, rows, cnt, s));
-    TC_TRY(select_rows(g, light_max + 1, huge_min - 1, heavy, cnt + 1, s));
-    TC_TRY(select_rows(g, huge_min, 0x7FFFFFFF, huge, cnt + 2, s));
-    uint32_t hc[4] = {0, 0, 0, 0};
-    TC_TRY(tc_read({{hc, cnt, 3}}, s));
-    const int64_t nl = hc[0], nh = hc[1], nz = hc[2];
-    g->n_light = nl;
-    g->n_heavy = nh;
-    g->n_huge = nz;
+    TC_TRY(tmp.get(&heavy, any_heavy ? g->n : 1));
+    TC_TRY(tmp.get(&huge, any_huge ? g->n : 1));
+    TC_TRY(tmp.get(&cnt, 3));
+    TC_HIP(hipMemsetAsync(cnt, 0, 12, s));
+    k_bin_rows<<<(unsigned)tc_div_up(g->n, BR_TILE), BK, 0, s>>>(g->n, g->orp, light_max, huge_min,
+                                                                rows, heavy, huge, cnt);
+    TC_LAUNCHED();
     g->light_max = light_max;
     g->huge_min = huge_min;
     tc_prof_mark(g, 5, s);
 
-    if (nl > 0) {
-        const int dcap = light_max;
+    {
+        // tables and counters for the longest light row there is; as many
+        // workgroups as stay resident (8 of 4 wavefronts per CU), each taking
+        // rows in turn
+        const int dcap = g->max_dplus < light_max ? g->max_dplus : light_max;
         const size_t per_wave = light_wave_bytes(dcap);
         int wpb = t.light_block / TC_WAVE;
         while (wpb > 1 && (size_t)wpb * per_wave > (size_t)lds_limit) --wpb;
         const int block = wpb * TC_WAVE;
         const size_t lds = (size_t)wpb * per_wave;
-        int64_t blocks = tc_div_up(nl, wpb);
-        if (blocks > 65536) blocks = 65536;
-        k_count_light<<<(unsigned)blocks, block, lds, s>>>(g->orp, g->ocol, rows, nl, dcap, g->osup,
+        int64_t blocks = tc_div_up(g->n, wpb);
+        if (blocks > 8192 / wpb) blocks = 8192 / wpb;
+        k_count_light<<<(unsigned)blocks, block, lds, s>>>(g->orp, g->ocol, rows, cnt, dcap, g->osup,
                                                          found);
         TC_LAUNCHED();
     }
     tc_prof_mark(g, 6, s);
-    if (nh > 0) {
+    if (any_heavy) {
         // every heavy row has light_max < d+ < huge_min and d+ <= max d+
         const int hmax = g->max_dplus < huge_min - 1 ? g->max_dplus : huge_min - 1;
         const size_t lds = heavy_bytes(hmax);
-        int64_t blocks = nh < 1048576 ? nh : 1048576;
+        const int64_t blocks = g->n < 8192 ? g->n : 8192;
         k_count_heavy<false><<<(unsigned)blocks, t.heavy_block, lds, s>>>(
-            g->orp, g->ocol, heavy, nh, hmax, g->osup, found);
+            g->orp, g->ocol, heavy, cnt + 1, hmax, g->osup, found);
         TC_LAUNCHED();
     }
     tc_prof_mark(g, 7, s);
-    if (nz > 0) {
-        int64_t blocks = nz < 65536 ? nz : 65536;
-        k_count_heavy<true><<<(unsigned)blocks, t.heavy_block, 0, s>>>(g->orp, g->ocol, huge, nz, 0,
-                                                                      g->osup, found);
+    if (any_huge) {
+        const int64_t blocks = g->n < 8192 ? g->n : 8192;
+        k_count_heavy<true><<<(unsigned)blocks, t.heavy_block, 0, s>>>(g->orp, g->ocol, huge, cnt + 2,
+                                                                      0, g->osup, found);
         TC_LAUNCHED();
     }
     tc_prof_mark(g, 8, s);

@@ -120,40 +120,43 @@ __global__ void k_in_len(int32_t n, const int32_t *__restrict__ perm,
 }
 
 // ---------------------------------------------------------------------------
-// Work items: pivot v with |N_H(v)| in [lo, hi] and at least one lower
-// neighbour, cut into slices of at most S pairs.
+// Work items: pivots with at least one lower neighbour, each in one class
+// (the kernel that takes it) and cut into slices of at most S[class] pairs;
+// and the rows that the two folds take.  All lists are built together: a
+// count per (list, tile of PLAN_TILE vertices), one scan of those few
+// counts, one read-back of the list sizes, and a second pass over the
+// vertices that writes every list in rank order.  (A count, a scan over all
+// vertices and a write for each of the ten lists were 62 launches at R-MAT
+// scale 20.)
 // ---------------------------------------------------------------------------
-// Items of the pivots with lo <= |N_H(v)| <= hi.  A pivot "fits the bitmap"
-// when its rank span is at most span_max and it has at least pairs_min
-// pairs; sel 1 keeps only such pivots, sel 2 only the others, sel 0 all.
-__global__ void k_item_count(int32_t n, const int64_t *__restrict__ orp,
-                             const int32_t *__restrict__ ocol, const int64_t *__restrict__ in_ptr,
-                             int lo, int hi, int S, int sel, int64_t span_max, int64_t pairs_min,
-                             int32_t rlo, int32_t rhi, uint32_t *__restrict__ cnt) {
-    GRID_STRIDE(v, n) {
-        const int64_t d = orp[v + 1] - orp[v];
-        const int64_t in = in_ptr[v + 1] - in_ptr[v];
-        bool ok = d >= lo && d <= hi && in > 0 && v >= rlo && v < rhi;
-        if (ok && sel != 0) {
-            const int64_t span = (int64_t)ocol[orp[v + 1] - 1] - ocol[orp[v]] + 1;
-            const bool fits = span <= span_max && in >= pairs_min;
-            ok = sel == 1 ? fits : !fits;
-        }
-        cnt[v] = ok ? (uint32_t)tc_div_up(in, S) : 0u;
+enum { P_GROUP, P_WAVE, P_LBITMAP, P_BITMAP16, P_BITMAP, P_BLOCK, P_HUGE, P_ZERO, NPLANS };
+enum { L_FOLD = NPLANS, L_FOLD_BIG, NLISTS };
+
+struct PlanRules {
+    int gmax, light_max, huge_min;  // |N_H(v)| bounds of the classes
+    int split, lsplit;              // span bitmap for workgroup / wavefront pivots
+    int64_t span_max, pairs_min;    // a pivot fits it up to this span; wavefront ones from
+                                    // this many pairs
+    int32_t r16s;                   // workgroup pivots from this rank on: LK_BITMAP16
+    int S[NPLANS];
+};
+
+__device__ __forceinline__ int item_class(const PlanRules &q, int64_t v, int64_t d, int64_t in,
+                                          const int32_t *__restrict__ row) {
+    if (in == 0) return -1;
+    if (d == 0) return P_ZERO;  // nothing to close: the pairs' bit rows are only cleared
+    if (d >= q.huge_min) return P_HUGE;
+    const bool heavy = d > q.light_max;
+    if (heavy && v >= q.r16s) return P_BITMAP16;
+    if (heavy ? q.split != 0 : q.lsplit != 0 && in >= q.pairs_min) {
+        const int64_t span = (int64_t)row[d - 1] - row[0] + 1;
+        if (span <= q.span_max) return heavy ? P_BITMAP : P_LBITMAP;
     }
+    return heavy ? P_BLOCK : (d <= q.gmax ? P_GROUP : P_WAVE);
 }
 
-__global__ void k_item_write(int32_t n, const uint32_t *__restrict__ cnt,
-                             const uint32_t *__restrict__ off, const int64_t *__restrict__ in_ptr,
-                             int S, int32_t *__restrict__ item_v, uint32_t *__restrict__ item_first) {
-    GRID_STRIDE(v, n) {
-        const uint32_t c = cnt[v];
-        for (uint32_t t = 0; t < c; ++t) {
-            item_v[off[v] + t] = (int32_t)v;
-            item_first[off[v] + t] = (uint32_t)(in_ptr[v] + (int64_t)t * S);
-        }
-    }
-}
+constexpr int PLAN_PER = 8;  // vertices per thread
+constexpr int PLAN_TILE = BK * PLAN_PER;
 
 // ---------------------------------------------------------------------------
 // Lookups of a pivot's row N_H(v) (position of a rank in the row, or -1).
@@ -1183,46 +1186,101 @@ __global__ __launch_bounds__(256, 4) void k_fold_big(const int32_t *__restrict__
     }
 }
 
-__global__ void k_dplus_flags(int32_t n, const int64_t *__restrict__ orp, int lo, int hi,
-                              uint32_t *__restrict__ f) {
-    GRID_STRIDE(r, n) {
-        const int64_t d = orp[r + 1] - orp[r];
-        f[r] = (d >= lo && d <= hi) ? 1u : 0u;
+// Per vertex its flag byte, the class in the low four bits (15: none) and the
+// fold list, less L_FOLD, above them (15: none); per (list, tile) the number
+// of entries.
+__global__ void k_dplus_flags(PlanRules q, int32_t n,
+                                                    const int64_t *__restrict__ orp,
+                                                    const int32_t *__restrict__ ocol,
+                                                    const int64_t *__restrict__ in_ptr,
+                                                    uint8_t *__restrict__ flags,
+                                                    int64_t *__restrict__ tile_cnt) {
+    __shared__ uint32_t red[NLISTS][BK / TC_WAVE];
+    const int64_t base = (int64_t)blockIdx.x * PLAN_TILE;
+    uint32_t c[NLISTS] = {};
+#pragma unroll
+    for (int k = 0; k < PLAN_PER; ++k) {
+        const int64_t v = base + k * BK + threadIdx.x;
+        if (v < n) {
+            const int64_t a = orp[v], d = orp[v + 1] - a, in = in_ptr[v + 1] - in_ptr[v];
+            const int cls = item_class(q, v, d, in, ocol + a);
+            const int fold = d < 2 ? 15 : (d <= 64 ? 0 : 1);
+            flags[v] = (uint8_t)((cls & 15) | fold << 4);
+#pragma unroll
+            for (int l = 0; l < NPLANS; ++l)
+                if (cls == l) c[l] += (uint32_t)tc_div_up(in, q.S[l]);
+            c[L_FOLD] += fold == 0 ? 1u : 0u;
+            c[L_FOLD_BIG] += fold == 1 ? 1u : 0u;
+        }
+    }
+#pragma unroll
+    for (int l = 0; l < NLISTS; ++l) {
+        const uint32_t t = tc_wave_sum(c[l]);
+        if (__lane_id() == 0) red[l][threadIdx.x / TC_WAVE] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < NLISTS) {
+        int64_t t = 0;
+        for (int w = 0; w < BK / TC_WAVE; ++w) t += red[threadIdx.x][w];
+        tile_cnt[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
     }
 }
 
-__global__ void k_dplus_write(int32_t n, const int64_t *__restrict__ orp, int lo, int hi,
-                              const uint32_t *__restrict__ pos, int32_t *__restrict__ out) {
-    GRID_STRIDE(r, n) {
-        const int64_t d = orp[r + 1] - orp[r];
-        if (d >= lo && d <= hi) out[pos[r]] = (int32_t)r;
+// tile_off: the scanned counts.  Items of all classes lie in one pair of
+// arrays, the fold's rows in another, from the first place of L_FOLD on.
+__global__ __launch_bounds__(BK) void k_plan_write(PlanRules q, int32_t n,
+                                                   const uint8_t *__restrict__ flags,
+                                                   const int64_t *__restrict__ in_ptr,
+                                                   const int64_t *__restrict__ tile_off,
+                                                   int32_t *__restrict__ item_v,
+                                                   uint32_t *__restrict__ item_first,
+                                                   int32_t *__restrict__ fold_rows) {
+    __shared__ uint32_t wsum[BK / TC_WAVE];
+    // consecutive vertices per thread, so that the lists come in rank order
+    int cls[PLAN_PER], fold[PLAN_PER];
+    uint32_t cnt[PLAN_PER];
+    const int64_t v0 = (int64_t)blockIdx.x * PLAN_TILE + threadIdx.x * PLAN_PER;
+#pragma unroll
+    for (int k = 0; k < PLAN_PER; ++k) {
+        cls[k] = fold[k] = 15;
+        cnt[k] = 0;
+        if (v0 + k < n) {
+            const int f = flags[v0 + k];
+            cls[k] = f & 15;
+            fold[k] = L_FOLD + (f >> 4);
+            int S = 1;
+#pragma unroll
+            for (int l = 0; l < NPLANS; ++l) S = cls[k] == l ? q.S[l] : S;
+            if (cls[k] != 15) cnt[k] = (uint32_t)tc_div_up(in_ptr[v0 + k + 1] - in_ptr[v0 + k], S);
+        }
     }
-}
-
-// Rows with lo <= |N_H| <= hi for the fold, in the same two phases.
-struct RowPlan {
-    int lo = 2, hi = 0;
-    uint32_t *pos = nullptr;
-    int64_t count = 0;
-    int32_t *rows = nullptr;
-};
-
-tc_status rows_count(const tc_graph *g, RowPlan &p, uint32_t *tot, tc_scratch &keep,
-                     hipStream_t s) {
-    const int32_t n = g->n;
-    TC_TRY(keep.get(&p.pos, n));
-    k_dplus_flags<<<grid_for(n), BK, 0, s>>>(n, g->orp, p.lo, p.hi, p.pos);
-    TC_LAUNCHED();
-    return tc_scan_u32(p.pos, p.pos, n, tot, s);
-}
-
-tc_status rows_write(const tc_graph *g, RowPlan &p, tc_scratch &keep, hipStream_t s) {
-    TC_TRY(keep.get(&p.rows, p.count));
-    if (p.count > 0) {
-        k_dplus_write<<<grid_for(g->n), BK, 0, s>>>(g->n, g->orp, p.lo, p.hi, p.pos, p.rows);
-        TC_LAUNCHED();
+    const int w = threadIdx.x / TC_WAVE;
+    const int64_t fold0 = tile_off[(int64_t)L_FOLD * gridDim.x];
+#pragma unroll
+    for (int l = 0; l < NLISTS; ++l) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int k = 0; k < PLAN_PER; ++k)
+            c += l < NPLANS ? (cls[k] == l ? cnt[k] : 0u) : (fold[k] == l ? 1u : 0u);
+        if (!__syncthreads_or(c != 0)) continue;
+        const uint32_t incl = tc_wave_incl_scan(c);
+        if (__lane_id() == TC_WAVE - 1) wsum[w] = incl;
+        __syncthreads();
+        int64_t at = tile_off[(int64_t)l * gridDim.x + blockIdx.x] + incl - c;
+        for (int p = 0; p < w; ++p) at += wsum[p];
+#pragma unroll
+        for (int k = 0; k < PLAN_PER; ++k) {
+            if (l >= NPLANS) {
+                if (fold[k] == l) fold_rows[at++ - fold0] = (int32_t)(v0 + k);
+            } else if (cls[k] == l) {
+                const int64_t first = in_ptr[v0 + k];
+                for (uint32_t t = 0; t < cnt[k]; ++t, ++at) {
+                    item_v[at] = (int32_t)(v0 + k);
+                    item_first[at] = (uint32_t)(first + (int64_t)t * q.S[l < NPLANS ? l : 0]);
+                }
+            }
+        }
     }
-    return TC_OK;
 }
 
 // The bit rows of the pairs whose pivot has no higher neighbours: no count
@@ -1322,51 +1380,14 @@ __global__ void k_mid_pivots(int32_t n, const int64_t *__restrict__ orp,
     }
 }
 
-// Work-item lists are built in two phases so that one read-back serves all
-// of them: count (per-pivot item counts and their scan; the total stays on
-// the device), then, with the totals on the host, allocate and write.
-struct ItemPlan {
-    int lo = 1, hi = 0, S = 64, sel = 0;
-    int64_t span_max = 0, pairs_min = 0;
-    int32_t rlo = 0, rhi = 0x7FFFFFFF;  // pivot ranks [rlo, rhi)
-    uint32_t *cnt = nullptr, *off = nullptr;
-    int64_t count = 0;
-    int32_t *item_v = nullptr;
-    uint32_t *item_first = nullptr;
-};
-
-tc_status plan_count(const tc_graph *g, ItemPlan &p, uint32_t *tot, tc_scratch &keep,
-                     hipStream_t s) {
-    const int32_t n = g->n;
-    TC_TRY(keep.get(&p.cnt, n));
-    TC_TRY(keep.get(&p.off, n));
-    k_item_count<<<grid_for(n), BK, 0, s>>>(n, g->orp, g->ocol, g->in_ptr, p.lo, p.hi, p.S, p.sel,
-                                            p.span_max, p.pairs_min, p.rlo, p.rhi, p.cnt);
-    TC_LAUNCHED();
-    return tc_scan_u32(p.cnt, p.off, n, tot, s);
-}
-
-tc_status plan_write(const tc_graph *g, ItemPlan &p, tc_scratch &keep, hipStream_t s) {
-    TC_TRY(keep.get(&p.item_v, p.count));
-    TC_TRY(keep.get(&p.item_first, p.count));
-    if (p.count > 0) {
-        k_item_write<<<grid_for(g->n), BK, 0, s>>>(g->n, p.cnt, p.off, g->in_ptr, p.S, p.item_v,
-                                                  p.item_first);
-        TC_LAUNCHED();
-    }
-    return TC_OK;
-}
-
 }  // namespace
 
 // Builds in_ptr / in_pair (the transposed orientation) once per handle.
-static tc_status bit_rows_prepare(tc_graph *g, hipStream_t s);
-
 tc_status tc_mid_prepare(tc_graph *g, hipStream_t s) {
     // the order by larger id is not needed from here on (the symmetric
     // fill sorts again if it is ever asked for)
     tc_release_transposition(g, s);
-    if (g->in_pair) return bit_rows_prepare(g, s);
+    if (g->in_pair) return TC_OK;
     const int32_t n = g->n;
     const int64_t m = g->m;
     const int64_t nn = n > 0 ? n : 1;
@@ -1398,7 +1419,7 @@ tc_status tc_mid_prepare(tc_graph *g, hipStream_t s) {
     } else {
         TC_HIP(hipMemsetAsync(g->in_ptr, 0, sizeof(int64_t), s));
     }
-    return bit_rows_prepare(g, s);
+    return TC_OK;
 }
 
 // Per row: its bit matrix's first word (low, high), its start and end in
@@ -1411,29 +1432,28 @@ __global__ void k_row_info(int32_t n, const int64_t *__restrict__ orp,
     }
 }
 
-// Bit matrices: rowbase = exclusive scan of each row's word count.
-static tc_status bit_rows_prepare(tc_graph *g, hipStream_t s) {
-    if (g->rowbase) return TC_OK;
+// Bit matrices: rowbase = exclusive scan of each row's word count, whose
+// total (rowbase[n]) stays on the device.
+static tc_status bit_rows_scan(tc_graph *g, hipStream_t s) {
     const int32_t n = g->n;
-    const int64_t nn = n > 0 ? n : 1;
     tc_scratch tmp(s);
     int64_t *len = nullptr;
-    TC_TRY(tmp.get(&len, nn));
-    TC_TRY(tc_graph_alloc(g, &g->rowbase, nn + 1, s));
+    TC_TRY(tmp.get(&len, n));
+    TC_TRY(tc_graph_alloc(g, &g->rowbase, (int64_t)n + 1, s));
     k_row_words<<<grid_for(n), BK, 0, s>>>(n, g->orp, len);
     TC_LAUNCHED();
-    TC_TRY(tc_scan_i64(len, g->rowbase, n, g->rowbase + n, s));
-    int64_t words = 0;
-    TC_TRY(tc_read({{&words, g->rowbase + n, 2}}, s));
-    g->bit_words = words;
+    return tc_scan_i64(len, g->rowbase, n, g->rowbase + n, s);
+}
+
+// The matrices themselves and the per-row records, with the total known.
+static tc_status bit_rows_alloc(tc_graph *g, int64_t words, hipStream_t s) {
     // 4 words of padding: the fold's row sums read up to 3 words past a
     // row's end
-    TC_TRY(tc_graph_alloc(g, &g->hitbits, words + 4, s));
-    TC_TRY(tc_graph_alloc(g, &g->rowinfo, nn, s));
-    if (n > 0) {
-        k_row_info<<<grid_for(n), BK, 0, s>>>(n, g->orp, g->rowbase, g->rowinfo);
-        TC_LAUNCHED();
-    }
+    if (!g->hitbits) TC_TRY(tc_graph_alloc(g, &g->hitbits, words + 4, s));
+    TC_TRY(tc_graph_alloc(g, &g->rowinfo, g->n, s));
+    k_row_info<<<grid_for(g->n), BK, 0, s>>>(g->n, g->orp, g->rowbase, g->rowinfo);
+    TC_LAUNCHED();
+    g->bit_words = words;
     return TC_OK;
 }
 
@@ -1477,65 +1497,59 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
     // 64 / GROUP_LANES to a wavefront, in items of at most GROUP_PAIRS pairs
     const int gmax = light_max < GROUP_DMAX ? light_max : GROUP_DMAX;
     const int group_pairs = wave_pairs < GROUP_PAIRS ? wave_pairs : GROUP_PAIRS;
-    enum { P_GROUP, P_WAVE, P_LBITMAP, P_BITMAP16, P_BITMAP, P_BLOCK, P_HUGE, P_ZERO, NPLANS };
-    ItemPlan pl[NPLANS];
-    pl[P_GROUP] = {1, gmax, group_pairs, 2 * lsplit, span_max, t.light_bitmap_pairs};
-    pl[P_WAVE] = {gmax + 1, light_max, wave_pairs, 2 * lsplit, span_max, t.light_bitmap_pairs};
-    pl[P_LBITMAP] = {1, lsplit ? light_max : 0, block_pairs, 1, span_max, t.light_bitmap_pairs};
     // workgroup pivots among the top 2^16 ranks take the 2048-word bitmap
     // over 16-bit values whatever their span (when the tuning allows that
     // many words), in a launch of their own whose smaller LDS footprint
     // keeps more wavefronts resident; the others take the span bitmap or
     // hash
     const int32_t r16s = bw >= BITMAP16_WORDS ? g->rank16_base : 0x7FFFFFFF;
-    pl[P_BITMAP16] = {light_max + 1, huge_min - 1, block_pairs, 0, 0, 0, r16s, 0x7FFFFFFF};
-    pl[P_BITMAP] = {light_max + 1, split ? huge_min - 1 : light_max, block_pairs, 1, span_max, 0,
-                    0, r16s};
-    pl[P_BLOCK] = {light_max + 1, huge_min - 1, block_pairs, 2 * split, span_max, 0, 0, r16s};
-    pl[P_HUGE] = {huge_min, 0x7FFFFFFF, block_pairs, 0, 0, 0};
-    // pivots with an empty row: their pairs' bit rows are only cleared
-    pl[P_ZERO] = {0, 0, wave_pairs, 0, 0, 0};
-    RowPlan rp[2];
-    rp[0].lo = 2;
-    rp[0].hi = 64;
-    rp[1].lo = 65;
-    rp[1].hi = 0x7FFFFFFF;
-    uint32_t *tots = nullptr;
-    TC_TRY(items.get(&tots, NPLANS + 2));
-    for (int i = 0; i < NPLANS; ++i) TC_TRY(plan_count(g, pl[i], tots + i, items, s));
-    if (g->bit_words > 0)
-        for (int i = 0; i < 2; ++i) TC_TRY(rows_count(g, rp[i], tots + NPLANS + i, items, s));
-    uint32_t h_tots[NPLANS + 2] = {};
-    TC_TRY(tc_read({{h_tots, tots, NPLANS + 2}}, s));
-    for (int i = 0; i < NPLANS; ++i) {
-        pl[i].count = h_tots[i];
-        TC_TRY(plan_write(g, pl[i], items, s));
-    }
-    if (g->bit_words > 0)
-        for (int i = 0; i < 2; ++i) {
-            rp[i].count = h_tots[NPLANS + i];
-            TC_TRY(rows_write(g, rp[i], items, s));
-        }
-    const int64_t n_group = pl[P_GROUP].count;
-    const int64_t n_wave = pl[P_WAVE].count, n_lbitmap = pl[P_LBITMAP].count;
-    const int64_t n_bitmap = pl[P_BITMAP].count, n_block = pl[P_BLOCK].count;
-    const int64_t n_bitmap16 = pl[P_BITMAP16].count;
-    const int64_t n_huge = pl[P_HUGE].count;
-    int32_t *wv_v = pl[P_WAVE].item_v, *lb_v = pl[P_LBITMAP].item_v, *bm_v = pl[P_BITMAP].item_v;
-    int32_t *bl_v = pl[P_BLOCK].item_v, *hu_v = pl[P_HUGE].item_v;
-    uint32_t *wv_f = pl[P_WAVE].item_first, *lb_f = pl[P_LBITMAP].item_first;
-    uint32_t *bm_f = pl[P_BITMAP].item_first, *bl_f = pl[P_BLOCK].item_first;
-    uint32_t *hu_f = pl[P_HUGE].item_first;
-    g->n_light = n_group + n_wave + n_lbitmap;
-    g->n_heavy = n_block + n_bitmap + n_bitmap16;
-    g->n_huge = n_huge;
+    PlanRules rules = {gmax, light_max, huge_min, split, lsplit, span_max, t.light_bitmap_pairs, r16s,
+                       {}};
+    for (int i = 0; i < NPLANS; ++i) rules.S[i] = block_pairs;
+    rules.S[P_GROUP] = group_pairs;
+    rules.S[P_WAVE] = rules.S[P_ZERO] = wave_pairs;
+    const int64_t plan_tiles = tc_div_up(g->n, PLAN_TILE);
+    int64_t *tile_cnt = nullptr;  // [NLISTS * plan_tiles], then the total
+    uint8_t *flags = nullptr;
+    TC_TRY(items.get(&tile_cnt, NLISTS * plan_tiles + 1));
+    TC_TRY(items.get(&flags, g->n));
+    k_dplus_flags<<<(unsigned)plan_tiles, BK, 0, s>>>(rules, g->n, g->orp, g->ocol, g->in_ptr, flags,
+                                                      tile_cnt);
+    TC_LAUNCHED();
+    TC_TRY(tc_scan_i64(tile_cnt, tile_cnt, NLISTS * plan_tiles, tile_cnt + NLISTS * plan_tiles, s));
+    // one read-back: where each list starts (and the last one ends), and the
+    // bit matrices' size
+    int64_t first[NLISTS + 1] = {}, words = g->bit_words;
+    const bool fresh = g->rowinfo == nullptr;
+    if (!g->rowbase) TC_TRY(bit_rows_scan(g, s));
+    TC_TRY(tc_read({{first, tile_cnt, 2 * (NLISTS + 1), plan_tiles},
+                    {&words, g->rowbase + g->n, fresh ? 2 : 0}},
+                   s));
+    if (fresh) TC_TRY(bit_rows_alloc(g, words, s));
+    const int64_t n_items = first[L_FOLD], n_rows = first[NLISTS] - first[L_FOLD];
+    int32_t *item_v = nullptr, *fold_rows = nullptr;
+    uint32_t *item_first = nullptr;
+    TC_TRY(items.get(&item_v, n_items));
+    TC_TRY(items.get(&item_first, n_items));
+    TC_TRY(items.get(&fold_rows, n_rows));
+    k_plan_write<<<(unsigned)plan_tiles, BK, 0, s>>>(rules, g->n, flags, g->in_ptr, tile_cnt, item_v,
+                                                     item_first, fold_rows);
+    TC_LAUNCHED();
+    const auto list_v = [&](int p) { return item_v + first[p]; };
+    const auto list_first = [&](int p) { return item_first + first[p]; };
+    const auto count_of = [&](int p) { return first[p + 1] - first[p]; };
+    const int64_t n_group = count_of(P_GROUP);
+    const int64_t n_wave = count_of(P_WAVE), n_lbitmap = count_of(P_LBITMAP);
+    const int64_t n_bitmap = count_of(P_BITMAP), n_block = count_of(P_BLOCK);
+    const int64_t n_bitmap16 = count_of(P_BITMAP16);
+    const int64_t n_huge = count_of(P_HUGE), n_zero = count_of(P_ZERO);
     // pairs whose pivot closes nothing are never scanned: their rows are
     // cleared, and every other word is written by the count
-    if (pl[P_ZERO].count > 0) {
-        int64_t zb = tc_div_up(pl[P_ZERO].count, BK / TC_WAVE);
+    if (n_zero > 0) {
+        int64_t zb = tc_div_up(n_zero, BK / TC_WAVE);
         k_zero_rows<<<(unsigned)(zb < 262144 ? zb : 262144), BK, 0, s>>>(
-            g->rowinfo, g->in_pair, g->in_ptr, pl[P_ZERO].item_v, pl[P_ZERO].item_first,
-            pl[P_ZERO].count, wave_pairs, g->hitbits);
+            g->rowinfo, g->in_pair, g->in_ptr, list_v(P_ZERO), list_first(P_ZERO), n_zero, wave_pairs,
+            g->hitbits);
         TC_LAUNCHED();
     }
     tc_prof_mark(g, 5, s);
@@ -1545,8 +1559,8 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         int64_t blocks = tc_div_up(n_group, gpb);
         if (blocks > 262144) blocks = 262144;
         k_mid_groups<GROUP_LANES><<<(unsigned)blocks, 256, (size_t)gpb * mid_group_bytes(gmax, GROUP_LANES), s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, pl[P_GROUP].item_v,
-            pl[P_GROUP].item_first, n_group, gmax, group_pairs, g->osup, found);
+            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_GROUP),
+            list_first(P_GROUP), n_group, gmax, group_pairs, g->osup, found);
         TC_LAUNCHED();
     }
     tc_prof_mark(g, 12, s);
@@ -1557,7 +1571,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         int64_t blocks = tc_div_up(n_wave, wpb);
         if (blocks > 262144) blocks = 262144;
         k_mid_wave<<<(unsigned)blocks, wpb * TC_WAVE, (size_t)wpb * per_wave, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, wv_v, wv_f, n_wave,
+            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_WAVE), list_first(P_WAVE), n_wave,
             light_max, wave_pairs, g->ocol16, g->rank16_base, g->osup, found);
         TC_LAUNCHED();
     }
@@ -1566,7 +1580,8 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         const size_t lds = mid_block_bytes(light_max, wpb_block, LK_BITMAP, bw);
         int64_t blocks = n_lbitmap < 1048576 ? n_lbitmap : 1048576;
         k_mid_block<LK_BITMAP><<<(unsigned)blocks, wpb_block * TC_WAVE, lds, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, lb_v, lb_f, n_lbitmap,
+            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_LBITMAP),
+            list_first(P_LBITMAP), n_lbitmap,
             light_max, block_pairs, bw, g->ocol16, g->rank16_base, g->osup, found);
         TC_LAUNCHED();
     }
@@ -1576,8 +1591,8 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         const size_t lds = mid_block16_bytes(hmax);
         int64_t blocks = n_bitmap16 < 1048576 ? n_bitmap16 : 1048576;
         k_mid_block16<<<(unsigned)blocks, wpb_block * TC_WAVE, lds, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, pl[P_BITMAP16].item_v,
-            pl[P_BITMAP16].item_first, n_bitmap16, hmax, block_pairs, g->ocol16, g->rank16_base,
+            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_BITMAP16),
+            list_first(P_BITMAP16), n_bitmap16, hmax, block_pairs, g->ocol16, g->rank16_base,
             g->osup, found);
         TC_LAUNCHED();
     }
@@ -1587,7 +1602,8 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         const size_t lds = mid_block_bytes(hmax, wpb_block, LK_BITMAP, bw);
         int64_t blocks = n_bitmap < 1048576 ? n_bitmap : 1048576;
         k_mid_block<LK_BITMAP><<<(unsigned)blocks, wpb_block * TC_WAVE, lds, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, bm_v, bm_f, n_bitmap,
+            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_BITMAP),
+            list_first(P_BITMAP), n_bitmap,
             hmax, block_pairs, bw, g->ocol16, g->rank16_base, g->osup, found);
         TC_LAUNCHED();
     }
@@ -1596,7 +1612,8 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         const size_t lds = mid_block_bytes(hmax, wpb_block, LK_HASH, 0);
         int64_t blocks = n_block < 1048576 ? n_block : 1048576;
         k_mid_block<LK_HASH><<<(unsigned)blocks, wpb_block * TC_WAVE, lds, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, bl_v, bl_f, n_block, hmax,
+            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_BLOCK),
+            list_first(P_BLOCK), n_block, hmax,
             block_pairs, 0, g->ocol16, g->rank16_base, g->osup, found);
         TC_LAUNCHED();
     }
@@ -1605,14 +1622,15 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         const size_t lds = mid_block_bytes(0, wpb_block, LK_GLOBAL, 0);
         int64_t blocks = n_huge < 1048576 ? n_huge : 1048576;
         k_mid_block<LK_GLOBAL><<<(unsigned)blocks, wpb_block * TC_WAVE, lds, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, hu_v, hu_f, n_huge, 0,
+            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_HUGE),
+            list_first(P_HUGE), n_huge, 0,
             block_pairs, 0, g->ocol16, g->rank16_base, g->osup, found);
         TC_LAUNCHED();
     }
     tc_prof_mark(g, 8, s);
     if (g->bit_words > 0) {
-        int32_t *small = rp[0].rows, *big = rp[1].rows;
-        const int64_t ns = rp[0].count, nb = rp[1].count;
+        const int64_t ns = count_of(L_FOLD), nb = count_of(L_FOLD_BIG);
+        const int32_t *small = fold_rows, *big = fold_rows + ns;
         if (ns > 0) {
             int64_t fb = tc_div_up(ns, BK / 16);
             k_fold<16><<<(unsigned)(fb < 1048576 ? fb : 1048576), BK, 0, s>>>(
@@ -1665,7 +1683,7 @@ tc_status tc_mid_stats(tc_graph *g, unsigned long long *acc, hipStream_t s) {
 }
 
 tc_status tc_mid_bit_words(const tc_graph *g, int64_t *words, hipStream_t s) {
-    if (g->rowbase) {
+    if (g->rowinfo) {
         *words = g->bit_words;
         return TC_OK;
     }

@@ -61,12 +61,14 @@ struct tc_call_scope {
 };
 
 // Reads words (32-bit, at most 64 in all) from device memory to the host and
-// waits for the stream.
+// waits for the stream.  With step > 0 the words are 64-bit values (two words
+// each) that lie step values apart.
 constexpr int TC_READ_MAX = 3;
 struct tc_read_item {
     void *dst = nullptr;
     const void *src = nullptr;
     int words = 0;
+    int64_t step = 0;
 };
 tc_status tc_read(const tc_read_item (&item)[TC_READ_MAX], hipStream_t s);
 
@@ -193,9 +195,8 @@ struct tc_graph {
     int64_t *h_vtx_off = nullptr;                   // host [G+1]
     int64_t *h_edge_off = nullptr;                  // host [G+1]
     int32_t max_dplus = 0;
-    int32_t *bin_rows = nullptr;                    // [n] rows with d+ >= 2, light then heavy
-    int64_t n_light = 0, n_heavy = 0, n_huge = 0;
-    uint32_t *err = nullptr;                        // device error word
+    int32_t max_degree = 0;
+    uint32_t *err = nullptr;  // device words: error bits, largest degree, 2 unused
 
     size_t bytes = 0;  // device bytes held
 
@@ -287,6 +288,13 @@ __device__ __forceinline__ T tc_wave_max(T x) {
     return x;
 }
 
+// Reserves c places for each thread of a BLOCK-thread workgroup behind the
+// counter *count, with one atomic for the workgroup (one per thread or
+// wavefront on a shared word serialises: 11 ns each); returns the thread's
+// first place.  Every thread calls.  lds: BLOCK / 64 + 1 words.
+template <int BLOCK>
+__device__ __forceinline__ uint32_t tc_block_reserve(uint32_t c, uint32_t *count, uint32_t *lds);
+
 // Inclusive scan across the 64 lanes of a wavefront.
 template <typename T>
 __device__ __forceinline__ T tc_wave_incl_scan(T x) {
@@ -297,4 +305,40 @@ __device__ __forceinline__ T tc_wave_incl_scan(T x) {
         if (l >= off) x += y;
     }
     return x;
+}
+
+template <int BLOCK>
+__device__ __forceinline__ uint32_t tc_block_reserve(uint32_t c, uint32_t *count, uint32_t *lds) {
+    constexpr int W = BLOCK / TC_WAVE;
+    const int w = threadIdx.x / TC_WAVE;
+    const uint32_t incl = tc_wave_incl_scan(c);
+    if (__lane_id() == TC_WAVE - 1) lds[w] = incl;
+    __syncthreads();
+    uint32_t before = incl - c, all = 0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        const uint32_t x = lds[q];
+        before += q < w ? x : 0u;
+        all += x;
+    }
+    if (threadIdx.x == 0) lds[W] = all ? atomicAdd(count, all) : 0u;
+    __syncthreads();
+    const uint32_t base = lds[W];
+    __syncthreads();
+    return base + before;
+}
+
+// Raises *word to the workgroup's largest x; reads the word first, so that
+// most workgroups of a launch do without the atomic.
+template <int BLOCK>
+__device__ __forceinline__ void tc_block_raise(uint32_t x, uint32_t *word, uint32_t *lds) {
+    x = tc_wave_max(x);
+    if (__lane_id() == 0) lds[threadIdx.x / TC_WAVE] = x;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < BLOCK / TC_WAVE; ++q) x = lds[q] > x ? lds[q] : x;
+        if (x > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(word, x);
+    }
+    __syncthreads();
 }
