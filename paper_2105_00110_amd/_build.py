@@ -28,6 +28,7 @@ HIP_SOURCES = [
     "tc_count.hip",
     "tc_count_mid.hip",
     "tc_aggregate.hip",
+    "tc_slots.hip",
     "tc_algebraic.hip",
     "tc_ingest.hip",
     "tc_fused.hip",

@@ -452,6 +452,7 @@ static tc_status support_to_edge_order(tc_graph *g, hipStream_t s) {
 }
 
 tc_status tc_aggregate(tc_graph *g, hipStream_t s) {
+    if (g->slots_used) return tc_aggregate_slots(g, s);
     // with the transposed orientation at hand, aggregate in rank space; the
     // symmetric adjacency is then never filled
     if (g->in_pair) return aggregate_rank_space(g, s);

@@ -31,12 +31,17 @@ namespace {
 
 constexpr int BK = 256;
 constexpr int UNROLL = 4;  // independent candidate loads in flight per lane
-// TC_ALGO_AUTO takes the middle pivot from AUTO_MID_MIN_EDGES edges when
-// the orientation has a row of AUTO_MID_MIN_DPLUS entries or more (degree
-// skew), and from AUTO_MID_MIN_EDGES_FLAT edges otherwise
-constexpr int64_t AUTO_MID_MIN_EDGES = 600000;
-constexpr int64_t AUTO_MID_MIN_EDGES_FLAT = 3000000;
-constexpr int AUTO_MID_MIN_DPLUS = 32;
+// Above the slot merge TC_ALGO_AUTO takes the middle pivot from this many
+// edges (whole calls, low / middle, us: 161 k edges 980 / 1264, 205 k 936 / 880,
+// 308 k 1098 / 909 and 954 / 973, 442 k 948 / 878, 910 k 1263 / 970).
+constexpr int64_t AUTO_MID_MIN_EDGES = 200000;
+// The slot merge (tc_slots.hip) up to this longest oriented row: a slot's merge
+// grows with the rows, a table or bitmap lookup does not.  Whole calls, merge
+// against the forms above (us): BA attach 32, 0.65 M edges, longest row 50:
+// 625 / 853; BA attach 64, 12.9 M edges, 94: 4305 / 5726; R-MAT scale 13, 103:
+// 570 / 634; BA attach 100, 126: 1203 / 1175; R-MAT scale 15, 192: 1146 / 931;
+// scale 16, 246: 1879 / 955.
+constexpr int AUTO_SLOTS_MAX_DPLUS = 128;
 using namespace tc_tab;
 
 static inline unsigned grid_for(int64_t n, int block = BK) {
@@ -292,13 +297,17 @@ static bool tuning_valid(const tc_tuning *t) {
            t->light_bitmap_pairs >= 0;
 }
 
+// AUTO merges slots (tc_slots.hip, a low-pivot form without tables) where every
+// oriented row is short.
+static bool use_slots(const tc_graph *g, const tc_tuning &t) {
+    return t.algorithm == TC_ALGO_AUTO && g->max_dplus <= AUTO_SLOTS_MAX_DPLUS;
+}
+
 // The pivot form AUTO (or the tuning) takes for this graph.
 static int choose_algo(const tc_graph *g, const tc_tuning &t) {
     if (t.algorithm != TC_ALGO_AUTO) return t.algorithm;
-    const int64_t m = g->m;
-    const bool mid = m >= AUTO_MID_MIN_EDGES_FLAT ||
-                     (m >= AUTO_MID_MIN_EDGES && g->max_dplus >= AUTO_MID_MIN_DPLUS);
-    return mid ? TC_ALGO_MID_PIVOT : TC_ALGO_LOW_PIVOT;
+    if (use_slots(g, t)) return TC_ALGO_LOW_PIVOT;
+    return g->m >= AUTO_MID_MIN_EDGES ? TC_ALGO_MID_PIVOT : TC_ALGO_LOW_PIVOT;
 }
 
 tc_status tc_count_bytes(tc_graph *g, const tc_tuning *tin, hipStream_t s, int64_t *bytes) {
@@ -335,6 +344,7 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     if (tin) t = *tin; else tc_tuning_default(&t);
     if (!tuning_valid(&t)) return TC_ERR_INVALID_ARG;
     const int64_t m = g->m;
+    g->slots_used = false;
     if (!g->osup) TC_TRY(tc_graph_alloc(g, &g->osup, m, s));
     if (!g->triG) TC_TRY(tc_graph_alloc(g, &g->triG, g->num_graphs + 1, s));
     TC_HIP(hipMemsetAsync(g->osup, 0, sizeof(uint32_t) * (m > 0 ? m : 1), s));
@@ -356,14 +366,20 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     TC_HIP(hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
     int max_entries = t.lds_max_entries;
     while (max_entries > 1024 && heavy_bytes(max_entries / 2) > (size_t)lds_limit) max_entries >>= 1;
-    // AUTO: the middle pivot streams fewer candidates (the oriented wedges),
-    // but its transposition, work items and fold cost a fixed number of
-    // launches and host round trips.  On this device the low pivot finishes
-    // first below about 0.6 M edges, and, on graphs whose oriented rows all
-    // stay short (no degree skew, e.g. ER at average degree 16), up to a few
-    // million.
+    // AUTO, above the slot merge: the middle pivot streams fewer candidates
+    // (the oriented wedges), but its transposition, work items and fold cost a
+    // fixed number of launches and a host round trip.
     const int algo = choose_algo(g, t);
     g->algo_used = algo;
+    if (use_slots(g, t)) {
+        g->slots_used = true;
+        g->light_max = t.light_max_dplus;
+        g->huge_min = 0x7FFFFFFF;
+        tc_prof_mark(g, 5, s);
+        TC_TRY(tc_count_slots(g, found, s));
+        for (int k = 6; k <= 9; ++k) tc_prof_mark(g, k, s);
+        return TC_OK;
+    }
     if (algo == TC_ALGO_MID_PIVOT) return tc_count_mid(g, t, lds_limit, max_entries, found, s);
     const int light_max = t.light_max_dplus;
     // heavy rows: light_max < d+ < huge_min (table at most half full); the

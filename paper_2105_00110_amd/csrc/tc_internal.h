@@ -203,6 +203,7 @@ struct tc_graph {
     // bins of the last count: light 2..light_max, heavy ..huge_min-1, huge
     int32_t light_max = 0, huge_min = 0;
     int32_t algo_used = 0;
+    bool slots_used = false;  // the last count merged slots (tc_slots.hip)
 
     // profiling marks (see tc_prof_mark)
     bool prof = false;
@@ -245,6 +246,10 @@ tc_status tc_work_stats(tc_graph *g, int64_t *stats, hipStream_t s);
 tc_status tc_mid_prepare(tc_graph *g, hipStream_t s);
 tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
                        unsigned long long *found, hipStream_t s);
+// Flat graphs (tc_slots.hip): support per slot into the zeroed g->osup, then
+// everything that tc_aggregate fills.
+tc_status tc_count_slots(tc_graph *g, unsigned long long *found, hipStream_t s);
+tc_status tc_aggregate_slots(tc_graph *g, hipStream_t s);
 tc_status tc_mid_stats(tc_graph *g, unsigned long long *acc, hipStream_t s);
 // Words of the middle pivot's bit matrices, Σ_r Σ_{t<|N_H(r)|} ceil(t/32)
 // (device reduction and one read-back; the stored total once they exist).

@@ -140,3 +140,61 @@ def test_scan_forms(tclib, n):
     dst = np.concatenate([dst, np.array([n - 2, n - 3, n - 1], np.int32)])
     _say("scan forms, n", n)
     assert_parity(run_gpu(tclib, src, dst, n), native.o2_paper(src, dst, n))
+
+
+def _hub_and_clique(n):
+    """A star on the last vertex plus K_6 on the lowest ids: the hub is the top
+    rank, the others fill the ranks below."""
+    s, d, _ = gg.clique(6)
+    return (np.concatenate([s, np.full(n - 1, n - 1, np.int32)]),
+            np.concatenate([d, np.arange(n - 1, dtype=np.int32)]), n)
+
+
+# the slot merge: rows at its window of 8 entries, the ranks kept in LDS (2048)
+# and just more, the longest row that takes it (128) and one more
+SLOT_GRAPHS = {
+    **{f"K{k}": (lambda k=k: gg.clique(k)) for k in (2, 8, 9, 10, 17, 18, 129, 130)},
+    "top_ranks": lambda: _hub_and_clique(2048),
+    "top_ranks_past": lambda: _hub_and_clique(2049),
+    "triangle_free": lambda: gg.single_triangle_with_pendants((0, 4000, 1)),
+    "ba_cliques": lambda: gg.ba(6000, 12, seed=9),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SLOT_GRAPHS))
+def test_slot_merge_edges(tclib, name):
+    src, dst, n = SLOT_GRAPHS[name]()
+    _say("slot merge", name, "n", n)
+    assert_parity(run_gpu(tclib, src, dst, n), native.o2_paper(src, dst, n))
+    # the same handle after the middle pivot, and the algebraic numerator
+    g = tclib.Graph.from_edges(src, dst, n)
+    g.compute({"algorithm": tclib.TC_ALGO_MID_PIVOT})
+    a = g.results()
+    g.compute()
+    b = g.results()
+    for k in ("tri", "support", "triG", "num"):
+        np.testing.assert_array_equal(a[k], b[k])
+    np.testing.assert_array_equal(g.numerator_algebraic(), b["num"])
+    g.close()
+
+
+def test_slot_merge_batch(tclib):
+    # graphs that end inside wavefronts, with and without triangles
+    graphs = [gg.clique(3 + i % 9) if i % 3 else (np.arange(5, dtype=np.int32),
+                                                 np.arange(1, 6, dtype=np.int32), 7 + i % 60)
+              for i in range(90)]
+    po = np.cumsum([0] + [len(g[0]) for g in graphs])
+    vo = np.cumsum([0] + [g[2] for g in graphs])
+    g = tclib.Graph.batch(np.concatenate([x[0] for x in graphs]),
+                          np.concatenate([x[1] for x in graphs]), po, vo)
+    _say("slot merge batch", len(graphs))
+    g.compute()
+    r, eoff = g.results(), g.edge_offsets()
+    for i, (s, d, n) in enumerate(graphs):
+        ref = native.o2_paper(s, d, n)
+        np.testing.assert_array_equal(r["support"][eoff[i]:eoff[i + 1]], ref.sup)
+        np.testing.assert_array_equal(r["tri"][vo[i]:vo[i + 1]], ref.tri)
+        np.testing.assert_array_equal(r["num"][vo[i]:vo[i + 1]], ref.num)
+        np.testing.assert_array_equal(r["tc"][vo[i]:vo[i + 1]].view(np.uint64), ref.tc.view(np.uint64))
+        assert int(r["triG"][i]) == ref.triG
+    g.close()
