@@ -27,36 +27,44 @@ namespace {
 
 constexpr int RB = 8;
 constexpr int RADIX = 1 << RB;
-constexpr int SORT_BLOCK = 256;
-constexpr int SORT_WAVES = SORT_BLOCK / TC_WAVE;
-// Keys per thread: tiles of 8192 elements for elements (key and value) of
-// up to 8 bytes; bigger tiles mean longer runs per digit in the scatter's
-// stores.  Wider elements take tiles of 4096, since their registers would
-// otherwise leave one wavefront per SIMD, and are staged in two rounds
-// (keys, then values, through the same LDS buffer), which keeps their LDS
-// near 36 KB.
+// Shape of the big tiles: 8192 elements of up to 8 bytes (key and value) by 512
+// threads, 4096 of wider ones by 256; bigger tiles mean longer runs per digit
+// in the scatter's stores.  With 512 threads two workgroups of a CU keep 16
+// wavefronts resident under the same LDS (256 threads: 8, and twice the
+// registers); 5 M 8-byte keys 36 -> 31 us a pass, 2^28 of them 1.34 -> 1.27 ms
+// (1024 threads: 1.5 ms).  Wider elements are staged in two rounds (keys, then
+// values, through the same LDS buffer), which keeps their LDS near 43 KB and
+// three workgroups resident; 512 threads made their pass slower (2.25 against
+// 2.13 ms for 2.6e8).
 template <typename K, typename V, bool HAS_VAL>
-constexpr int sort_items() {
-    return (sizeof(K) + (HAS_VAL ? sizeof(V) : 0)) <= 8 ? 32 : 16;
+constexpr bool sort_wide() {
+    return sizeof(K) + (HAS_VAL ? sizeof(V) : 0) > 8;
 }
-// Below this many elements the big tiles would leave CUs idle: 8 keys per
-// thread (tiles of 2048) instead.
+template <typename K, typename V, bool HAS_VAL>
+constexpr int sort_block() {
+    return sort_wide<K, V, HAS_VAL>() ? 256 : 512;
+}
+constexpr int BIG_ITEMS = 16;
+// Below this many elements the big tiles would leave CUs idle: tiles of 2048,
+// 256 threads of 8 elements.
 constexpr int64_t SORT_BIG_TILES_MIN = (int64_t)1 << 22;
+constexpr int SMALL_BLOCK = 256;
 constexpr int SORT_SMALL_ITEMS = 8;
 // Up to this many tiles the scatter sums the tile counts itself: at 128 tiles
 // (2^18 keys) that is 128 KB out of the L2 per workgroup, about the time of
 // the launch that it saves.
 constexpr int64_t FEW_TILES = 128;
 
-static_assert(SORT_BLOCK == RADIX, "one digit per thread in the scatter's digit scans");
+static_assert(SMALL_BLOCK >= RADIX, "one digit per thread in the digit scans");
 
 struct NoVal {};
 
-template <typename K, int SORT_ITEMS, bool FEW>
+template <typename K, int SORT_BLOCK, int SORT_ITEMS, bool FEW>
 __global__ __launch_bounds__(SORT_BLOCK) void k_radix_hist(const K *__restrict__ keys, int64_t n,
                                                            int shift, uint32_t *__restrict__ counts,
                                                            int64_t tiles) {
     constexpr int SORT_TILE = SORT_BLOCK * SORT_ITEMS;
+    constexpr int SORT_WAVES = SORT_BLOCK / TC_WAVE;
     __shared__ uint32_t hist[SORT_WAVES][RADIX];
     for (int i = threadIdx.x; i < SORT_WAVES * RADIX; i += SORT_BLOCK) (&hist[0][0])[i] = 0;
     __syncthreads();
@@ -121,7 +129,8 @@ __global__ __launch_bounds__(ROWS_BLOCK) void k_radix_rows(uint32_t *__restrict_
     if (tid == 0) tot[blockIdx.x] = carry;
 }
 
-// Exclusive scan over the workgroup of one value per thread (digit).
+// Exclusive scan of one value per digit (the first RADIX threads; the others
+// pass 0).
 __device__ __forceinline__ uint32_t digit_scan(uint32_t x, uint32_t *wsum) {
     const int w = threadIdx.x / TC_WAVE;
     const uint32_t incl = tc_wave_incl_scan(x);
@@ -133,12 +142,13 @@ __device__ __forceinline__ uint32_t digit_scan(uint32_t x, uint32_t *wsum) {
     return before;
 }
 
-template <typename K, typename V, bool HAS_VAL, int SORT_ITEMS, bool FEW>
+template <typename K, typename V, bool HAS_VAL, int SORT_BLOCK, int SORT_ITEMS, bool FEW>
 __global__ __launch_bounds__(SORT_BLOCK) void k_radix_scatter(
     const K *__restrict__ kin, const V *__restrict__ vin, K *__restrict__ kout,
     V *__restrict__ vout, int64_t n, int shift, const uint32_t *__restrict__ counts,
     int64_t tiles, const uint32_t *__restrict__ tot, const uint32_t *__restrict__ vhi) {
     constexpr int SORT_TILE = SORT_BLOCK * SORT_ITEMS;
+    constexpr int SORT_WAVES = SORT_BLOCK / TC_WAVE;
     // The tile is first put in digit order in LDS, then written out by
     // consecutive threads to consecutive positions of each digit's run, so
     // the global stores coalesce.
@@ -207,35 +217,42 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_radix_scatter(
     }
     __syncthreads();
     // per digit: offsets of the waves, the tile total, and the global base
-    uint32_t tile_tot = 0;
     {
         __shared__ uint32_t wsum[SORT_WAVES];
-        const int d = threadIdx.x;  // SORT_BLOCK == RADIX
-        uint32_t run = 0;
+        const int d = threadIdx.x;
+        const bool own = d < RADIX;
+        uint32_t tile_tot = 0;
+        if (own) {
 #pragma unroll
-        for (int q = 0; q < SORT_WAVES; ++q) {
-            uint32_t c = wcnt[q][d];
-            wcnt[q][d] = run;
-            run += c;
+            for (int q = 0; q < SORT_WAVES; ++q) {
+                uint32_t c = wcnt[q][d];
+                wcnt[q][d] = tile_tot;
+                tile_tot += c;
+            }
         }
-        tile_tot = run;
         // keys of this digit in all tiles, and in those before this one
         uint32_t all = 0, before = 0;
         if constexpr (FEW) {
             const int nt = (int)tiles;
+            if (own) {
 #pragma unroll 16
-            for (int t = 0; t < nt; ++t) {
-                const uint32_t c = counts[t * RADIX + d];
-                all += c;
-                before += t < (int)blockIdx.x ? c : 0u;
+                for (int t = 0; t < nt; ++t) {
+                    const uint32_t c = counts[t * RADIX + d];
+                    all += c;
+                    before += t < (int)blockIdx.x ? c : 0u;
+                }
             }
-        } else {
+        } else if (own) {
             all = tot[d];
             before = counts[(int64_t)d * tiles + blockIdx.x];
         }
-        gbase[d] = digit_scan(all, wsum) + before;
+        const uint32_t gb = digit_scan(all, wsum) + before;
         // start of the digit within the tile
-        lbase[d] = digit_scan(tile_tot, wsum);
+        const uint32_t lb = digit_scan(tile_tot, wsum);
+        if (own) {
+            gbase[d] = gb;
+            lbase[d] = lb;
+        }
     }
     __syncthreads();
     // place of each item in the tile's digit order
@@ -274,17 +291,17 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_radix_scatter(
 }
 
 // counts: tiles * RADIX words, then the RADIX digit totals
-template <typename K, typename V, bool HAS_VAL, int ITEMS, bool FEW>
+template <typename K, typename V, bool HAS_VAL, int BLOCK, int ITEMS, bool FEW>
 tc_status radix_pass_form(const K *in, const V *vin, K *kout, V *vout, int64_t n, int shift,
                           uint32_t *counts, int64_t tiles, const uint32_t *vhi, hipStream_t s) {
     uint32_t *tot = counts + tiles * RADIX;
-    k_radix_hist<K, ITEMS, FEW><<<(unsigned)tiles, SORT_BLOCK, 0, s>>>(in, n, shift, counts, tiles);
+    k_radix_hist<K, BLOCK, ITEMS, FEW><<<(unsigned)tiles, BLOCK, 0, s>>>(in, n, shift, counts, tiles);
     TC_LAUNCHED();
     if constexpr (!FEW) {
         k_radix_rows<<<RADIX, ROWS_BLOCK, 0, s>>>(counts, tiles, tot);
         TC_LAUNCHED();
     }
-    k_radix_scatter<K, V, HAS_VAL, ITEMS, FEW><<<(unsigned)tiles, SORT_BLOCK, 0, s>>>(
+    k_radix_scatter<K, V, HAS_VAL, BLOCK, ITEMS, FEW><<<(unsigned)tiles, BLOCK, 0, s>>>(
         in, vin, kout, vout, n, shift, counts, tiles, tot, vhi);
     TC_LAUNCHED();
     return TC_OK;
@@ -294,20 +311,21 @@ tc_status radix_pass_form(const K *in, const V *vin, K *kout, V *vout, int64_t n
 template <typename K, typename V, bool HAS_VAL>
 tc_status radix_pass(const K *in, const V *vin, K *kout, V *vout, int64_t n, int shift,
                      uint32_t *counts, int64_t tiles, const uint32_t *vhi, hipStream_t s) {
-    if (tiles <= FEW_TILES && n < SORT_BIG_TILES_MIN)
-        return radix_pass_form<K, V, HAS_VAL, SORT_SMALL_ITEMS, true>(in, vin, kout, vout, n, shift,
-                                                                     counts, tiles, vhi, s);
-    if (n < SORT_BIG_TILES_MIN)
-        return radix_pass_form<K, V, HAS_VAL, SORT_SMALL_ITEMS, false>(in, vin, kout, vout, n, shift,
-                                                                      counts, tiles, vhi, s);
-    return radix_pass_form<K, V, HAS_VAL, sort_items<K, V, HAS_VAL>(), false>(
+    if (n >= SORT_BIG_TILES_MIN)
+        return radix_pass_form<K, V, HAS_VAL, sort_block<K, V, HAS_VAL>(), BIG_ITEMS, false>(
+            in, vin, kout, vout, n, shift, counts, tiles, vhi, s);
+    if (tiles <= FEW_TILES)
+        return radix_pass_form<K, V, HAS_VAL, SMALL_BLOCK, SORT_SMALL_ITEMS, true>(
+            in, vin, kout, vout, n, shift, counts, tiles, vhi, s);
+    return radix_pass_form<K, V, HAS_VAL, SMALL_BLOCK, SORT_SMALL_ITEMS, false>(
         in, vin, kout, vout, n, shift, counts, tiles, vhi, s);
 }
 
 template <typename K, typename V, bool HAS_VAL>
 int64_t sort_tiles(int64_t n) {
-    const int items = n >= SORT_BIG_TILES_MIN ? sort_items<K, V, HAS_VAL>() : SORT_SMALL_ITEMS;
-    return tc_div_up(n, (int64_t)SORT_BLOCK * items);
+    return tc_div_up(n, (int64_t)(n >= SORT_BIG_TILES_MIN
+                                      ? sort_block<K, V, HAS_VAL>() * BIG_ITEMS
+                                      : SMALL_BLOCK * SORT_SMALL_ITEMS));
 }
 
 // src, when given, is read by the first pass in place of *keys (which then
