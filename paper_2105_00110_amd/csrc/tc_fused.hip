@@ -1,7 +1,10 @@
 // Batched small graphs in one persistent launch.
 //
 // Every workgroup of k_fused_graphs pulls graph indices from a device
-// counter and runs the whole path on one graph with workgroup-local steps:
+// counter and runs the whole path on one graph with workgroup-local steps, in
+// one of three forms by the graph's size: everything in LDS (fused_small),
+// per-vertex arrays in LDS (fused_medium), everything in the workspace
+// (fused_large).  The steps, as the last one has them:
 //
 //   keys      each pair as lo * n + hi (lo < hi, ids local to the graph),
 //             self-loops as the sentinel n * n;
@@ -38,6 +41,7 @@
 #include <mutex>
 
 #include "tc_internal.h"
+#include "tc_small.h"
 
 namespace {
 
@@ -83,7 +87,6 @@ struct FusedLds {
     uint32_t tot[FUSED_RADIX];
     uint32_t wsum[WAVES];
     uint64_t wsum64[WAVES];
-    uint32_t bcast;
 };
 
 // Atomic add ordered for the workgroup.  Every array these touch belongs to
@@ -123,7 +126,7 @@ __device__ __forceinline__ int fused_bits(uint32_t max_value) {
 
 // Sum over the workgroup (every thread returns it).
 template <int BLOCK>
-__device__ uint64_t block_sum64(uint64_t x, FusedLds<BLOCK> &sh) {
+__device__ __forceinline__ uint64_t block_sum64(uint64_t x, FusedLds<BLOCK> &sh) {
     x = tc_wave_sum(x);
     if (__lane_id() == 0) sh.wsum64[threadIdx.x / TC_WAVE] = x;
     __syncthreads();
@@ -135,7 +138,7 @@ __device__ uint64_t block_sum64(uint64_t x, FusedLds<BLOCK> &sh) {
 }
 
 template <int BLOCK>
-__device__ uint32_t block_max32(uint32_t x, FusedLds<BLOCK> &sh) {
+__device__ __forceinline__ uint32_t block_max32(uint32_t x, FusedLds<BLOCK> &sh) {
     x = tc_wave_max(x);
     if (__lane_id() == 0) sh.wsum[threadIdx.x / TC_WAVE] = x;
     __syncthreads();
@@ -148,7 +151,7 @@ __device__ uint32_t block_max32(uint32_t x, FusedLds<BLOCK> &sh) {
 
 // Exclusive prefix of v[0..256) in place; threads below 256 hold one digit.
 template <int BLOCK>
-__device__ void scan256(uint32_t *v, FusedLds<BLOCK> &sh) {
+__device__ __forceinline__ void scan256(uint32_t *v, FusedLds<BLOCK> &sh) {
     static_assert(BLOCK >= FUSED_RADIX, "one digit per thread");
     const int tid = threadIdx.x;
     const uint32_t x = tid < FUSED_RADIX ? v[tid] : 0u;
@@ -168,7 +171,7 @@ __device__ void scan256(uint32_t *v, FusedLds<BLOCK> &sh) {
 // are ping-pong space.  One read of the keys counts the digits of every
 // pass (the multiset of keys is the same before each pass).
 template <int BLOCK, bool VAL>
-__device__ void block_sort(uint32_t *&k, uint32_t *&kt, uint32_t *&v, uint32_t *&vt, uint32_t n,
+__device__ __forceinline__ void block_sort(uint32_t *&k, uint32_t *&kt, uint32_t *&v, uint32_t *&vt, uint32_t n,
                            int bits, FusedLds<BLOCK> &sh) {
     constexpr int WAVES = FusedLds<BLOCK>::WAVES;
     constexpr int TILE = BLOCK * FUSED_ITEMS;
@@ -260,7 +263,7 @@ __device__ void block_sort(uint32_t *&k, uint32_t *&kt, uint32_t *&v, uint32_t *
 // The distinct keys of the sorted a[0..n) that lie below `limit`, in order,
 // written to out; returns their count.
 template <int BLOCK>
-__device__ uint32_t block_unique(const uint32_t *a, uint32_t n, uint32_t limit, uint32_t *out,
+__device__ __forceinline__ uint32_t block_unique(const uint32_t *a, uint32_t n, uint32_t limit, uint32_t *out,
                                  FusedLds<BLOCK> &sh) {
     constexpr int WAVES = FusedLds<BLOCK>::WAVES;
     const int w = threadIdx.x / TC_WAVE;
@@ -293,7 +296,7 @@ __device__ uint32_t block_unique(const uint32_t *a, uint32_t n, uint32_t limit, 
 // Writes the outputs of a graph that is not computed (status < 0): no
 // edges, zero counts and quotients for its vertices.
 template <int BLOCK>
-__device__ void fused_fail(const FusedArgs &a, int32_t g, int64_t va, int64_t n, int32_t st) {
+__device__ __forceinline__ void fused_fail(const FusedArgs &a, int32_t g, int64_t va, int64_t n, int32_t st) {
     for (int64_t v = threadIdx.x; v < n; v += BLOCK) {
         if (a.tri) a.tri[va + v] = 0;
         if (a.num) a.num[va + v] = 0;
@@ -306,36 +309,615 @@ __device__ void fused_fail(const FusedArgs &a, int32_t g, int64_t va, int64_t n,
     }
 }
 
-template <int BLOCK>
-__device__ void fused_one_graph(const FusedArgs &a, int32_t g, FusedLds<BLOCK> &sh) {
-    const int tid = threadIdx.x;
-    const int64_t pa = a.pair_off[g], pb = a.pair_off[g + 1];
-    const int64_t va = a.vtx_off[g], vb = a.vtx_off[g + 1];
-    // offsets outside the arrays, or decreasing: nothing of this graph is
-    // touched but its status
-    if (pa < 0 || pb < pa || pb > a.P || va < 0 || vb < va || vb > a.N) {
-        if (tid == 0) {
-            a.num_edges[g] = 0;
-            a.status[g] = TC_ERR_INVALID_ARG;
-        }
-        return;
-    }
-    if (vb - va > FUSED_MAX_N || pb - pa > 0x7FFFFFFFll) {
-        fused_fail<BLOCK>(a, g, va, vb - va, TC_ERR_UNSUPPORTED);
-        return;
-    }
-    const uint32_t n = (uint32_t)(vb - va), P = (uint32_t)(pb - pa);
-    const uint32_t sentinel = n * n;  // n <= 65535: below 2^32
+// Any thread's flag, as a scalar: branches on it stay uniform.
+__device__ __forceinline__ bool wg_any(bool x) {
+    return __builtin_amdgcn_readfirstlane(__syncthreads_or(x)) != 0;
+}
 
-    // workspace of this graph: 5 pair arrays, then the vertex arrays
-    uint32_t *A = reinterpret_cast<uint32_t *>(a.ws + FUSED_HEADER) + 5 * pa;
-    uint32_t *B = A + P, *C = B + P, *D = C + P, *E = D + P;
-    unsigned char *vbase = a.ws + FUSED_HEADER + pair_region(a.P) + FUSED_VTX_BYTES * va +
-                           FUSED_GRAPH_BYTES * (int64_t)g;
-    uint64_t *triR = reinterpret_cast<uint64_t *>(vbase);
-    uint64_t *numR = triR + n;
-    uint32_t *deg = reinterpret_cast<uint32_t *>(numR + n);
-    uint32_t *rank = deg + n, *perm = rank + n, *vtmp = perm + n, *orp = vtmp + n;  // orp[n+1]
+// A graph of the batch: where its pairs and vertices lie, and its slice of the
+// workspace (five uint32 arrays per pair, then the vertex arrays).
+struct GraphRef {
+    int32_t g;
+    int64_t pa, va;
+    uint32_t n, P;
+    uint32_t *A, *B, *C, *D, *E;
+    uint64_t *triR, *numR;
+    uint32_t *deg, *rank, *perm, *vtmp, *orp;  // orp[n + 1]
+};
+
+// ---------------------------------------------------------------------------
+// Graphs that fit LDS (at most 16 pairs per thread): tc_small.h's steps, the
+// slot merge and the sums in LDS, outputs straight from registers.  Bound by
+// LDS and VALU work between some forty barriers; in device memory the same
+// steps were bound by the memory latency that 16 wavefronts cannot cover (five
+// ER graphs of 10 k pairs at once: 237 us a call before, 90 us so).
+// ---------------------------------------------------------------------------
+template <int BLOCK>
+__device__ __forceinline__ void fused_small(const FusedArgs &a, const GraphRef q, tc_small::Lds<BLOCK> &L) {
+    using namespace tc_small;
+    constexpr int MW = 4;
+    const uint32_t n = q.n, P = q.P;
+    const int b = bits_of(n > 1 ? n - 1 : 1);
+    const int itn = P == 0 ? 1 : (int)((P + BLOCK - 1) / BLOCK);
+    const uint32_t none = (uint32_t)((1ull << (2 * b)) - 1ull);
+    uint32_t key[ITEMS];
+    bool bad = false;
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        key[it] = none;
+        if (it < itn) {
+            const uint32_t i = elem(it, itn);
+            if (i < P) {
+                const uint32_t x = (uint32_t)a.src[q.pa + i], y = (uint32_t)a.dst[q.pa + i];
+                if (x >= n || y >= n) bad = true;
+                else if (x != y) key[it] = (x < y ? x << b | y : y << b | x);
+            }
+        }
+    }
+    if (wg_any(bad)) {
+        fused_fail<BLOCK>(a, q.g, q.va, n, TC_ERR_VERTEX_RANGE);
+        __syncthreads();
+        return;
+    }
+    Edges E;
+    const uint32_t m = canonical<BLOCK>(key, itn, b, E, L);
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it)
+        if (E.ends[it] != NONE) {
+            if (a.eu) a.eu[q.pa + E.tag[it]] = (int32_t)(E.ends[it] >> 16);
+            if (a.ev) a.ev[q.pa + E.tag[it]] = (int32_t)(E.ends[it] & 0xFFFFu);
+        }
+    (void)degree_rank<BLOCK>(E, n, L, [](uint32_t, uint32_t) {});
+    (void)orient<BLOCK>(E, n, m, L);
+    // count: the tail of N_H(r) after c merged with N_H(c); supports as 16-bit
+    // halves (a support is below n <= 2^12)
+    for (uint32_t i = threadIdx.x; i < (m + 1) / 2; i += BLOCK) L.cnt[i] = 0;
+    for (uint32_t v = threadIdx.x; v < n; v += BLOCK) L.tri[v] = L.num[v] = 0;
+    __syncthreads();
+    const auto add_sup = [&](uint32_t s, uint32_t x) {
+        atomicAdd(&L.cnt[s >> 1], x << (16 * (s & 1u)));
+    };
+    const auto support = [&](uint32_t s) { return (L.cnt[s >> 1] >> (16 * (s & 1u))) & 0xFFFFu; };
+#pragma unroll 1
+    for (uint32_t s = threadIdx.x; s < m; s += BLOCK) {
+        const uint32_t r = L.xchg[s] >> 16, c = L.xchg[s] & 0xFFFFu;
+        uint32_t i = s + 1, j = L.orp[c], t = 0;
+        const uint32_t ie = L.orp[r + 1], je = L.orp[c + 1];
+        while (i < ie && j < je) {
+            uint32_t x[MW], y[MW];
+#pragma unroll
+            for (int e = 0; e < MW; ++e) {
+                x[e] = L.xchg[i + e < ie ? i + e : i] & 0xFFFFu;
+                y[e] = L.xchg[j + e < je ? j + e : j] & 0xFFFFu;
+            }
+#pragma unroll
+            for (int e = 0; e < MW; ++e) {
+                x[e] = i + e < ie ? x[e] : 0xFFFFFFFFu;
+                y[e] = j + e < je ? y[e] : 0xFFFFFFFEu;
+            }
+            const uint32_t lim = x[MW - 1] < y[MW - 1] ? x[MW - 1] : y[MW - 1];
+            uint32_t na = 0, nb = 0;
+#pragma unroll
+            for (int e = 0; e < MW; ++e) {
+                na += x[e] <= lim ? 1u : 0u;
+                nb += y[e] <= lim ? 1u : 0u;
+                int f = -1;
+#pragma unroll
+                for (int p = 0; p < MW; ++p) f = x[e] == y[p] ? p : f;
+                if (f >= 0) {
+                    add_sup(i + e, 1u);
+                    add_sup(j + (uint32_t)f, 1u);
+                    ++t;
+                }
+            }
+            i += na;
+            j += nb;
+        }
+        if (t) add_sup(s, t);
+    }
+    __syncthreads();
+    if (a.sup) {
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (E.ends[it] != NONE)
+                a.sup[q.pa + (E.tag[it] & 0xFFFFu)] = support(E.tag[it] >> 16);
+    }
+    // sums over every vertex's edges: twice the triangles, then the numerator
+    // (all below 2^32: at most 16384 edges make at most 988000 triangles)
+    uint32_t *const tri = L.tri, *const num = L.num;
+    uint32_t local = 0;
+    for (uint32_t s = threadIdx.x; s < m; s += BLOCK) {
+        const uint32_t x = support(s);
+        if (x) {
+            atomicAdd(&tri[L.xchg[s] >> 16], x);
+            atomicAdd(&tri[L.xchg[s] & 0xFFFFu], x);
+            local += x;
+        }
+    }
+    const uint32_t three_t = wg_sum<BLOCK>(local, L.wsum);  // has the barrier
+    bool odd = three_t % 3 != 0;
+    for (uint32_t s = threadIdx.x; s < m; s += BLOCK) {
+        const uint32_t r = L.xchg[s] >> 16, c = L.xchg[s] & 0xFFFFu;
+        const uint32_t f = support(s) ? 1u : 3u, tr = tri[r] >> 1, tcn = tri[c] >> 1;
+        if (tcn) atomicAdd(&num[r], f * tcn);
+        if (tr) atomicAdd(&num[c], f * tr);
+    }
+    __syncthreads();
+    const uint64_t tg = three_t / 3;
+    for (uint32_t v = threadIdx.x; v < n; v += BLOCK) {
+        const uint32_t r = L.rank[v];
+        odd |= (tri[r] & 1u) != 0;
+        const uint64_t t = tri[r] >> 1, x = num[r] + t;
+        if (a.tri) a.tri[q.va + v] = t;
+        if (a.num) a.num[q.va + v] = x;
+        if (a.tc) a.tc[q.va + v] = tg == 0 ? 0.0 : __ddiv_rn((double)x, (double)(3 * tg));
+    }
+    odd = wg_any(odd);
+    if (threadIdx.x == 0) {
+        a.num_edges[q.g] = m;
+        if (a.triG) a.triG[q.g] = tg;
+        a.status[q.g] = odd ? TC_ERR_DEVICE : (tg == 0 ? TC_TRIANGLE_FREE : TC_OK);
+    }
+    __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// Graphs of up to 2^20 pairs whose per-vertex arrays fit LDS: the pairs and
+// slots stay in the workspace, read and written in tiles of 8 or 16 elements a
+// thread, all loads of a tile issued before the first use; every per-vertex
+// count, offset, rank and sum that the edges gather or add to is in LDS.  Bound
+// by the memory latency of one workgroup's 16 wavefronts, so loads in flight
+// count: a loop over single elements waits a round trip for each (4096 BA
+// graphs: 25.8 ms before, 14.9 ms so, of which the merge's random rows take 8.4).
+// ---------------------------------------------------------------------------
+template <int BLOCK>
+struct Medium {
+    static constexpr uint32_t NMAX = 21 * BLOCK;
+    static constexpr uint32_t PMAX = 1u << 20;
+    static constexpr uint32_t LT = 8 * BLOCK;   // elements per tile of the loops
+    static constexpr uint32_t ST = 16 * BLOCK;  // of the sort
+    // longest oriented row: d+ neighbours of degree >= d+ each, so d+^2 <= 2m
+    static constexpr uint32_t HALO = 1536;
+    // bytes: per-vertex words and the row sort's tile with its halo, or a rank
+    // and a cursor per vertex, or the sort's exchange and digit counts
+    static constexpr size_t ROWS = 4 * (size_t)NMAX + 4 * (LT + 2 * HALO);
+    static constexpr size_t ORIENT = 6 * (size_t)NMAX;
+    static constexpr size_t SORT = 4 * (size_t)ST + 4 * (size_t)(BLOCK / TC_WAVE) * tc_small::RADIX;
+    static constexpr size_t BYTES = ROWS > ORIENT ? (ROWS > SORT ? ROWS : SORT)
+                                                  : (ORIENT > SORT ? ORIENT : SORT);
+};
+
+// Digit counts of up to 4 passes, running bases during a pass; scan words.
+template <int BLOCK>
+struct MediumTail {
+    uint32_t hist[4][tc_small::RADIX];
+    uint32_t wsum[BLOCK / TC_WAVE + 1];
+};
+
+// The arena of a workgroup, used by one tier at a time.
+template <int BLOCK>
+union FusedArena {
+    tc_small::Lds<BLOCK> small;
+    FusedLds<BLOCK> large;
+    struct {
+        unsigned char raw[Medium<BLOCK>::BYTES];
+        MediumTail<BLOCK> tail;
+    } medium;
+};
+
+// Passes and digit width of a sort on `bits` bits (at most 8 a pass).
+struct SortPlan {
+    int shift, bits, passes, width;
+    __device__ SortPlan(int sh, int bt) : shift(sh), bits(bt) {
+        passes = (bits + 7) / 8;
+        width = (bits + passes - 1) / passes;
+    }
+    __device__ int at(int p) const { return shift + p * width; }
+    __device__ int bits_at(int p) const {
+        const int left = bits - p * width;
+        return width < left ? width : left;
+    }
+};
+
+template <int BLOCK>
+__device__ __forceinline__ void medium_hist(const SortPlan &sp, uint32_t key, MediumTail<BLOCK> &T) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+        if (p < sp.passes)
+            atomicAdd(&T.hist[p][(key >> sp.at(p)) & ((1u << sp.bits_at(p)) - 1u)], 1u);
+}
+
+// Stable sort of k[0..n) (result in k, kt the other buffer) with the digit
+// counts of every pass already in T.hist.
+// Element i of a slice of under 2^32 bytes: a scalar base and a 32-bit offset
+// (64-bit addresses for every load in flight cost the tiles their registers).
+template <typename T>
+__device__ __forceinline__ T &at(T *base, uint32_t i) {
+    return *reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(base) + (uintptr_t)(i * (uint32_t)sizeof(T)));
+}
+
+template <int BLOCK>
+__device__ __forceinline__ void medium_sort(uint32_t *&k, uint32_t *&kt, uint32_t n,
+                                            const SortPlan &sp, unsigned char *raw,
+                                            MediumTail<BLOCK> &T) {
+    using namespace tc_small;
+    constexpr uint32_t ST = Medium<BLOCK>::ST;
+    uint32_t *xchg = reinterpret_cast<uint32_t *>(raw);
+    uint32_t(*wcnt)[RADIX] = reinterpret_cast<uint32_t(*)[RADIX]>(raw + 4 * (size_t)ST);
+    const int tid = threadIdx.x, w = tid / TC_WAVE;
+    for (int p = 0; p < sp.passes; ++p) {
+        uint32_t *base = T.hist[p];
+        uint32_t all;
+        const uint32_t c0 = tid < RADIX ? base[tid] : 0u;
+        const uint32_t b0 = wg_scan<BLOCK>(c0, &all, T.wsum);
+        if (tid < RADIX) base[tid] = b0;
+        const int sh = sp.at(p), wd = sp.bits_at(p);
+        const uint32_t mask = (1u << wd) - 1u;
+        for (uint32_t t0 = 0; t0 < n; t0 += ST) {
+            const uint32_t tn = n - t0 < ST ? n - t0 : ST;
+            const int itn = (int)((tn + BLOCK - 1) / BLOCK);
+            uint32_t key[ITEMS], place[ITEMS];
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) {
+                const uint32_t i = elem(it, itn);
+                key[it] = it < itn && i < tn ? at(k, t0 + i) : NONE;
+            }
+            digit_ranks<BLOCK, ITEMS>(key, itn, sh, wd, place, wcnt);
+            __syncthreads();
+            const uint32_t cnt = digit_starts<BLOCK>(wcnt, T.wsum);
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it)
+                if (it < itn) xchg[place[it] + wcnt[w][(key[it] >> sh) & mask]] = key[it];
+            __syncthreads();
+            // absent places (all ones) are last in the tile
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it) {
+                const uint32_t i = it * BLOCK + tid;
+                if (i < tn) {
+                    const uint32_t x = xchg[i], d = (x >> sh) & mask;
+                    at(kt, base[d] + i - wcnt[0][d]) = x;
+                }
+            }
+            __syncthreads();
+            if (tid < RADIX) base[tid] += cnt;
+        }
+        __syncthreads();
+        uint32_t *t = k;
+        k = kt;
+        kt = t;
+    }
+}
+
+// An oriented edge on its way to its row.
+struct alignas(4) Entry {
+    uint32_t ends, edge;
+};
+
+template <int BLOCK>
+__device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef q, unsigned char *raw,
+                             MediumTail<BLOCK> &T) {
+    using namespace tc_small;
+    constexpr uint32_t NMAX = Medium<BLOCK>::NMAX, LT = Medium<BLOCK>::LT, HALO = Medium<BLOCK>::HALO;
+    constexpr int U = 8;  // elements per thread of a tile
+    const uint32_t n = q.n, P = q.P;
+    const int tid = threadIdx.x;
+    // the graph's own slices
+    const uint32_t *const src = reinterpret_cast<const uint32_t *>(a.src) + q.pa;
+    const uint32_t *const dst = reinterpret_cast<const uint32_t *>(a.dst) + q.pa;
+    const int b = bits_of(n > 1 ? n - 1 : 1);
+    const uint32_t none = (uint32_t)((1ull << (2 * b)) - 1ull), vm = (1u << b) - 1u;
+    uint32_t *const words = reinterpret_cast<uint32_t *>(raw);        // one per vertex
+    uint32_t *const second = reinterpret_cast<uint32_t *>(raw) + NMAX;  // after them
+    for (int i = tid; i < 4 * RADIX; i += BLOCK) (&T.hist[0][0])[i] = 0;
+    __syncthreads();
+    // keys lo << b | hi (self-loops all ones), with the id range check and the
+    // digit counts of their sort
+    const SortPlan kp(0, 2 * b);
+    bool bad = false;
+    for (uint32_t t0 = 0; t0 < P; t0 += LT) {
+        uint32_t x[U], y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = t0 + u * BLOCK + tid;
+            x[u] = i < P ? at(src, i) : 0u;
+            y[u] = i < P ? at(dst, i) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = t0 + u * BLOCK + tid;
+            if (i < P) {
+                uint32_t key = none;
+                if (x[u] >= n || y[u] >= n) bad = true;
+                else if (x[u] != y[u]) key = x[u] < y[u] ? x[u] << b | y[u] : y[u] << b | x[u];
+                at(q.A, i) = key;
+                medium_hist<BLOCK>(kp, key, T);
+            }
+        }
+    }
+    if (wg_any(bad)) {
+        fused_fail<BLOCK>(a, q.g, q.va, n, TC_ERR_VERTEX_RANGE);
+        __syncthreads();
+        return;
+    }
+    uint32_t *k = q.A, *kt = q.B;
+    medium_sort<BLOCK>(k, kt, P, kp, raw, T);
+    // canonical edges (to C, and eu / ev) with the degrees in LDS
+    for (uint32_t v = tid; v < n; v += BLOCK) words[v] = 0;
+    __syncthreads();
+    uint32_t m = 0;
+    for (uint32_t t0 = 0; t0 < P; t0 += LT) {
+        uint32_t key[U], prev[U], pos[U];
+        bool keep[U];
+        uint32_t mine = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = t0 + elem(u, U);
+            key[u] = i < P ? at(k, i) : none;
+            prev[u] = i > 0 && i < P ? at(k, i - 1) : none;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            keep[u] = key[u] != none && prev[u] != key[u];
+            const uint64_t bal = __ballot(keep[u]);
+            pos[u] = mine + (uint32_t)__popcll(bal & tc_lanemask_lt());
+            mine += (uint32_t)__popcll(bal);
+        }
+        uint32_t all;
+        const uint32_t first = wg_scan<BLOCK>(__lane_id() == 0 ? mine : 0u, &all, T.wsum);
+        const uint32_t base = m + __shfl(first, 0, TC_WAVE);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (keep[u]) {
+                const uint32_t e = base + pos[u], lo = key[u] >> b, hi = key[u] & vm;
+                at(q.C, e) = key[u];
+                if (a.eu) at(a.eu + q.pa, e) = (int32_t)lo;
+                if (a.ev) at(a.ev + q.pa, e) = (int32_t)hi;
+                atomicAdd(&words[lo], 1u);
+                atomicAdd(&words[hi], 1u);
+            }
+        m += all;
+    }
+    __syncthreads();
+    // order (degree, id): degree << 16 | id, stable on the degree's bits
+    uint32_t dmax = 0;
+    for (uint32_t v = tid; v < n; v += BLOCK) dmax = words[v] > dmax ? words[v] : dmax;
+    dmax = wg_max<BLOCK>(dmax, T.wsum);
+    const SortPlan rp(16, bits_of(dmax));
+    for (int i = tid; i < 4 * RADIX; i += BLOCK) (&T.hist[0][0])[i] = 0;
+    __syncthreads();
+    for (uint32_t v = tid; v < n; v += BLOCK) {
+        const uint32_t key = words[v] << 16 | v;
+        at(q.deg, v) = key;
+        medium_hist<BLOCK>(rp, key, T);
+    }
+    __syncthreads();
+    k = q.deg;
+    kt = q.vtmp;
+    medium_sort<BLOCK>(k, kt, n, rp, raw, T);
+    uint16_t *const rank = reinterpret_cast<uint16_t *>(second);
+    for (uint32_t v = tid; v < n; v += BLOCK) words[v] = 0;
+    for (uint32_t r = tid; r < n; r += BLOCK) {
+        const uint32_t v = at(k, r) & 0xFFFFu;
+        rank[v] = (uint16_t)r;
+        at(q.rank, v) = r;
+    }
+    __syncthreads();
+    // orientation: row lengths, their offsets as cursors, then every edge into
+    // its row as (lower rank << 16 | higher rank, edge), any order: one 8-byte
+    // store per edge (A and B), since each store of the scatter is a sector
+    Entry *const entry = reinterpret_cast<Entry *>(q.A);
+    for (int pass = 0; pass < 2; ++pass) {
+        for (uint32_t t0 = 0; t0 < m; t0 += LT) {
+            uint32_t key[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t e = t0 + u * BLOCK + tid;
+                key[u] = e < m ? at(q.C, e) : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t e = t0 + u * BLOCK + tid;
+                if (e < m) {
+                    const uint32_t x = rank[key[u] >> b], y = rank[key[u] & vm];
+                    const uint32_t r = x < y ? x : y, h = x < y ? y : x;
+                    const uint32_t s = atomicAdd(&words[r], 1u);
+                    if (pass == 1) {
+                        at(entry, s) = Entry{r << 16 | h, e};
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (pass == 0) {
+            constexpr int PER = (int)(NMAX / BLOCK);
+            uint32_t sum = 0, all;
+            const uint32_t r0 = tid * PER;
+            for (int j = 0; j < PER; ++j) sum += r0 + j < n ? words[r0 + j] : 0u;
+            uint32_t off = wg_scan<BLOCK>(sum, &all, T.wsum);
+            for (int j = 0; j < PER; ++j)
+                if (r0 + j < n) {
+                    const uint32_t d = words[r0 + j];
+                    words[r0 + j] = off;
+                    off += d;
+                }
+            __syncthreads();
+        }
+    }
+    // words[r] is now the end of row r.  Each row in order of the higher rank:
+    // an entry's place is the number of smaller ones in its row, counted in an
+    // LDS copy of the tile and the rows that reach into it
+    const auto row_start = [&](uint32_t r) { return r > 0 ? words[r - 1] : 0u; };
+    uint32_t *const tile = second, *const ocol = q.D, *const o2e = q.E;
+    for (uint32_t t0 = 0; t0 < m; t0 += LT) {
+        const uint32_t lo = t0 > HALO ? t0 - HALO : 0u;
+        const uint32_t hi = m - t0 > LT + HALO ? t0 + LT + HALO : m;
+        for (uint32_t i = lo + tid; i < hi; i += BLOCK) tile[i - lo] = at(entry, i).ends;
+        uint32_t e[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t s = t0 + u * BLOCK + tid;
+            e[u] = s < m ? at(entry, s).edge : 0u;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t s = t0 + u * BLOCK + tid;
+            if (s < m) {
+                const uint32_t me = tile[s - lo], r = me >> 16;
+                const uint32_t ra = row_start(r), re = words[r];
+                uint32_t to = ra;
+                for (uint32_t i = ra; i < re; ++i) to += tile[i - lo] < me ? 1u : 0u;
+                at(ocol, to) = me;
+                at(o2e, to) = e[u];
+            }
+        }
+        __syncthreads();
+    }
+    // count: the tail of N_H(r) after c merged with N_H(c), supports added to
+    // the canonical edges (so that they leave in order).  A lane goes on to its
+    // next slot as soon as its merge ends, without waiting for the longest
+    // merge of the wavefront
+    uint32_t *const esup = q.A;  // the entries are no longer needed
+    for (uint32_t e = tid; e < m; e += BLOCK) at(esup, e) = 0;
+    __syncthreads();
+    {
+        uint32_t s = tid, t = 0, i = 0, ie = 0, j = 0, je = 0;
+        uint32_t w = s < m ? at(ocol, s) : 0u;
+        bool open = false;  // slot s is being merged
+        for (;;) {
+            while (s < m && !(open && i < ie && j < je)) {
+                if (open) {
+                    if (t) wg_add(&at(esup, at(o2e, s)), t);
+                    s += BLOCK;
+                    if (s >= m) break;
+                    w = at(ocol, s);
+                }
+                const uint32_t c = w & 0xFFFFu;
+                i = s + 1;
+                ie = words[w >> 16];
+                j = row_start(c);
+                je = words[c];
+                t = 0;
+                open = true;
+            }
+            if (s >= m) break;
+            // windows may reach past their row, and past the last one into the
+            // array that follows
+            uint32_t x[8], y[8], na, nb, hits, where;
+            load8(&at(ocol, i), x);
+            load8(&at(ocol, j), y);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                x[e] &= 0xFFFFu;
+                y[e] &= 0xFFFFu;
+            }
+            merge_round(x, y, ie - i, je - j, na, nb, hits, where);
+            t += (uint32_t)__popc(hits);
+            while (hits) {
+                const uint32_t e = (uint32_t)__ffs((int)hits) - 1u;
+                hits &= hits - 1u;
+                wg_add(&at(esup, at(o2e, i + e)), 1u);
+                wg_add(&at(esup, at(o2e, j + ((where >> (4 * e)) & 15u))), 1u);
+            }
+            i += na;
+            j += nb;
+        }
+    }
+    __syncthreads();
+    // twice the triangles per rank, in LDS (at most 2^20 edges make at most
+    // 5.1e8 triangles: every sum here is below 2^32), with the supports out
+    for (uint32_t v = tid; v < n; v += BLOCK) {
+        words[v] = 0;
+        rank[v] = (uint16_t)at(q.rank, v);
+    }
+    __syncthreads();
+    uint32_t local = 0;
+    for (uint32_t t0 = 0; t0 < m; t0 += LT) {
+        uint32_t key[U], x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t e = t0 + u * BLOCK + tid;
+            key[u] = e < m ? at(q.C, e) : 0u;
+            x[u] = e < m ? at(esup, e) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t e = t0 + u * BLOCK + tid;
+            if (e < m && a.sup) at(a.sup + q.pa, e) = x[u];
+            if (x[u]) {
+                atomicAdd(&words[rank[key[u] >> b]], x[u]);
+                atomicAdd(&words[rank[key[u] & vm]], x[u]);
+                local += x[u];
+            }
+        }
+    }
+    const uint32_t three_t = wg_sum<BLOCK>(local, T.wsum);  // has the barrier
+    bool odd = three_t % 3 != 0;
+    uint32_t *const tri = reinterpret_cast<uint32_t *>(q.triR);
+    for (uint32_t r = tid; r < n; r += BLOCK) {
+        const uint32_t t2 = words[r];
+        odd |= (t2 & 1u) != 0;
+        at(tri, r) = t2 >> 1;
+        words[r] = 0;
+    }
+    __syncthreads();
+    // numerator: weight 1 for triangle neighbours (support > 0), 3 for others
+    for (uint32_t t0 = 0; t0 < m; t0 += LT) {
+        uint32_t key[U], x[U], tl[U], th[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t e = t0 + u * BLOCK + tid;
+            key[u] = e < m ? at(q.C, e) : 0u;
+            x[u] = e < m ? at(esup, e) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            key[u] = (uint32_t)rank[key[u] >> b] << 16 | rank[key[u] & vm];
+            tl[u] = at(tri, key[u] >> 16);
+            th[u] = at(tri, key[u] & 0xFFFFu);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t e = t0 + u * BLOCK + tid;
+            if (e < m) {
+                const uint32_t f = x[u] ? 1u : 3u;
+                if (th[u]) atomicAdd(&words[key[u] >> 16], f * th[u]);
+                if (tl[u]) atomicAdd(&words[key[u] & 0xFFFFu], f * tl[u]);
+            }
+        }
+    }
+    __syncthreads();
+    const uint64_t tg = three_t / 3;
+    for (uint32_t v = tid; v < n; v += BLOCK) {
+        const uint32_t r = at(q.rank, v);
+        const uint64_t t = at(tri, r), x = words[r] + t;
+        if (a.tri) a.tri[q.va + v] = t;
+        if (a.num) a.num[q.va + v] = x;
+        if (a.tc) a.tc[q.va + v] = tg == 0 ? 0.0 : __ddiv_rn((double)x, (double)(3 * tg));
+    }
+    odd = wg_any(odd);
+    if (tid == 0) {
+        a.num_edges[q.g] = m;
+        if (a.triG) a.triG[q.g] = tg;
+        a.status[q.g] = odd ? TC_ERR_DEVICE : (tg == 0 ? TC_TRIANGLE_FREE : TC_OK);
+    }
+    __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// Every other graph (more vertices than LDS holds, or more pairs): all arrays
+// in the workspace.
+// ---------------------------------------------------------------------------
+template <int BLOCK>
+__device__ __forceinline__ void fused_large(const FusedArgs &a, const GraphRef q, FusedLds<BLOCK> &sh) {
+    const int tid = threadIdx.x;
+    const int32_t g = q.g;
+    const int64_t pa = q.pa, va = q.va;
+    const uint32_t n = q.n, P = q.P;
+    const uint32_t sentinel = n * n;  // n <= 65535: below 2^32
+    uint32_t *A = q.A, *B = q.B, *C = q.C, *D = q.D, *E = q.E;
+    uint64_t *triR = q.triR, *numR = q.numR;
+    uint32_t *deg = q.deg, *rank = q.rank, *perm = q.perm, *vtmp = q.vtmp, *orp = q.orp;
 
     // keys, with the id range check
     bool bad = false;
@@ -350,7 +932,7 @@ __device__ void fused_one_graph(const FusedArgs &a, int32_t g, FusedLds<BLOCK> &
         }
         A[i] = key;
     }
-    if (__syncthreads_or(bad)) {
+    if (wg_any(bad)) {
         fused_fail<BLOCK>(a, g, va, n, TC_ERR_VERTEX_RANGE);
         __syncthreads();
         return;
@@ -553,6 +1135,54 @@ __device__ void fused_one_graph(const FusedArgs &a, int32_t g, FusedLds<BLOCK> &
     __syncthreads();
 }
 
+
+template <int BLOCK>
+__device__ __forceinline__ void fused_one_graph(const FusedArgs &a, int32_t g, FusedArena<BLOCK> &sh) {
+    const int tid = threadIdx.x;
+    const int64_t pa = a.pair_off[g], pb = a.pair_off[g + 1];
+    const int64_t va = a.vtx_off[g], vb = a.vtx_off[g + 1];
+    // offsets outside the arrays, or decreasing: nothing of this graph is
+    // touched but its status
+    if (pa < 0 || pb < pa || pb > a.P || va < 0 || vb < va || vb > a.N) {
+        if (tid == 0) {
+            a.num_edges[g] = 0;
+            a.status[g] = TC_ERR_INVALID_ARG;
+        }
+        return;
+    }
+    if (vb - va > FUSED_MAX_N || pb - pa > 0x7FFFFFFFll) {
+        fused_fail<BLOCK>(a, g, va, vb - va, TC_ERR_UNSUPPORTED);
+        return;
+    }
+    GraphRef q;
+    q.g = g;
+    q.pa = pa;
+    q.va = va;
+    q.n = (uint32_t)(vb - va);
+    q.P = (uint32_t)(pb - pa);
+    // workspace of this graph: 5 pair arrays, then the vertex arrays
+    q.A = reinterpret_cast<uint32_t *>(a.ws + FUSED_HEADER) + 5 * pa;
+    q.B = q.A + q.P;
+    q.C = q.B + q.P;
+    q.D = q.C + q.P;
+    q.E = q.D + q.P;
+    unsigned char *vbase = a.ws + FUSED_HEADER + pair_region(a.P) + FUSED_VTX_BYTES * va +
+                           FUSED_GRAPH_BYTES * (int64_t)g;
+    q.triR = reinterpret_cast<uint64_t *>(vbase);
+    q.numR = q.triR + q.n;
+    q.deg = reinterpret_cast<uint32_t *>(q.numR + q.n);
+    q.rank = q.deg + q.n;
+    q.perm = q.rank + q.n;
+    q.vtmp = q.perm + q.n;
+    q.orp = q.vtmp + q.n;
+    if (q.P <= (uint32_t)tc_small::Lds<BLOCK>::CAP && q.n <= (uint32_t)tc_small::Lds<BLOCK>::NMAX)
+        fused_small<BLOCK>(a, q, sh.small);
+    else if (q.P <= Medium<BLOCK>::PMAX && q.n <= Medium<BLOCK>::NMAX)
+        fused_medium<BLOCK>(a, q, sh.medium.raw, sh.medium.tail);
+    else
+        fused_large<BLOCK>(a, q, sh.large);
+}
+
 __global__ void k_fused_init(unsigned char *ws) {
     if (threadIdx.x == 0) reinterpret_cast<uint32_t *>(ws)[0] = 0;
 }
@@ -561,14 +1191,15 @@ __global__ void k_fused_init(unsigned char *ws) {
 // so that two of them fit on a compute unit
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_fused_graphs(FusedArgs a) {
-    __shared__ FusedLds<BLOCK> sh;
+    __shared__ FusedArena<BLOCK> sh;
+    __shared__ uint32_t next;
     uint32_t *head = reinterpret_cast<uint32_t *>(a.ws);
     for (;;) {
-        if (threadIdx.x == 0) sh.bcast = atomicAdd(head, 1u);
+        if (threadIdx.x == 0) next = atomicAdd(head, 1u);
         __syncthreads();
         // the same value in every lane: keep it (and what derives from it) in
         // scalar registers
-        const uint32_t slot = __builtin_amdgcn_readfirstlane(sh.bcast);
+        const uint32_t slot = __builtin_amdgcn_readfirstlane(next);
         __syncthreads();
         if (slot >= (uint32_t)a.G) break;
         const int32_t g = a.order ? __builtin_amdgcn_readfirstlane(a.order[slot]) : (int32_t)slot;

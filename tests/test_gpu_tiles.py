@@ -10,6 +10,7 @@ import pytest
 
 from oracle import native
 from paper_2105_00110_amd import graphgen as gg
+from tests.test_gpu_fused import check_all, run_fused
 from tests.test_gpu_parity import _csr, _say, assert_parity, run_gpu
 
 pytestmark = pytest.mark.gpu
@@ -198,3 +199,41 @@ def test_slot_merge_batch(tclib):
         np.testing.assert_array_equal(r["tc"][vo[i]:vo[i + 1]].view(np.uint64), ref.tc.view(np.uint64))
         assert int(r["triG"][i]) == ref.triG
     g.close()
+
+
+def _pairs_over(n, P, seed):
+    """P random pairs over n vertices, a clique on the top ids among them."""
+    rng = np.random.default_rng(seed)
+    s, d, _ = gg.clique(12)
+    src, dst = rng.integers(0, n, (2, P)).astype(np.int32)
+    k = min(P, s.shape[0])
+    src[:k], dst[:k] = s[:k] + (n - 12), d[:k] + (n - 12)
+    return src, dst, n
+
+
+# the tiers of the fused launch at 1024 threads: LDS (16384 pairs, 4096
+# vertices), LDS for vertices only (2^20 pairs, 21504 vertices), workspace
+FUSED_TIERS = {
+    "lds_full": lambda: _pairs_over(4096, 16384, 1),
+    "lds_pairs_past": lambda: _pairs_over(4096, 16385, 2),
+    "lds_vertices_past": lambda: _pairs_over(4097, 16000, 3),
+    "tile_full": lambda: _pairs_over(6000, 3 * 8192, 4),
+    "tile_past": lambda: _pairs_over(6000, 3 * 8192 + 1, 5),
+    "few_pairs": lambda: _pairs_over(21504, 70, 6),
+    "vertices_full": lambda: _pairs_over(21504, 100_000, 7),
+    "vertices_past": lambda: _pairs_over(21505, 100_000, 8),
+    "dense": lambda: gg.clique(400),
+    "most_pairs": lambda: gg.rmat(14, 64, seed=9),
+    "pairs_past": lambda: gg.rmat(14, 64, seed=9, num_pairs=(1 << 20) + 1),
+    "longest_rows": lambda: gg.clique(1440),
+}
+
+
+def test_fused_tiers(tclib):
+    graphs = [FUSED_TIERS[k]() for k in sorted(FUSED_TIERS)]
+    refs = [native.o2_paper(*g) for g in graphs]
+    for order in ("largest_first", None):
+        _say("fused tiers", sorted(FUSED_TIERS), order)
+        fb, res = run_fused(tclib, graphs, order=order)
+        check_all(fb, res, graphs, refs)
+
