@@ -31,6 +31,7 @@ HIP_SOURCES = [
     "tc_slots.hip",
     "tc_algebraic.hip",
     "tc_ingest.hip",
+    "tc_single.hip",
     "tc_fused.hip",
     "tc_topk.hip",
     "tc_api.hip",

@@ -372,6 +372,27 @@ __global__ void k_widen(const uint32_t *__restrict__ a, int64_t n, uint64_t *__r
     GRID_STRIDE(i, n) out[i] = a[i];
 }
 
+// All results into device buffers in one launch (null: not wanted).
+struct ResultArgs {
+    const uint64_t *tri, *num, *triG;
+    const double *tcv;
+    const uint32_t *esup;
+    uint64_t *o_tri, *o_num, *o_triG, *o_sup;
+    double *o_tc;
+};
+
+__global__ void k_results(ResultArgs a, int64_t n, int64_t m, int64_t G) {
+    GRID_STRIDE(i, m > n ? m : n) {
+        if (i < n) {
+            if (a.o_tri) a.o_tri[i] = a.tri[i];
+            if (a.o_num) a.o_num[i] = a.num[i];
+            if (a.o_tc) a.o_tc[i] = a.tcv[i];
+        }
+        if (i < m && a.o_sup) a.o_sup[i] = a.esup[i];
+        if (i < G && a.o_triG) a.o_triG[i] = a.triG[i];
+    }
+}
+
 // CSR -> pairs: entry k belongs to the last row v with row_ptr[v] <= k.
 __global__ void k_csr_check(const int64_t *__restrict__ rp, int32_t n, uint32_t *__restrict__ err) {
     GRID_STRIDE(v, n) {
@@ -473,6 +494,8 @@ tc_status build_common(tc_graph *g, const int32_t *src, const int32_t *dst, int6
         d_src = a;
         d_dst = b;
     }
+    // one small graph: two launches in place of some fifty
+    if (!h_pair_off && tc_single_fits(P, g->n)) return tc_single_build(g, d_src, d_dst, P, s);
     int64_t *d_pair_off = nullptr;
     if (h_pair_off) {
         TC_TRY(tmp.get(&d_pair_off, g->num_graphs + 1));
@@ -728,6 +751,15 @@ tc_status tc_get_results(const tc_graph *g, uint64_t *tri, uint64_t *support, ui
     if (!g->computed) return TC_ERR_NOT_COMPUTED;
     hipStream_t s = (hipStream_t)stream;
     tc_call_scope scope(s);
+    // the buffers may lie at any address that their types allow, and G <= n but
+    // for graphs without vertices
+    const int64_t most = g->m > g->n ? g->m : g->n;
+    if (mem_kind == TC_MEM_DEVICE && most >= g->num_graphs) {
+        const ResultArgs a{g->tri, g->num, g->triG, g->tcv, g->esup, tri, num, triG, support, tc};
+        k_results<<<grid_for(most), BK, 0, s>>>(a, g->n, g->m, g->num_graphs);
+        TC_LAUNCHED();
+        return TC_OK;
+    }
     tc_scratch tmp(s);
     if (tri) TC_TRY(copy_out(tri, g->tri, sizeof(uint64_t) * g->n, mem_kind, s));
     if (num) TC_TRY(copy_out(num, g->num, sizeof(uint64_t) * g->n, mem_kind, s));

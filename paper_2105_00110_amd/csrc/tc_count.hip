@@ -347,9 +347,19 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     g->slots_used = false;
     if (!g->osup) TC_TRY(tc_graph_alloc(g, &g->osup, m, s));
     if (!g->triG) TC_TRY(tc_graph_alloc(g, &g->triG, g->num_graphs + 1, s));
-    TC_HIP(hipMemsetAsync(g->osup, 0, sizeof(uint32_t) * (m > 0 ? m : 1), s));
     // triG[num_graphs] is the scratch total of triangles found by the count
     unsigned long long *found = (unsigned long long *)(g->triG + g->num_graphs);
+    if (g->single && m > 0 && use_slots(g, t)) {  // one launch, aggregation included
+        g->algo_used = TC_ALGO_LOW_PIVOT;
+        g->slots_used = true;
+        g->light_max = t.light_max_dplus;
+        g->huge_min = 0x7FFFFFFF;
+        tc_prof_mark(g, 5, s);
+        TC_TRY(tc_single_count(g, s));
+        for (int k = 6; k <= 9; ++k) tc_prof_mark(g, k, s);
+        return TC_OK;
+    }
+    TC_HIP(hipMemsetAsync(g->osup, 0, sizeof(uint32_t) * (m > 0 ? m : 1), s));
     TC_HIP(hipMemsetAsync(found, 0, sizeof(uint64_t), s));
     if (m == 0 || g->max_dplus < 2) {
         g->light_max = t.light_max_dplus;

@@ -335,7 +335,6 @@ struct GraphRef {
 template <int BLOCK>
 __device__ __forceinline__ void fused_small(const FusedArgs &a, const GraphRef q, tc_small::Lds<BLOCK> &L) {
     using namespace tc_small;
-    constexpr int MW = 4;
     const uint32_t n = q.n, P = q.P;
     const int b = bits_of(n > 1 ? n - 1 : 1);
     const int itn = P == 0 ? 1 : (int)((P + BLOCK - 1) / BLOCK);
@@ -369,80 +368,16 @@ __device__ __forceinline__ void fused_small(const FusedArgs &a, const GraphRef q
         }
     (void)degree_rank<BLOCK>(E, n, L, [](uint32_t, uint32_t) {});
     (void)orient<BLOCK>(E, n, m, L);
-    // count: the tail of N_H(r) after c merged with N_H(c); supports as 16-bit
-    // halves (a support is below n <= 2^12)
-    for (uint32_t i = threadIdx.x; i < (m + 1) / 2; i += BLOCK) L.cnt[i] = 0;
-    for (uint32_t v = threadIdx.x; v < n; v += BLOCK) L.tri[v] = L.num[v] = 0;
-    __syncthreads();
-    const auto add_sup = [&](uint32_t s, uint32_t x) {
-        atomicAdd(&L.cnt[s >> 1], x << (16 * (s & 1u)));
-    };
-    const auto support = [&](uint32_t s) { return (L.cnt[s >> 1] >> (16 * (s & 1u))) & 0xFFFFu; };
-#pragma unroll 1
-    for (uint32_t s = threadIdx.x; s < m; s += BLOCK) {
-        const uint32_t r = L.xchg[s] >> 16, c = L.xchg[s] & 0xFFFFu;
-        uint32_t i = s + 1, j = L.orp[c], t = 0;
-        const uint32_t ie = L.orp[r + 1], je = L.orp[c + 1];
-        while (i < ie && j < je) {
-            uint32_t x[MW], y[MW];
-#pragma unroll
-            for (int e = 0; e < MW; ++e) {
-                x[e] = L.xchg[i + e < ie ? i + e : i] & 0xFFFFu;
-                y[e] = L.xchg[j + e < je ? j + e : j] & 0xFFFFu;
-            }
-#pragma unroll
-            for (int e = 0; e < MW; ++e) {
-                x[e] = i + e < ie ? x[e] : 0xFFFFFFFFu;
-                y[e] = j + e < je ? y[e] : 0xFFFFFFFEu;
-            }
-            const uint32_t lim = x[MW - 1] < y[MW - 1] ? x[MW - 1] : y[MW - 1];
-            uint32_t na = 0, nb = 0;
-#pragma unroll
-            for (int e = 0; e < MW; ++e) {
-                na += x[e] <= lim ? 1u : 0u;
-                nb += y[e] <= lim ? 1u : 0u;
-                int f = -1;
-#pragma unroll
-                for (int p = 0; p < MW; ++p) f = x[e] == y[p] ? p : f;
-                if (f >= 0) {
-                    add_sup(i + e, 1u);
-                    add_sup(j + (uint32_t)f, 1u);
-                    ++t;
-                }
-            }
-            i += na;
-            j += nb;
-        }
-        if (t) add_sup(s, t);
-    }
-    __syncthreads();
+    count_slots<BLOCK>(m, n, L);
     if (a.sup) {
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it)
             if (E.ends[it] != NONE)
-                a.sup[q.pa + (E.tag[it] & 0xFFFFu)] = support(E.tag[it] >> 16);
+                a.sup[q.pa + (E.tag[it] & 0xFFFFu)] = support(E.tag[it] >> 16, L);
     }
-    // sums over every vertex's edges: twice the triangles, then the numerator
-    // (all below 2^32: at most 16384 edges make at most 988000 triangles)
-    uint32_t *const tri = L.tri, *const num = L.num;
-    uint32_t local = 0;
-    for (uint32_t s = threadIdx.x; s < m; s += BLOCK) {
-        const uint32_t x = support(s);
-        if (x) {
-            atomicAdd(&tri[L.xchg[s] >> 16], x);
-            atomicAdd(&tri[L.xchg[s] & 0xFFFFu], x);
-            local += x;
-        }
-    }
-    const uint32_t three_t = wg_sum<BLOCK>(local, L.wsum);  // has the barrier
+    const uint32_t three_t = slot_sums<BLOCK>(m, L);
     bool odd = three_t % 3 != 0;
-    for (uint32_t s = threadIdx.x; s < m; s += BLOCK) {
-        const uint32_t r = L.xchg[s] >> 16, c = L.xchg[s] & 0xFFFFu;
-        const uint32_t f = support(s) ? 1u : 3u, tr = tri[r] >> 1, tcn = tri[c] >> 1;
-        if (tcn) atomicAdd(&num[r], f * tcn);
-        if (tr) atomicAdd(&num[c], f * tr);
-    }
-    __syncthreads();
+    const uint32_t *const tri = L.tri, *const num = L.num;
     const uint64_t tg = three_t / 3;
     for (uint32_t v = threadIdx.x; v < n; v += BLOCK) {
         const uint32_t r = L.rank[v];

@@ -204,6 +204,7 @@ struct tc_graph {
     int32_t light_max = 0, huge_min = 0;
     int32_t algo_used = 0;
     bool slots_used = false;  // the last count merged slots (tc_slots.hip)
+    bool single = false;      // built by one workgroup (tc_single.hip)
 
     // profiling marks (see tc_prof_mark)
     bool prof = false;
@@ -246,6 +247,14 @@ tc_status tc_work_stats(tc_graph *g, int64_t *stats, hipStream_t s);
 tc_status tc_mid_prepare(tc_graph *g, hipStream_t s);
 tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
                        unsigned long long *found, hipStream_t s);
+// One small graph by one workgroup (tc_single.hip): everything that
+// tc_build_from_pairs and tc_orient leave but the order by larger ends (made
+// again where a consumer needs it), and everything that tc_count and
+// tc_aggregate leave.
+bool tc_single_fits(int64_t P, int32_t n);
+tc_status tc_single_build(tc_graph *g, const int32_t *d_src, const int32_t *d_dst, int64_t P,
+                          hipStream_t s);
+tc_status tc_single_count(tc_graph *g, hipStream_t s);
 // Flat graphs (tc_slots.hip): support per slot into the zeroed g->osup, then
 // everything that tc_aggregate fills.
 tc_status tc_count_slots(tc_graph *g, unsigned long long *found, hipStream_t s);

@@ -376,4 +376,88 @@ __device__ __forceinline__ uint32_t orient(Edges &E, uint32_t n, uint32_t m, Lds
     return dmax;
 }
 
+// Support of slot s, a 16-bit half (a support is below the number of vertices).
+template <int BLOCK>
+__device__ __forceinline__ uint32_t support(uint32_t s, const Lds<BLOCK> &L) {
+    return (L.cnt[s >> 1] >> (16 * (s & 1u))) & 0xFFFFu;
+}
+
+// Count on the m slots in L.xchg (rows at L.orp): the tail of N_H(r) after c
+// merged with N_H(c) for every slot r -> c; supports in L.cnt.  Clears L.tri and
+// L.num.  Ends with a barrier.
+template <int BLOCK>
+__device__ __forceinline__ void count_slots(uint32_t m, uint32_t n, Lds<BLOCK> &L) {
+    constexpr int MW = 4;
+    for (uint32_t i = threadIdx.x; i < (m + 1) / 2; i += BLOCK) L.cnt[i] = 0;
+    for (uint32_t v = threadIdx.x; v < n; v += BLOCK) L.tri[v] = L.num[v] = 0;
+    __syncthreads();
+    const auto add = [&](uint32_t s, uint32_t x) {
+        atomicAdd(&L.cnt[s >> 1], x << (16 * (s & 1u)));
+    };
+#pragma unroll 1
+    for (uint32_t s = threadIdx.x; s < m; s += BLOCK) {
+        const uint32_t r = L.xchg[s] >> 16, c = L.xchg[s] & 0xFFFFu;
+        uint32_t i = s + 1, j = L.orp[c], t = 0;
+        const uint32_t ie = L.orp[r + 1], je = L.orp[c + 1];
+        while (i < ie && j < je) {
+            uint32_t x[MW], y[MW];
+#pragma unroll
+            for (int e = 0; e < MW; ++e) {
+                x[e] = L.xchg[i + e < ie ? i + e : i] & 0xFFFFu;
+                y[e] = L.xchg[j + e < je ? j + e : j] & 0xFFFFu;
+            }
+#pragma unroll
+            for (int e = 0; e < MW; ++e) {
+                x[e] = i + e < ie ? x[e] : 0xFFFFFFFFu;
+                y[e] = j + e < je ? y[e] : 0xFFFFFFFEu;
+            }
+            const uint32_t lim = x[MW - 1] < y[MW - 1] ? x[MW - 1] : y[MW - 1];
+            uint32_t na = 0, nb = 0;
+#pragma unroll
+            for (int e = 0; e < MW; ++e) {
+                na += x[e] <= lim ? 1u : 0u;
+                nb += y[e] <= lim ? 1u : 0u;
+                int f = -1;
+#pragma unroll
+                for (int p = 0; p < MW; ++p) f = x[e] == y[p] ? p : f;
+                if (f >= 0) {
+                    add(i + e, 1u);
+                    add(j + (uint32_t)f, 1u);
+                    ++t;
+                }
+            }
+            i += na;
+            j += nb;
+        }
+        if (t) add(s, t);
+    }
+    __syncthreads();
+}
+
+// Sums over every vertex's edges: L.tri = twice the triangles of each rank,
+// L.num = Σ weight * triangles of the other end (1 on edges with support, 3 on
+// the others).  All below 2^32: at most 16384 edges make at most 988000
+// triangles.  Returns Σ supports, three times the graph's triangles.
+template <int BLOCK>
+__device__ __forceinline__ uint32_t slot_sums(uint32_t m, Lds<BLOCK> &L) {
+    uint32_t local = 0;
+    for (uint32_t s = threadIdx.x; s < m; s += BLOCK) {
+        const uint32_t x = support(s, L);
+        if (x) {
+            atomicAdd(&L.tri[L.xchg[s] >> 16], x);
+            atomicAdd(&L.tri[L.xchg[s] & 0xFFFFu], x);
+            local += x;
+        }
+    }
+    const uint32_t all = wg_sum<BLOCK>(local, L.wsum);  // has the barrier
+    for (uint32_t s = threadIdx.x; s < m; s += BLOCK) {
+        const uint32_t r = L.xchg[s] >> 16, c = L.xchg[s] & 0xFFFFu;
+        const uint32_t f = support(s, L) ? 1u : 3u, tr = L.tri[r] >> 1, tc = L.tri[c] >> 1;
+        if (tc) atomicAdd(&L.num[r], f * tc);
+        if (tr) atomicAdd(&L.num[c], f * tr);
+    }
+    __syncthreads();
+    return all;
+}
+
 }  // namespace tc_small

@@ -237,3 +237,36 @@ def test_fused_tiers(tclib):
         fb, res = run_fused(tclib, graphs, order=order)
         check_all(fb, res, graphs, refs)
 
+
+
+# one small graph by one workgroup: its largest size and one more of each, and
+# rows above the slot merge's limit (the general count on such a build)
+SINGLE_GRAPHS = {
+    "one_pair": lambda: (np.array([0], np.int32), np.array([1], np.int32), 2),
+    "one_loop": lambda: (np.array([0], np.int32), np.array([0], np.int32), 1),
+    "full": FUSED_TIERS["lds_full"],
+    "pairs_past": FUSED_TIERS["lds_pairs_past"],
+    "vertices_past": FUSED_TIERS["lds_vertices_past"],
+    "long_rows": lambda: gg.clique(180),
+    "star": lambda: _star(4096, 9, np.setdiff1d(np.arange(4096), [9])),
+    "repeats": lambda: (np.tile(np.array([1, 2, 0], np.int32), 5000),
+                        np.tile(np.array([2, 0, 1], np.int32), 5000), 3),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SINGLE_GRAPHS))
+def test_single_workgroup_graphs(tclib, name):
+    src, dst, n = SINGLE_GRAPHS[name]()
+    ref = native.o2_paper(src, dst, n)
+    _say("single workgroup", name, "n", n, "pairs", src.shape[0])
+    assert_parity(run_gpu(tclib, src, dst, n), ref)
+    assert_parity(run_gpu(tclib, src, dst, n, device=False), ref)
+    for algorithm in (tclib.TC_ALGO_LOW_PIVOT, tclib.TC_ALGO_MID_PIVOT):
+        assert_parity(run_gpu(tclib, src, dst, n, tuning={"algorithm": algorithm}), ref)
+    g = tclib.Graph.from_edges(src, dst, n)
+    g.compute()
+    np.testing.assert_array_equal(g.numerator_algebraic(), ref.num)
+    assert g.work_stats()["triangles"] == ref.triG
+    g.compute()  # again on the same handle
+    np.testing.assert_array_equal(g.results()["support"], ref.sup)
+    g.close()
