@@ -27,6 +27,7 @@ HIP_SOURCES = [
     "tc_build.hip",
     "tc_count.hip",
     "tc_count_mid.hip",
+    "tc_core.hip",
     "tc_aggregate.hip",
     "tc_slots.hip",
     "tc_algebraic.hip",

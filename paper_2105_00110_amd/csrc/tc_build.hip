@@ -521,6 +521,30 @@ __global__ void k_place_by_larger(int64_t m, const uint32_t *__restrict__ lt_key
     }
 }
 
+// Adds the oriented wedges of a workgroup's ranks, from base on, to the word of
+// the smallest core that holds them.  The sizes lie at least a workgroup's
+// ranks apart, so that it meets two words at most.
+template <int PER>
+__device__ __forceinline__ void core_wedges(int32_t n, int64_t base, const uint32_t (&d)[PER],
+                                            unsigned long long *__restrict__ wedges) {
+    static_assert(PER * BK <= 2048, "sizes of cores are 2048 apart");
+    if (base + PER * BK <= (int64_t)n - tc_core_ranks(TC_CORE_SIZES - 1)) return;
+    int j0 = 0;  // the word of the workgroup's highest ranks
+    while (base + PER * BK - 1 < (int64_t)n - tc_core_ranks(j0)) ++j0;
+    unsigned long long a = 0, b = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int64_t r = base + k * BK + threadIdx.x;
+        const unsigned long long w = (unsigned long long)d[k] * (d[k] - 1ull * (d[k] > 0)) / 2;
+        if (r >= (int64_t)n - tc_core_ranks(j0)) a += w; else b += w;
+    }
+    a = tc_wave_sum(a);
+    b = tc_wave_sum(b);
+    if (__lane_id() != 0) return;
+    if (a) atomicAdd(&wedges[j0], a);
+    if (b && j0 + 1 < TC_CORE_SIZES) atomicAdd(&wedges[j0 + 1], b);
+}
+
 // d+ by rank row, its maximum (info[0]), and the vertices whose buckets a
 // wavefront (more than SEG_SMALL entries) or a workgroup (more than SEG_MID)
 // sorts: list_mid and list_big in any order, their counts in info[1] and
@@ -536,7 +560,8 @@ __global__ __launch_bounds__(BK) void k_dplus_lists(int32_t n, const uint32_t *_
                                                     int64_t *__restrict__ dplus,
                                                     int32_t *__restrict__ list_mid,
                                                     int32_t *__restrict__ list_big,
-                                                    uint32_t *__restrict__ info) {
+                                                    uint32_t *__restrict__ info,
+                                                    unsigned long long *__restrict__ wedges) {
     constexpr int PER = DL_TILE / BK;
     __shared__ uint32_t lds[BK / TC_WAVE + 1];
     const int64_t base = (int64_t)blockIdx.x * DL_TILE;
@@ -553,6 +578,7 @@ __global__ __launch_bounds__(BK) void k_dplus_lists(int32_t n, const uint32_t *_
         nbig += d[k] > SEG_MID ? 1u : 0u;
     }
     tc_block_raise<BK>(mx, &info[0], lds);
+    core_wedges<PER>(n, base, d, wedges);
     if (!__syncthreads_or(nmid | nbig)) return;
     uint32_t pm = tc_block_reserve<BK>(nmid, &info[1], lds);
     uint32_t pb = tc_block_reserve<BK>(nbig, &info[2], lds);
@@ -890,10 +916,12 @@ tc_status tc_orient(tc_graph *g, hipStream_t s) {
     TC_TRY(tmp.get(&cursor, nn));
     TC_TRY(tmp.get(&tbuf, 2 * m));
     TC_TRY(tmp.get(&dplus, nn));
-    TC_TRY(tmp.get(&info, 4));  // max d+, mid-list count, big-list count
+    // max d+, mid-list count, big-list count; wedges of the cores (64-bit)
+    constexpr int INFO = 4 + 2 * TC_CORE_SIZES;
+    TC_TRY(tmp.get(&info, INFO));
     TC_TRY(tmp.get(&list_mid, nn));
     TC_TRY(tmp.get(&list_big, nn));
-    TC_HIP(hipMemsetAsync(info, 0, 16, s));
+    TC_HIP(hipMemsetAsync(info, 0, INFO * sizeof(uint32_t), s));
     TC_HIP(hipMemsetAsync(cursor, 0, sizeof(uint32_t) * nn, s));
     // pass A: buckets of the lower-ordered endpoints
     {
@@ -907,11 +935,16 @@ tc_status tc_orient(tc_graph *g, hipStream_t s) {
         TC_LAUNCHED();
     }
     // with the largest d+ and the lists, whose counts one read-back brings
+    unsigned long long *wedges = reinterpret_cast<unsigned long long *>(info + 4);
     k_dplus_lists<<<(unsigned)tc_div_up(n, DL_TILE), BK, 0, s>>>(n, cursor, g->perm, dplus, list_mid,
-                                                                list_big, info);
+                                                                list_big, info, wedges);
     TC_LAUNCHED();
     uint32_t h_info[4] = {0, 0, 0, 0};
-    TC_TRY(tc_read({{h_info, info, 3}, {&g->max_degree, g->err + 1, 1}}, s));
+    TC_TRY(tc_read({{h_info, info, 3},
+                    {&g->max_degree, g->err + 1, 1},
+                    {g->core_wedges, wedges, 2 * TC_CORE_SIZES}},
+                   s));
+    for (int j = 1; j < TC_CORE_SIZES; ++j) g->core_wedges[j] += g->core_wedges[j - 1];
     const uint32_t h_max = h_info[0];
     const int64_t nmid = h_info[1], nblk = h_info[2];
     g->max_dplus = (int32_t)h_max;

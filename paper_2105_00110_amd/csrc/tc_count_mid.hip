@@ -33,6 +33,10 @@
 // and key their lookup structure the same way: half the bytes of the scan
 // for most of its candidates on skewed graphs.
 //
+// The core.  Pairs whose u is among the highest ranks are left to matrix
+// products where those are faster (tc_core.hip): a pivot's pairs end at
+// tc_pairs_end, and the fold leaves such rows out.
+//
 // Work mapping.  A work item is a pivot with a slice of its pairs.  A
 // wavefront takes 64 pairs at a time and flattens their bit rows: a prefix
 // sum of the row lengths in words places word x of the group, and the lane
@@ -450,7 +454,7 @@ __host__ __device__ __forceinline__ size_t mid_wave_bytes(int dcap) {
 // One wavefront per item; pivots with |N_H(v)| <= dcap.
 __global__ __launch_bounds__(1024) void k_mid_wave(const int64_t *__restrict__ orp,
                                                    const int32_t *__restrict__ ocol,
-                                                   const int64_t *__restrict__ in_ptr,
+                                                   const int64_t *__restrict__ in_ptr, tc_core core,
                                                    const uint64_t *__restrict__ in_pair,
                                                    const uint4 *__restrict__ rowinfo,
                                                    uint32_t *__restrict__ bits,
@@ -479,7 +483,7 @@ __global__ __launch_bounds__(1024) void k_mid_wave(const int64_t *__restrict__ o
     for (int64_t it = (int64_t)blockIdx.x * wpb + wv; it < nitems; it += (int64_t)gridDim.x * wpb) {
         const int32_t v = item_v[it];
         const int64_t first = item_first[it];
-        const int64_t pend = min(first + (int64_t)item_pairs, in_ptr[v + 1]);
+        const int64_t pend = min(first + (int64_t)item_pairs, tc_pairs_end(in_ptr, core, v));
         const int64_t vstart = orp[v];
         const int d = (int)(orp[v + 1] - vstart);
         const RowTable t{keys, pos, bucket_bits(d)};
@@ -531,7 +535,7 @@ __host__ __device__ __forceinline__ size_t mid_group_bytes(int dcap, int gl) {
 template <int GL>
 __global__ __launch_bounds__(256, 4) void k_mid_groups(const int64_t *__restrict__ orp,
                                                     const int32_t *__restrict__ ocol,
-                                                    const int64_t *__restrict__ in_ptr,
+                                                    const int64_t *__restrict__ in_ptr, tc_core core,
                                                     const uint64_t *__restrict__ in_pair,
                                                     const uint4 *__restrict__ rowinfo,
                                                     uint32_t *__restrict__ bits,
@@ -559,7 +563,7 @@ __global__ __launch_bounds__(256, 4) void k_mid_groups(const int64_t *__restrict
     for (int64_t it = (int64_t)blockIdx.x * gpb + gi; it < nitems; it += (int64_t)gridDim.x * gpb) {
         const int32_t v = item_v[it];
         const int64_t first = item_first[it];
-        const int64_t pend = min(first + (int64_t)item_pairs, in_ptr[v + 1]);
+        const int64_t pend = min(first + (int64_t)item_pairs, tc_pairs_end(in_ptr, core, v));
         const int64_t vstart = orp[v];
         const int d = (int)(orp[v + 1] - vstart);
         const RowTable t{keys, pos, bucket_bits(d)};
@@ -588,7 +592,7 @@ __global__ __launch_bounds__(256, 4) void k_mid_groups(const int64_t *__restrict
 template <int LK>
 __global__ __launch_bounds__(1024) void k_mid_block(const int64_t *__restrict__ orp,
                                                     const int32_t *__restrict__ ocol,
-                                                    const int64_t *__restrict__ in_ptr,
+                                                    const int64_t *__restrict__ in_ptr, tc_core core,
                                                     const uint64_t *__restrict__ in_pair,
                                                     const uint4 *__restrict__ rowinfo,
                                                     uint32_t *__restrict__ bits,
@@ -629,7 +633,7 @@ __global__ __launch_bounds__(1024) void k_mid_block(const int64_t *__restrict__ 
     for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
         const int32_t v = item_v[it];
         const int64_t first = item_first[it];
-        const int64_t pend = min(first + (int64_t)item_pairs, in_ptr[v + 1]);
+        const int64_t pend = min(first + (int64_t)item_pairs, tc_pairs_end(in_ptr, core, v));
         const int64_t vstart = orp[v];
         const int d = (int)(orp[v + 1] - vstart);
         RowTable t{keys, pos, 0};
@@ -694,7 +698,7 @@ __host__ __device__ __forceinline__ size_t mid_block16_bytes(int dmax) {
 // SIMD stay resident to cover the latency of the candidate loads.
 __global__ __launch_bounds__(1024, 6) void k_mid_block16(
     const int64_t *__restrict__ orp, const int32_t *__restrict__ ocol,
-    const int64_t *__restrict__ in_ptr, const uint64_t *__restrict__ in_pair,
+    const int64_t *__restrict__ in_ptr, tc_core core, const uint64_t *__restrict__ in_pair,
     const uint4 *__restrict__ rowinfo, uint32_t *__restrict__ bits,
     const int32_t *__restrict__ item_v, const uint32_t *__restrict__ item_first, int64_t nitems,
     int dmax, int item_pairs, const uint16_t *__restrict__ ocol16, int32_t r16,
@@ -711,7 +715,7 @@ __global__ __launch_bounds__(1024, 6) void k_mid_block16(
     for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
         const int32_t v = item_v[it];
         const int64_t first = item_first[it];
-        const int64_t pend = min(first + (int64_t)item_pairs, in_ptr[v + 1]);
+        const int64_t pend = min(first + (int64_t)item_pairs, tc_pairs_end(in_ptr, core, v));
         const int64_t vstart = orp[v];
         const int d = (int)(orp[v + 1] - vstart);
         // 2048 words over the 16-bit values, that is ranks r16 .. r16 + 2^16 - 1
@@ -1192,7 +1196,7 @@ __global__ __launch_bounds__(256, 4) void k_fold_big(const int32_t *__restrict__
 __global__ void k_dplus_flags(PlanRules q, int32_t n,
                                                     const int64_t *__restrict__ orp,
                                                     const int32_t *__restrict__ ocol,
-                                                    const int64_t *__restrict__ in_ptr,
+                                                    const int64_t *__restrict__ in_ptr, tc_core core,
                                                     uint8_t *__restrict__ flags,
                                                     int64_t *__restrict__ tile_cnt) {
     __shared__ uint32_t red[NLISTS][BK / TC_WAVE];
@@ -1202,9 +1206,9 @@ __global__ void k_dplus_flags(PlanRules q, int32_t n,
     for (int k = 0; k < PLAN_PER; ++k) {
         const int64_t v = base + k * BK + threadIdx.x;
         if (v < n) {
-            const int64_t a = orp[v], d = orp[v + 1] - a, in = in_ptr[v + 1] - in_ptr[v];
+            const int64_t a = orp[v], d = orp[v + 1] - a, in = tc_pairs_end(in_ptr, core, v) - in_ptr[v];
             const int cls = item_class(q, v, d, in, ocol + a);
-            const int fold = d < 2 ? 15 : (d <= 64 ? 0 : 1);
+            const int fold = d < 2 || v >= core.r0 ? 15 : (d <= 64 ? 0 : 1);
             flags[v] = (uint8_t)((cls & 15) | fold << 4);
 #pragma unroll
             for (int l = 0; l < NPLANS; ++l)
@@ -1230,7 +1234,7 @@ __global__ void k_dplus_flags(PlanRules q, int32_t n,
 // arrays, the fold's rows in another, from the first place of L_FOLD on.
 __global__ __launch_bounds__(BK) void k_plan_write(PlanRules q, int32_t n,
                                                    const uint8_t *__restrict__ flags,
-                                                   const int64_t *__restrict__ in_ptr,
+                                                   const int64_t *__restrict__ in_ptr, tc_core core,
                                                    const int64_t *__restrict__ tile_off,
                                                    int32_t *__restrict__ item_v,
                                                    uint32_t *__restrict__ item_first,
@@ -1251,7 +1255,7 @@ __global__ __launch_bounds__(BK) void k_plan_write(PlanRules q, int32_t n,
             int S = 1;
 #pragma unroll
             for (int l = 0; l < NPLANS; ++l) S = cls[k] == l ? q.S[l] : S;
-            if (cls[k] != 15) cnt[k] = (uint32_t)tc_div_up(in_ptr[v0 + k + 1] - in_ptr[v0 + k], S);
+            if (cls[k] != 15) cnt[k] = (uint32_t)tc_div_up(tc_pairs_end(in_ptr, core, v0 + k) - in_ptr[v0 + k], S);
         }
     }
     const int w = threadIdx.x / TC_WAVE;
@@ -1288,7 +1292,7 @@ __global__ __launch_bounds__(BK) void k_plan_write(PlanRules q, int32_t n,
 // other pair's row is written whole by the kernel that scans it, so no
 // other word needs clearing.  One wavefront per item, a lane per pair.
 __global__ void k_zero_rows(const uint4 *__restrict__ rowinfo, const uint64_t *__restrict__ in_pair,
-                            const int64_t *__restrict__ in_ptr, const int32_t *__restrict__ item_v,
+                            const int64_t *__restrict__ in_ptr, tc_core core, const int32_t *__restrict__ item_v,
                             const uint32_t *__restrict__ item_first, int64_t nitems, int S,
                             uint32_t *__restrict__ bits) {
     const int wpb = blockDim.x / TC_WAVE;
@@ -1297,7 +1301,7 @@ __global__ void k_zero_rows(const uint4 *__restrict__ rowinfo, const uint64_t *_
     for (int64_t it = (int64_t)blockIdx.x * wpb + wv; it < nitems; it += (int64_t)gridDim.x * wpb) {
         const int32_t v = item_v[it];
         const int64_t first = item_first[it];
-        const int64_t pend = min(first + (int64_t)S, in_ptr[v + 1]);
+        const int64_t pend = min(first + (int64_t)S, tc_pairs_end(in_ptr, core, v));
         for (int64_t i = first + lane; i < pend; i += TC_WAVE) {
             const uint64_t pr = in_pair[i];
             const int64_t k = (int64_t)(uint32_t)pr;
@@ -1326,7 +1330,7 @@ __global__ void k_row_words_total(int32_t n, const int64_t *__restrict__ orp,
 }
 
 // Work per bin for the statistics: scan lengths of every pair, binned by
-// the pivot's |N_H|.
+// the pivot's |N_H| (those of the core included, which no scan reads).
 __global__ void k_mid_stats(int64_t m, const int64_t *__restrict__ orp,
                             const int32_t *__restrict__ ocol, const uint64_t *__restrict__ in_pair,
                             int light_max, int huge_min, int32_t r16,
@@ -1485,6 +1489,21 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
     const int wave_pairs = t.item_pairs;
     const int block_pairs = t.item_pairs * wpb_block;
     tc_scratch items(s);
+    // the triangles inside the core come from matrix products
+    tc_core core;
+    uint4 *core_mat = nullptr;
+    int32_t core_n = tc_core_size(g);
+    if (core_n > 0) {
+        int64_t *end = nullptr;
+        TC_TRY(items.get(&end, core_n));
+        // no memory for the matrix: the scan takes every pair
+        if (items.get(&core_mat, (int64_t)core_n * core_n / 32) == TC_OK) {
+            TC_TRY(tc_core_fill(g, core_n, end, core_mat, s));
+            core = {g->n - core_n, end};
+        } else {
+            core_n = 0;
+        }
+    }
     // workgroup pivots whose rank span fits the LDS bitmap use it; the
     // others hash (or, above huge_min, search device memory).  Wavefront
     // pivots with at least light_bitmap_pairs pairs and a span that fits go
@@ -1513,7 +1532,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
     uint8_t *flags = nullptr;
     TC_TRY(items.get(&tile_cnt, NLISTS * plan_tiles + 1));
     TC_TRY(items.get(&flags, g->n));
-    k_dplus_flags<<<(unsigned)plan_tiles, BK, 0, s>>>(rules, g->n, g->orp, g->ocol, g->in_ptr, flags,
+    k_dplus_flags<<<(unsigned)plan_tiles, BK, 0, s>>>(rules, g->n, g->orp, g->ocol, g->in_ptr, core, flags,
                                                       tile_cnt);
     TC_LAUNCHED();
     TC_TRY(tc_scan_i64(tile_cnt, tile_cnt, NLISTS * plan_tiles, tile_cnt + NLISTS * plan_tiles, s));
@@ -1532,7 +1551,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
     TC_TRY(items.get(&item_v, n_items));
     TC_TRY(items.get(&item_first, n_items));
     TC_TRY(items.get(&fold_rows, n_rows));
-    k_plan_write<<<(unsigned)plan_tiles, BK, 0, s>>>(rules, g->n, flags, g->in_ptr, tile_cnt, item_v,
+    k_plan_write<<<(unsigned)plan_tiles, BK, 0, s>>>(rules, g->n, flags, g->in_ptr, core, tile_cnt, item_v,
                                                      item_first, fold_rows);
     TC_LAUNCHED();
     const auto list_v = [&](int p) { return item_v + first[p]; };
@@ -1548,7 +1567,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
     if (n_zero > 0) {
         int64_t zb = tc_div_up(n_zero, BK / TC_WAVE);
         k_zero_rows<<<(unsigned)(zb < 262144 ? zb : 262144), BK, 0, s>>>(
-            g->rowinfo, g->in_pair, g->in_ptr, list_v(P_ZERO), list_first(P_ZERO), n_zero, wave_pairs,
+            g->rowinfo, g->in_pair, g->in_ptr, core, list_v(P_ZERO), list_first(P_ZERO), n_zero, wave_pairs,
             g->hitbits);
         TC_LAUNCHED();
     }
@@ -1559,7 +1578,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         int64_t blocks = tc_div_up(n_group, gpb);
         if (blocks > 262144) blocks = 262144;
         k_mid_groups<GROUP_LANES><<<(unsigned)blocks, 256, (size_t)gpb * mid_group_bytes(gmax, GROUP_LANES), s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_GROUP),
+            g->orp, g->ocol, g->in_ptr, core, g->in_pair, g->rowinfo, g->hitbits, list_v(P_GROUP),
             list_first(P_GROUP), n_group, gmax, group_pairs, g->osup, found);
         TC_LAUNCHED();
     }
@@ -1571,7 +1590,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         int64_t blocks = tc_div_up(n_wave, wpb);
         if (blocks > 262144) blocks = 262144;
         k_mid_wave<<<(unsigned)blocks, wpb * TC_WAVE, (size_t)wpb * per_wave, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_WAVE), list_first(P_WAVE), n_wave,
+            g->orp, g->ocol, g->in_ptr, core, g->in_pair, g->rowinfo, g->hitbits, list_v(P_WAVE), list_first(P_WAVE), n_wave,
             light_max, wave_pairs, g->ocol16, g->rank16_base, g->osup, found);
         TC_LAUNCHED();
     }
@@ -1580,7 +1599,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         const size_t lds = mid_block_bytes(light_max, wpb_block, LK_BITMAP, bw);
         int64_t blocks = n_lbitmap < 1048576 ? n_lbitmap : 1048576;
         k_mid_block<LK_BITMAP><<<(unsigned)blocks, wpb_block * TC_WAVE, lds, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_LBITMAP),
+            g->orp, g->ocol, g->in_ptr, core, g->in_pair, g->rowinfo, g->hitbits, list_v(P_LBITMAP),
             list_first(P_LBITMAP), n_lbitmap,
             light_max, block_pairs, bw, g->ocol16, g->rank16_base, g->osup, found);
         TC_LAUNCHED();
@@ -1591,7 +1610,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         const size_t lds = mid_block16_bytes(hmax);
         int64_t blocks = n_bitmap16 < 1048576 ? n_bitmap16 : 1048576;
         k_mid_block16<<<(unsigned)blocks, wpb_block * TC_WAVE, lds, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_BITMAP16),
+            g->orp, g->ocol, g->in_ptr, core, g->in_pair, g->rowinfo, g->hitbits, list_v(P_BITMAP16),
             list_first(P_BITMAP16), n_bitmap16, hmax, block_pairs, g->ocol16, g->rank16_base,
             g->osup, found);
         TC_LAUNCHED();
@@ -1602,7 +1621,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         const size_t lds = mid_block_bytes(hmax, wpb_block, LK_BITMAP, bw);
         int64_t blocks = n_bitmap < 1048576 ? n_bitmap : 1048576;
         k_mid_block<LK_BITMAP><<<(unsigned)blocks, wpb_block * TC_WAVE, lds, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_BITMAP),
+            g->orp, g->ocol, g->in_ptr, core, g->in_pair, g->rowinfo, g->hitbits, list_v(P_BITMAP),
             list_first(P_BITMAP), n_bitmap,
             hmax, block_pairs, bw, g->ocol16, g->rank16_base, g->osup, found);
         TC_LAUNCHED();
@@ -1612,7 +1631,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         const size_t lds = mid_block_bytes(hmax, wpb_block, LK_HASH, 0);
         int64_t blocks = n_block < 1048576 ? n_block : 1048576;
         k_mid_block<LK_HASH><<<(unsigned)blocks, wpb_block * TC_WAVE, lds, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_BLOCK),
+            g->orp, g->ocol, g->in_ptr, core, g->in_pair, g->rowinfo, g->hitbits, list_v(P_BLOCK),
             list_first(P_BLOCK), n_block, hmax,
             block_pairs, 0, g->ocol16, g->rank16_base, g->osup, found);
         TC_LAUNCHED();
@@ -1622,7 +1641,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
         const size_t lds = mid_block_bytes(0, wpb_block, LK_GLOBAL, 0);
         int64_t blocks = n_huge < 1048576 ? n_huge : 1048576;
         k_mid_block<LK_GLOBAL><<<(unsigned)blocks, wpb_block * TC_WAVE, lds, s>>>(
-            g->orp, g->ocol, g->in_ptr, g->in_pair, g->rowinfo, g->hitbits, list_v(P_HUGE),
+            g->orp, g->ocol, g->in_ptr, core, g->in_pair, g->rowinfo, g->hitbits, list_v(P_HUGE),
             list_first(P_HUGE), n_huge, 0,
             block_pairs, 0, g->ocol16, g->rank16_base, g->osup, found);
         TC_LAUNCHED();
@@ -1662,6 +1681,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
             }
         }
     }
+    if (core_n > 0) TC_TRY(tc_core_count(g, core_n, core_mat, found, s));
     tc_prof_mark(g, 9, s);
     return TC_OK;
 }

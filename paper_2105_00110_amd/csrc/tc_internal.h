@@ -138,6 +138,29 @@ tc_status tc_sort_u32_u32(uint32_t **keys, uint32_t **vals, uint32_t **tmp_keys,
                           uint32_t **tmp_vals, int64_t n, int bits, hipStream_t s);
 
 // ---------------------------------------------------------------------------
+// The core: the vertices of the N highest ranks, whose inner triangles the
+// middle-pivot count takes from matrix products (tc_core.hip).
+// ---------------------------------------------------------------------------
+constexpr int TC_CORE_SIZES = 8;
+// multiples of 1024 (whole panels of tiles)
+__host__ __device__ __forceinline__ int32_t tc_core_ranks(int j) {
+    constexpr int32_t K[TC_CORE_SIZES] = {2, 4, 6, 8, 12, 16, 24, 32};
+    return K[j] * 1024;
+}
+
+// What the scan leaves out: the pairs of core vertex v from end[v - r0] on.
+struct tc_core {
+    int32_t r0 = 0x7FFFFFFF;  // the core's first rank (no core: above every rank)
+    const int64_t *end = nullptr;
+};
+
+// The end of pivot v's pairs.
+__device__ __forceinline__ int64_t tc_pairs_end(const int64_t *__restrict__ in_ptr, tc_core core,
+                                                int64_t v) {
+    return v >= core.r0 ? core.end[v - core.r0] : in_ptr[v + 1];
+}
+
+// ---------------------------------------------------------------------------
 // The graph handle.
 // ---------------------------------------------------------------------------
 struct tc_graph {
@@ -196,6 +219,9 @@ struct tc_graph {
     int64_t *h_edge_off = nullptr;                  // host [G+1]
     int32_t max_dplus = 0;
     int32_t max_degree = 0;
+    // oriented wedges of the rows of the tc_core_ranks(j) highest ranks, the
+    // sizes of the core that tc_core.hip takes
+    unsigned long long core_wedges[TC_CORE_SIZES] = {};
     uint32_t *err = nullptr;  // device words: error bits, largest degree, 2 unused
 
     size_t bytes = 0;  // device bytes held
@@ -247,6 +273,13 @@ tc_status tc_work_stats(tc_graph *g, int64_t *stats, hipStream_t s);
 tc_status tc_mid_prepare(tc_graph *g, hipStream_t s);
 tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
                        unsigned long long *found, hipStream_t s);
+// tc_core.hip: the core's size for this graph (0: none); its matrix
+// (N * N / 32 words of 16 bytes) and the ends of its pairs; its products added
+// to g->osup and its triangles to *found.
+int32_t tc_core_size(const tc_graph *g);
+tc_status tc_core_fill(const tc_graph *g, int32_t N, int64_t *end, uint4 *mat, hipStream_t s);
+tc_status tc_core_count(const tc_graph *g, int32_t N, const uint4 *mat, unsigned long long *found,
+                        hipStream_t s);
 // One small graph by one workgroup (tc_single.hip): everything that
 // tc_build_from_pairs and tc_orient leave but the order by larger ends (made
 // again where a consumer needs it), and everything that tc_count and

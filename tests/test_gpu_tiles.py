@@ -270,3 +270,42 @@ def test_single_workgroup_graphs(tclib, name):
     g.compute()  # again on the same handle
     np.testing.assert_array_equal(g.results()["support"], ref.sup)
     g.close()
+
+
+def _dense_core(n, k, density, seed, extra):
+    """A random graph of the given density on k of n vertices, shuffled, and extra random pairs."""
+    rng = np.random.default_rng(seed)
+    a, b = np.nonzero(np.triu(rng.random((k, k)) < density, 1))
+    ids = rng.permutation(n)
+    src = np.concatenate([ids[a], rng.integers(0, n, extra)])
+    dst = np.concatenate([ids[b], rng.integers(0, n, extra)])
+    return src.astype(np.int32), dst.astype(np.int32), n
+
+
+# the middle pivot's core of the 2048, 4096, ... highest ranks, taken by matrix
+# products: the whole graph, one rank below it, a core cut out of a larger
+# dense part, several panels of tiles, and a core with all its edges
+CORE_GRAPHS = {
+    "whole": lambda: _dense_core(2048, 2048, 0.35, 1, 0),
+    "one_below": lambda: _dense_core(2049, 2049, 0.35, 2, 0),
+    "cut": lambda: _dense_core(9000, 2600, 0.4, 3, 40_000),
+    "panels": lambda: _dense_core(20_000, 4200, 0.3, 4, 100_000),
+    "clique": lambda: _dense_core(3000, 2100, 2.0, 5, 5000),
+    "skewed": lambda: gg.rmat(16, 16, seed=3),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CORE_GRAPHS))
+def test_core_products(tclib, name):
+    src, dst, n = CORE_GRAPHS[name]()
+    _say("core products", name, "n", n)
+    assert_parity(run_gpu(tclib, src, dst, n), native.o2_paper(src, dst, n))
+    g = tclib.Graph.from_edges(src, dst, n)
+    g.compute({"algorithm": tclib.TC_ALGO_LOW_PIVOT})
+    a = g.results()
+    g.compute()
+    assert g.work_stats()["algorithm"] == tclib.TC_ALGO_MID_PIVOT
+    b = g.results()
+    for k in ("tri", "support", "triG", "num"):
+        np.testing.assert_array_equal(a[k], b[k])
+    g.close()
