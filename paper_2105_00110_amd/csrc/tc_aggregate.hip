@@ -52,16 +52,6 @@ __device__ T block_sum(T x, T *red) {
     return t;
 }
 
-__device__ __forceinline__ int32_t graph_of(const int64_t *__restrict__ vtx_off, int32_t G,
-                                            int64_t v) {
-    int32_t lo = 0, hi = G - 1;
-    while (lo < hi) {
-        int32_t mid = (lo + hi + 1) >> 1;
-        if (vtx_off[mid] <= v) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
 // esup[e[i]] = sup[i] for pairs already grouped by the top bits of e, so
 // that the stores of neighbouring blocks fall in a few narrow windows.
 __global__ void k_store_pairs(int64_t m, const uint32_t *__restrict__ e,
@@ -146,7 +136,7 @@ __global__ __launch_bounds__(BK) void k_tri_sum(int32_t n, const uint64_t *__res
     for (int64_t v0 = a; v0 < b; v0 += BK) {  // every lane of a wavefront takes part
         const int64_t v = v0 + threadIdx.x;
         const bool valid = v < b;
-        const int32_t g = valid ? graph_of(vtx_off, G, v) : G;
+        const int32_t g = valid ? tc_graph_of(vtx_off, G, v) : G;
         uint64_t x = valid ? tri[v] : 0;
         // sum of the lanes of one graph, at its last lane
         const int lane = __lane_id();
@@ -198,7 +188,7 @@ __global__ void k_num_small(int32_t n, const int64_t *__restrict__ row_ptr,
         if (sub == 0) {
             uint64_t x = acc + tri[v];
             num[v] = x;
-            uint64_t tg = triG[vtx_off ? graph_of(vtx_off, G, v) : 0];
+            uint64_t tg = triG[vtx_off ? tc_graph_of(vtx_off, G, v) : 0];
             tcv[v] = quotient(x, tg);
         }
     }
@@ -223,7 +213,7 @@ __global__ void k_num_big(const int32_t *__restrict__ big, const uint32_t *__res
         if (threadIdx.x == 0) {
             uint64_t x = acc + tri[v];
             num[v] = x;
-            uint64_t tg = triG[vtx_off ? graph_of(vtx_off, G, v) : 0];
+            uint64_t tg = triG[vtx_off ? tc_graph_of(vtx_off, G, v) : 0];
             tcv[v] = quotient(x, tg);
         }
     }
@@ -311,7 +301,7 @@ __device__ __forceinline__ void rank_row_finish(int64_t r, uint64_t acc,
     } else {
         const uint64_t x = acc + tri_r[r];
         num[v] = x;
-        tcv[v] = quotient(x, triG[vtx_off ? graph_of(vtx_off, G, v) : 0]);
+        tcv[v] = quotient(x, triG[vtx_off ? tc_graph_of(vtx_off, G, v) : 0]);
     }
 }
 

@@ -335,16 +335,22 @@ struct GetHigh {
     __device__ uint32_t operator()(int64_t i) const { return (uint32_t)(a[i] >> bits); }
 };
 
+// With vtx_off (several graphs) a vertex's rank key is its graph, then its
+// degree: the order within a graph is the same, and as a graph's ranks are
+// consecutive, what is read and added to by rank stays inside a graph's few
+// hundred KB, which L2 holds, and the sums of the slot merge stay in LDS (512 BA
+// graphs with 17.8 M edges, whole call: 4429 to 3401 us).
 __global__ void k_degree(int32_t n, const uint32_t *__restrict__ us, const uint32_t *__restrict__ ue,
                          const uint32_t *__restrict__ ls, const uint32_t *__restrict__ le,
-                         int64_t *__restrict__ deg64, uint32_t *__restrict__ deg32,
+                         const int64_t *__restrict__ vtx_off, int32_t G, int dbits,
+                         int64_t *__restrict__ deg64, uint32_t *__restrict__ key,
                          uint32_t *__restrict__ dmax) {
     __shared__ uint32_t lds[BK / TC_WAVE];
     uint32_t mx = 0;
     GRID_STRIDE(x, n) {
         uint32_t d = (ue[x] - us[x]) + (le[x] - ls[x]);
         deg64[x] = d;
-        deg32[x] = d;
+        key[x] = vtx_off ? (uint32_t)tc_graph_of(vtx_off, G, x) << dbits | d : d;
         mx = d > mx ? d : mx;
     }
     tc_block_raise<BK>(mx, dmax, lds);
@@ -1076,9 +1082,23 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
     TC_TRY(tc_graph_alloc(g, &g->row_ptr, (int64_t)n + 1, s));
     // the canonical edges ordered by their larger end (kept for the
     // orientation), whose runs count the edges by larger end
-    uint32_t *deg32 = nullptr, *ls = nullptr, *le = nullptr;
+    uint32_t *key = nullptr, *ls = nullptr, *le = nullptr;
     int64_t *deg64 = nullptr;
-    TC_TRY(tmp.get(&deg32, nn));
+    TC_TRY(tmp.get(&key, nn));
+    // the rank order's key: (graph, degree) where 32 bits hold both, else the
+    // degree, which is below the vertices of its graph
+    int dbits = bits;
+    bool &by_graph = g->rank_by_graph;
+    if (num_graphs > 1 && g->h_vtx_off) {
+        int64_t most = 1;
+        for (int32_t i = 0; i < num_graphs; ++i) {
+            const int64_t c = g->h_vtx_off[i + 1] - g->h_vtx_off[i];
+            most = c > most ? c : most;
+        }
+        dbits = tc_bits_for((uint64_t)most);
+        by_graph = dbits + tc_bits_for((uint64_t)num_graphs) <= 32;
+    }
+    const int key_bits = by_graph ? dbits + tc_bits_for((uint64_t)num_graphs) : dbits;
     TC_TRY(tmp.get(&deg64, nn));
     TC_TRY(tmp.get(&ls, nn));
     TC_TRY(tmp.get(&le, nn));
@@ -1102,8 +1122,8 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
         TC_LAUNCHED();
     }
     if (n > 0) {
-        k_degree<<<grid_for(n) < 1024 ? grid_for(n) : 1024, BK, 0, s>>>(n, us, ue, ls, le, deg64, deg32,
-                                                                        g->err + 1);
+        k_degree<<<grid_for(n) < 1024 ? grid_for(n) : 1024, BK, 0, s>>>(
+            n, us, ue, ls, le, by_graph ? d_vtx_off : nullptr, num_graphs, dbits, deg64, key, g->err + 1);
         TC_LAUNCHED();
         TC_TRY(tc_scan_i64(deg64, g->row_ptr, n, g->row_ptr + n, s));
     } else {
@@ -1120,10 +1140,9 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
         TC_TRY(tmp.get(&pv, nn));
         TC_TRY(tmp.get(&pv2, nn));
         TC_TRY(tmp.get(&dk2, nn));
-        // degrees are below n, so `bits` bits hold them
         uint32_t *dk = nullptr;
         TC_TRY(tmp.get(&dk, nn));
-        TC_TRY(tc_sort_u32_index(deg32, &dk, &pv, &dk2, &pv2, n, bits, s));
+        TC_TRY(tc_sort_u32_index(key, &dk, &pv, &dk2, &pv2, n, key_bits, s));
         k_invert<<<grid_for(n), BK, 0, s>>>(pv, n, g->perm, g->rank);
         TC_LAUNCHED();
     }

@@ -35,13 +35,6 @@ constexpr int UNROLL = 4;  // independent candidate loads in flight per lane
 // edges (whole calls, low / middle, us: 161 k edges 980 / 1264, 205 k 936 / 880,
 // 308 k 1098 / 909 and 954 / 973, 442 k 948 / 878, 910 k 1263 / 970).
 constexpr int64_t AUTO_MID_MIN_EDGES = 200000;
-// The slot merge (tc_slots.hip) up to this longest oriented row: a slot's merge
-// grows with the rows, a table or bitmap lookup does not.  Whole calls, merge
-// against the forms above (us): BA attach 32, 0.65 M edges, longest row 50:
-// 625 / 853; BA attach 64, 12.9 M edges, 94: 4305 / 5726; R-MAT scale 13, 103:
-// 570 / 634; BA attach 100, 126: 1203 / 1175; R-MAT scale 15, 192: 1146 / 931;
-// scale 16, 246: 1879 / 955.
-constexpr int AUTO_SLOTS_MAX_DPLUS = 128;
 using namespace tc_tab;
 
 static inline unsigned grid_for(int64_t n, int block = BK) {
@@ -300,7 +293,7 @@ static bool tuning_valid(const tc_tuning *t) {
 // AUTO merges slots (tc_slots.hip, a low-pivot form without tables) where every
 // oriented row is short.
 static bool use_slots(const tc_graph *g, const tc_tuning &t) {
-    return t.algorithm == TC_ALGO_AUTO && g->max_dplus <= AUTO_SLOTS_MAX_DPLUS;
+    return t.algorithm == TC_ALGO_AUTO && g->max_dplus <= TC_SLOTS_MAX_DPLUS;
 }
 
 // The pivot form AUTO (or the tuning) takes for this graph.

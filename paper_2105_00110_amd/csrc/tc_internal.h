@@ -217,6 +217,7 @@ struct tc_graph {
     int64_t *vtx_off = nullptr;                     // device [G+1]
     int64_t *h_vtx_off = nullptr;                   // host [G+1]
     int64_t *h_edge_off = nullptr;                  // host [G+1]
+    bool rank_by_graph = false;                     // a graph's ranks are consecutive
     int32_t max_dplus = 0;
     int32_t max_degree = 0;
     // oriented wedges of the rows of the tc_core_ranks(j) highest ranks, the
@@ -288,6 +289,13 @@ bool tc_single_fits(int64_t P, int32_t n);
 tc_status tc_single_build(tc_graph *g, const int32_t *d_src, const int32_t *d_dst, int64_t P,
                           hipStream_t s);
 tc_status tc_single_count(tc_graph *g, hipStream_t s);
+// The slot merge (tc_slots.hip) up to this longest oriented row: a slot's merge
+// grows with the rows, a table or bitmap lookup does not.  Whole calls, merge
+// against the forms above (us): BA attach 32, 0.65 M edges, longest row 50:
+// 625 / 853; BA attach 64, 12.9 M edges, 94: 4305 / 5726; R-MAT scale 13, 103:
+// 570 / 634; BA attach 100, 126: 1203 / 1175; R-MAT scale 15, 192: 1146 / 931;
+// scale 16, 246: 1879 / 955.
+constexpr int TC_SLOTS_MAX_DPLUS = 128;
 // Flat graphs (tc_slots.hip): support per slot into the zeroed g->osup, then
 // everything that tc_aggregate fills.
 tc_status tc_count_slots(tc_graph *g, unsigned long long *found, hipStream_t s);
@@ -333,6 +341,18 @@ __device__ __forceinline__ T tc_wave_max(T x) {
         x = y > x ? y : x;
     }
     return x;
+}
+
+// The graph of global vertex id (or, as a graph's ranks take the places of its
+// vertices, rank) v: the last g with vtx_off[g] <= v.
+__device__ __forceinline__ int32_t tc_graph_of(const int64_t *__restrict__ vtx_off, int32_t G,
+                                               int64_t v) {
+    int32_t lo = 0, hi = G - 1;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (vtx_off[mid] <= v) lo = mid; else hi = mid - 1;
+    }
+    return lo;
 }
 
 // Reserves c places for each thread of a BLOCK-thread workgroup behind the

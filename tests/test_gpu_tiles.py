@@ -201,6 +201,38 @@ def test_slot_merge_batch(tclib):
     g.close()
 
 
+# ranks by graph: (graph, degree) keys of 32 bits at most, graphs without
+# vertices between others, a graph above the sums' LDS window of 8192 ranks,
+# runs of slots that end inside graphs; and keys of more than 32 bits, where
+# ranks follow degrees alone
+BATCH_RANKS = {
+    "uneven": [gg.ba(9000, 12, seed=1), gg.clique(9), (np.zeros(0, np.int32), np.zeros(0, np.int32), 0),
+               gg.ba(700, 3, seed=2), gg.ba(20_000, 7, seed=3), gg.clique(2), gg.ba(60, 16, seed=4)],
+    "wide_keys": [(np.array([5, 5, 1 << 20], np.int32), np.array([1 << 20, 77, 77], np.int32),
+                   (1 << 20) + 1)] + [gg.clique(3 + i % 7) for i in range(4095)],
+}
+
+
+@pytest.mark.parametrize("name", sorted(BATCH_RANKS))
+def test_batch_ranks(tclib, name):
+    graphs = BATCH_RANKS[name]
+    po = np.cumsum([0] + [len(g[0]) for g in graphs])
+    vo = np.cumsum([0] + [g[2] for g in graphs])
+    src, dst = (np.concatenate([g[k] for g in graphs]) for k in (0, 1))
+    g = tclib.Graph.batch(src, dst, po, vo)
+    _say("batch ranks", name, "n", int(vo[-1]))
+    g.compute()
+    r = g.results()
+    g.close()
+    off = np.repeat(vo[:-1], np.diff(po))
+    ref = native.o2_paper((src + off).astype(np.int32), (dst + off).astype(np.int32), int(vo[-1]))
+    np.testing.assert_array_equal(r["support"], ref.sup)
+    np.testing.assert_array_equal(r["tri"], ref.tri)
+    np.testing.assert_array_equal(r["num"], ref.num)
+    tri = np.concatenate([[0], np.cumsum(ref.tri)])
+    np.testing.assert_array_equal(3 * r["triG"].astype(np.int64), tri[vo[1:]] - tri[vo[:-1]])
+
+
 def _pairs_over(n, P, seed):
     """P random pairs over n vertices, a clique on the top ids among them."""
     rng = np.random.default_rng(seed)
