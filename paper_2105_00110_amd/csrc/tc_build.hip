@@ -595,55 +595,75 @@ __global__ __launch_bounds__(BK) void k_dplus_lists(int32_t n, const uint32_t *_
     }
 }
 
-// Buckets of 1..SEG_SMALL entries.  Every wavefront reads the sizes of 64
+// Buckets of 1..SEG_SMALL entries.  A wavefront reads the sizes of up to 64
 // consecutive vertices and sorts their buckets by size class (lo, GL],
 // GL = 8, 16, 32, 64: GL lanes per bucket, 64 / GL buckets at a time, taken
-// from the ballot of the class (classes (64, 128] and (128, 256]: the whole
-// wavefront, orient_class_wide).  Each lane places its entry by the number of
-// smaller keys in its group (keys of a bucket are distinct ranks).  The grid
-// strides over the vertices, so there is no wavefront per vertex to
-// dispatch.
+// from the class's list of lanes in LDS (classes (64, 128] and (128, 256]: the
+// whole wavefront, orient_class_wide).  Each lane places its entry by the number
+// of smaller keys in its group (keys of a bucket are distinct ranks; groups are
+// filled up with the largest value, so that they are read four at a time).  The
+// next bucket's entries are loaded while one is sorted.
+//
+// Bound by the scattered rows (a few lines each) and, where there are few
+// wavefronts, by the chain of one bucket after the other: below 2^19 vertices a
+// wavefront takes 16, not 64 (R-MAT scale 16: 104 us before, 32; at scale 20, 16
+// take 202 us and 64 178, where it was 300; scale 24 2546 to 1882).
+struct OrientOut {
+    int32_t *ocol;
+    uint32_t *o2e;
+    int32_t *orow;
+};
+
+// The lanes whose bucket is of the class, in order, in lst; their number.
+__device__ __forceinline__ int orient_list(bool in, uint8_t *lst) {
+    const uint64_t mask = __ballot(in);
+    if (in) lst[__popcll(mask & tc_lanemask_lt())] = (uint8_t)__lane_id();
+    __builtin_amdgcn_wave_barrier();
+    return __popcll(mask);
+}
+
 template <int GL>
-__device__ __forceinline__ void orient_class(int64_t x0, uint32_t dl, uint32_t lo, uint32_t *wsk,
+__device__ __forceinline__ void orient_class(uint32_t dl, uint32_t lo, uint32_t *wsk, uint8_t *lst,
                                              int64_t bl, int32_t rl, int64_t ol,
-                                             const uint64_t *__restrict__ tbuf,
-                                             int32_t *__restrict__ ocol, uint32_t *__restrict__ o2e,
-                                             int32_t *__restrict__ orow) {
-    static_assert(GL <= SEG_WAVE && TC_WAVE % GL == 0, "group size");
+                                             const uint64_t *__restrict__ tbuf, OrientOut out) {
+    static_assert(GL <= SEG_WAVE && TC_WAVE % GL == 0 && GL % 4 == 0, "group size");
     constexpr int GPW = TC_WAVE / GL;
+    const int cnt = orient_list(dl > lo && dl <= (uint32_t)GL, lst);
     const int lane = __lane_id();
     const int grp = lane / GL, sl = lane % GL;
     uint32_t *gsk = wsk + grp * GL;
-    uint64_t mask = __ballot(dl > lo && dl <= (uint32_t)GL);
-    while (mask) {
-        // this group's vertex: the grp-th set bit of the mask, if any
-        uint64_t mm = mask;
-        for (int q = 0; q < grp && mm; ++q) mm &= mm - 1;
-        const bool has = mm != 0;
-        const int j = has ? __ffsll((long long)mm) - 1 : 0;
-        for (int q = 0; q < GPW && mask; ++q) mask &= mask - 1;
-        const int d = (int)__shfl(dl, j, TC_WAVE);
-        // the row's bucket start, rank and oriented start, loaded once per
-        // chunk by the lane of the vertex
+    // this group's it-th vertex, its size (0: none) and this lane's entry
+    int j = 0, d = 0;
+    uint64_t w = 0;
+    const auto load = [&](int at) {
+        j = at < cnt ? lst[at] : 0;
         const int64_t bx = __shfl(bl, j, TC_WAVE);
+        const int dj = (int)__shfl(dl, j, TC_WAVE);
+        d = at < cnt ? dj : 0;
+        if (sl < d) w = tbuf[bx + sl];
+    };
+    load(grp);
+    for (int it = 0; it < cnt; it += GPW) {
+        const int dc = d;
+        const uint64_t wc = w;
         const int32_t rx = __shfl(rl, j, TC_WAVE);
         const int64_t ob = __shfl(ol, j, TC_WAVE);
-        const bool mine = has && sl < d;
-        uint32_t key = 0xFFFFFFFFu, val = 0;
-        if (mine) {
-            const uint64_t w = tbuf[bx + sl];
-            key = (uint32_t)(w >> 32);
-            val = (uint32_t)w;
-        }
+        load(it + GPW + grp);
+        const bool mine = sl < dc;
+        const uint32_t key = mine ? (uint32_t)(wc >> 32) : 0xFFFFFFFFu;
         gsk[sl] = key;
         __builtin_amdgcn_wave_barrier();
         if (mine) {
             int pos = 0;
-            for (int t = 0; t < d; ++t) pos += gsk[t] < key ? 1 : 0;
+            for (int t = 0; t < dc; t += 4) {
+                const uint4 q = *reinterpret_cast<const uint4 *>(gsk + t);
+                pos += (q.x < key ? 1 : 0) + (q.y < key ? 1 : 0) + (q.z < key ? 1 : 0) +
+                       (q.w < key ? 1 : 0);
+            }
             const int64_t k = ob + pos;
-            ocol[k] = (int32_t)key;
-            o2e[k] = val;
-            orow[k] = rx;
+            out.ocol[k] = (int32_t)key;
+            out.o2e[k] = (uint32_t)wc;
+            out.orow[k] = rx;
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -651,69 +671,78 @@ __device__ __forceinline__ void orient_class(int64_t x0, uint32_t dl, uint32_t l
 
 // Buckets of lo < d <= 64 E entries: the whole wavefront, E entries per
 // lane, each placed by counting the smaller keys (the keys are read back from
-// LDS one at a time, the same word for every lane).
+// LDS, the same words for every lane).
 template <int E>
-__device__ __forceinline__ void orient_class_wide(int64_t x0, uint32_t dl, uint32_t lo,
-                                                  uint32_t *wsk, int64_t bl, int32_t rl,
-                                                  int64_t ol, const uint64_t *__restrict__ tbuf,
-                                                  int32_t *__restrict__ ocol,
-                                                  uint32_t *__restrict__ o2e,
-                                                  int32_t *__restrict__ orow) {
+__device__ __forceinline__ void orient_class_wide(uint32_t dl, uint32_t lo, uint32_t *wsk,
+                                                  uint8_t *lst, int64_t bl, int32_t rl, int64_t ol,
+                                                  const uint64_t *__restrict__ tbuf, OrientOut out) {
+    const int cnt = orient_list(dl > lo && dl <= (uint32_t)(TC_WAVE * E), lst);
     const int lane = __lane_id();
-    uint64_t mask = __ballot(dl > lo && dl <= (uint32_t)(TC_WAVE * E));
-    while (mask) {
-        const int j = __ffsll((long long)mask) - 1;
-        mask &= mask - 1;
-        const int d = (int)__shfl(dl, j, TC_WAVE);
+    int j = 0, d = 0;
+    uint64_t w[E] = {};
+    const auto load = [&](int at) {
+        if (at >= cnt) return;
+        j = lst[at];
+        d = (int)__shfl(dl, j, TC_WAVE);
         const int64_t b = __shfl(bl, j, TC_WAVE);
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (lane + TC_WAVE * e < d) w[e] = tbuf[b + lane + TC_WAVE * e];
+    };
+    load(0);
+    for (int it = 0; it < cnt; ++it) {
+        const int dc = d;
         const int32_t rx = __shfl(rl, j, TC_WAVE);
         const int64_t ob = __shfl(ol, j, TC_WAVE);
         uint32_t key[E], val[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int i = lane + TC_WAVE * e;
-            key[e] = 0xFFFFFFFFu;
-            val[e] = 0;
-            if (i < d) {
-                const uint64_t w = tbuf[b + i];
-                key[e] = (uint32_t)(w >> 32);
-                val[e] = (uint32_t)w;
-            }
+            key[e] = i < dc ? (uint32_t)(w[e] >> 32) : 0xFFFFFFFFu;
+            val[e] = (uint32_t)w[e];
             wsk[i] = key[e];
         }
+        load(it + 1);
         __builtin_amdgcn_wave_barrier();
         int pos[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) pos[e] = 0;
-        for (int t = 0; t < d; ++t) {
-            const uint32_t kt = wsk[t];
+        for (int t = 0; t < dc; t += 4) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(wsk + t);
 #pragma unroll
-            for (int e = 0; e < E; ++e) pos[e] += kt < key[e] ? 1 : 0;
+            for (int e = 0; e < E; ++e)
+                pos[e] += (q.x < key[e] ? 1 : 0) + (q.y < key[e] ? 1 : 0) +
+                          (q.z < key[e] ? 1 : 0) + (q.w < key[e] ? 1 : 0);
         }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            if (lane + TC_WAVE * e < d) {
-                ocol[ob + pos[e]] = (int32_t)key[e];
-                o2e[ob + pos[e]] = val[e];
-                orow[ob + pos[e]] = rx;
+            if (lane + TC_WAVE * e < dc) {
+                out.ocol[ob + pos[e]] = (int32_t)key[e];
+                out.o2e[ob + pos[e]] = val[e];
+                out.orow[ob + pos[e]] = rx;
             }
         }
         __builtin_amdgcn_wave_barrier();
     }
 }
 
+// per: vertices of a wavefront at a time, at most 64
 __global__ __launch_bounds__(256) void k_orient_small(
-    int32_t n, const int64_t *__restrict__ row_ptr, const uint32_t *__restrict__ cursor,
+    int32_t n, int per, const int64_t *__restrict__ row_ptr, const uint32_t *__restrict__ cursor,
     const int32_t *__restrict__ rank, const int64_t *__restrict__ orp,
     const uint64_t *__restrict__ tbuf, int32_t *__restrict__ ocol, uint32_t *__restrict__ o2e,
     int32_t *__restrict__ orow) {
-    __shared__ uint32_t sk[4][SEG_SMALL];
+    __shared__ uint4 sk[4][SEG_SMALL / 4];
+    __shared__ uint8_t lists[4][TC_WAVE];
     const int wv = threadIdx.x / TC_WAVE;
     const int lane = __lane_id();
     const int64_t nwaves = (int64_t)gridDim.x * 4;
-    for (int64_t x0 = ((int64_t)blockIdx.x * 4 + wv) * TC_WAVE; x0 < n; x0 += nwaves * TC_WAVE) {
+    uint32_t *wsk = reinterpret_cast<uint32_t *>(sk[wv]);
+    uint8_t *lst = lists[wv];
+    const OrientOut out{ocol, o2e, orow};
+    for (int64_t x0 = ((int64_t)blockIdx.x * 4 + wv) * per; x0 < n; x0 += nwaves * per) {
         const int64_t xl = x0 + lane;
-        const uint32_t dl = xl < n ? cursor[xl] : 0u;
+        const uint32_t dl = lane < per && xl < n ? cursor[xl] : 0u;
         // each lane's vertex: bucket start, rank, oriented row start (the
         // rows of every class in this chunk read them from here)
         int64_t bl = 0, ol = 0;
@@ -723,12 +752,12 @@ __global__ __launch_bounds__(256) void k_orient_small(
             rl = rank[xl];
             ol = orp[rl];
         }
-        orient_class<8>(x0, dl, 0, sk[wv], bl, rl, ol, tbuf, ocol, o2e, orow);
-        orient_class<16>(x0, dl, 8, sk[wv], bl, rl, ol, tbuf, ocol, o2e, orow);
-        orient_class<32>(x0, dl, 16, sk[wv], bl, rl, ol, tbuf, ocol, o2e, orow);
-        orient_class<64>(x0, dl, 32, sk[wv], bl, rl, ol, tbuf, ocol, o2e, orow);
-        orient_class_wide<2>(x0, dl, 64, sk[wv], bl, rl, ol, tbuf, ocol, o2e, orow);
-        orient_class_wide<4>(x0, dl, 128, sk[wv], bl, rl, ol, tbuf, ocol, o2e, orow);
+        orient_class<8>(dl, 0, wsk, lst, bl, rl, ol, tbuf, out);
+        orient_class<16>(dl, 8, wsk, lst, bl, rl, ol, tbuf, out);
+        orient_class<32>(dl, 16, wsk, lst, bl, rl, ol, tbuf, out);
+        orient_class<64>(dl, 32, wsk, lst, bl, rl, ol, tbuf, out);
+        orient_class_wide<2>(dl, 64, wsk, lst, bl, rl, ol, tbuf, out);
+        orient_class_wide<4>(dl, 128, wsk, lst, bl, rl, ol, tbuf, out);
     }
 }
 
@@ -969,9 +998,10 @@ tc_status tc_orient(tc_graph *g, hipStream_t s) {
     TC_TRY(tc_scan_i64(dplus, g->orp, n, g->orp + n, s));
     // pass B: each bucket in rank order
     {
-        const int64_t want = tc_div_up(n, 4 * TC_WAVE);
-        const unsigned grid = (unsigned)(want < 2048 ? (want > 0 ? want : 1) : 2048);
-        k_orient_small<<<grid, BK, 0, s>>>(n, g->row_ptr, cursor, g->rank, g->orp, tbuf, g->ocol,
+        const int per = n < (1 << 19) ? 16 : TC_WAVE;
+        const int64_t want = tc_div_up(n, 4 * per);
+        const unsigned grid = (unsigned)(want < 65536 ? (want > 0 ? want : 1) : 65536);
+        k_orient_small<<<grid, BK, 0, s>>>(n, per, g->row_ptr, cursor, g->rank, g->orp, tbuf, g->ocol,
                                            g->o2e, g->orow);
         TC_LAUNCHED();
     }

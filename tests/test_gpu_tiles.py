@@ -341,3 +341,22 @@ def test_core_products(tclib, name):
     for k in ("tri", "support", "triG", "num"):
         np.testing.assert_array_equal(a[k], b[k])
     g.close()
+
+
+# orientation buckets at the edges of the size classes (8, 16, 32, 64, 128, 256
+# and the sorts above), several of a class in one wavefront, in wavefronts of 16
+# vertices and of 64 (from 2^19 on)
+@pytest.mark.parametrize("n", [3000, (1 << 19) + 5000])
+def test_orientation_buckets(tclib, n):
+    # every hub links to `size` vertices of higher degree, so its bucket has that many
+    sizes = [1, 7, 8, 9, 9, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 66, 127, 128, 129, 255, 256, 257]
+    s, d, _ = gg.clique(600)
+    src, dst = [s], [d]
+    for rep in range(3):
+        for i, size in enumerate(sizes):
+            v = 600 + rep * len(sizes) + i if rep < 2 else n - 1 - i
+            src.append(np.full(size, v, np.int32))
+            dst.append(np.arange(size, dtype=np.int32) + 7 * rep)
+    src, dst = np.concatenate(src).astype(np.int32), np.concatenate(dst).astype(np.int32)
+    _say("orientation buckets", n)
+    assert_parity(run_gpu(tclib, src, dst, n), native.o2_paper(src, dst, n))
