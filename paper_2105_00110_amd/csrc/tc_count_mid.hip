@@ -57,7 +57,13 @@ constexpr int BK = 256;
 constexpr size_t GROUP_BYTES = 64 * 8 * 3 + 64 * 4;  // gx, gs, gb (int64), gt (int32)
 constexpr int GROUP_LANES = 16;  // lanes per short pivot (k_mid_groups)
 constexpr int GROUP_DMAX = 128;  // rows up to this many entries go to k_mid_groups
-constexpr int GROUP_PAIRS = 64;  // pairs per k_mid_groups item
+// Pairs per k_mid_groups item.  A group takes 16 at a time, one after the other:
+// where there are few items, that chain is what the kernel waits for (R-MAT
+// scale 15, whole call: 16 pairs 718 us, 64 819; scale 18 1963, 2110); where
+// there are many, it is the tables (scale 20: 16 pairs 5916 us, 32 5858, 64
+// 5832; scale 22 23277, 22929, 22966).
+constexpr int GROUP_PAIRS_FEW = 16, GROUP_PAIRS = 32;
+constexpr int64_t FEW_EDGES = (int64_t)1 << 23;
 
 // Words of the bit rows of a row with d entries: Σ_{t=1}^{d-1} ceil(t/32).
 __host__ __device__ __forceinline__ int64_t bit_words(int64_t d) {
@@ -139,8 +145,8 @@ enum { L_FOLD = NPLANS, L_FOLD_BIG, NLISTS };
 struct PlanRules {
     int gmax, light_max, huge_min;  // |N_H(v)| bounds of the classes
     int split, lsplit;              // span bitmap for workgroup / wavefront pivots
-    int64_t span_max, pairs_min;    // a pivot fits it up to this span; wavefront ones from
-                                    // this many pairs
+    int64_t span_max;               // a pivot fits it up to this span; a wavefront one
+    int64_t pairs_min, wide_min;    // takes it from this many pairs, above gmax from these
     int32_t r16s;                   // workgroup pivots from this rank on: LK_BITMAP16
     int S[NPLANS];
 };
@@ -152,14 +158,16 @@ __device__ __forceinline__ int item_class(const PlanRules &q, int64_t v, int64_t
     if (d >= q.huge_min) return P_HUGE;
     const bool heavy = d > q.light_max;
     if (heavy && v >= q.r16s) return P_BITMAP16;
-    if (heavy ? q.split != 0 : q.lsplit != 0 && in >= q.pairs_min) {
+    if (heavy ? q.split != 0 : q.lsplit != 0 && in >= (d > q.gmax ? q.wide_min : q.pairs_min)) {
         const int64_t span = (int64_t)row[d - 1] - row[0] + 1;
         if (span <= q.span_max) return heavy ? P_BITMAP : P_LBITMAP;
     }
     return heavy ? P_BLOCK : (d <= q.gmax ? P_GROUP : P_WAVE);
 }
 
-constexpr int PLAN_PER = 8;  // vertices per thread
+// Vertices per thread: few, for the chain of a thread (8: 48 us for the two passes
+// and the scan at R-MAT scale 20, 38 at scale 16; 2: 39 and 20).
+constexpr int PLAN_PER = 2;
 constexpr int PLAN_TILE = BK * PLAN_PER;
 
 // ---------------------------------------------------------------------------
@@ -1515,15 +1523,19 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
     // wavefront pivots with rows of at most GROUP_DMAX entries run
     // 64 / GROUP_LANES to a wavefront, in items of at most GROUP_PAIRS pairs
     const int gmax = light_max < GROUP_DMAX ? light_max : GROUP_DMAX;
-    const int group_pairs = wave_pairs < GROUP_PAIRS ? wave_pairs : GROUP_PAIRS;
+    const int group_most = g->m < FEW_EDGES ? GROUP_PAIRS_FEW : GROUP_PAIRS;
+    const int group_pairs = wave_pairs < group_most ? wave_pairs : group_most;
     // workgroup pivots among the top 2^16 ranks take the 2048-word bitmap
     // over 16-bit values whatever their span (when the tuning allows that
     // many words), in a launch of their own whose smaller LDS footprint
     // keeps more wavefronts resident; the others take the span bitmap or
     // hash
     const int32_t r16s = bw >= BITMAP16_WORDS ? g->rank16_base : 0x7FFFFFFF;
-    PlanRules rules = {gmax, light_max, huge_min, split, lsplit, span_max, t.light_bitmap_pairs, r16s,
-                       {}};
+    // few edges: not a launch of k_mid_wave for a handful of pivots (26 us at
+    // R-MAT scale 16, of 850), which the bitmaps take as well
+    const int64_t wide_min = g->m < FEW_EDGES ? 1 : t.light_bitmap_pairs;
+    PlanRules rules = {gmax, light_max, huge_min, split, lsplit, span_max, t.light_bitmap_pairs, wide_min,
+                       r16s, {}};
     for (int i = 0; i < NPLANS; ++i) rules.S[i] = block_pairs;
     rules.S[P_GROUP] = group_pairs;
     rules.S[P_WAVE] = rules.S[P_ZERO] = wave_pairs;

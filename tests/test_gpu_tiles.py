@@ -360,3 +360,29 @@ def test_orientation_buckets(tclib, n):
     src, dst = np.concatenate(src).astype(np.int32), np.concatenate(dst).astype(np.int32)
     _say("orientation buckets", n)
     assert_parity(run_gpu(tclib, src, dst, n), native.o2_paper(src, dst, n))
+
+
+# the middle pivot's items: short pivots with one, 15 to 17, 31 to 33 and 63 to 65
+# pairs, and wavefront pivots (rows of 129 to 200) with one to 70 pairs
+def test_mid_pivot_items(tclib):
+    src, dst, nxt = [], [], 400
+    s, d, _ = gg.clique(400)
+    src.append(s), dst.append(d)
+    for pairs in (1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 70):
+        for row in (2, 60, 128, 129, 200):
+            v, nxt = nxt, nxt + 1
+            src.append(np.full(row, v)), dst.append(np.arange(row) + pairs)
+            low = np.arange(nxt, nxt + pairs)  # lower ends, each also in the pivot's row
+            nxt += pairs
+            for t in (0, row // 2, row - 1):
+                src.append(low), dst.append(np.full(pairs, pairs + t))
+            src.append(low), dst.append(np.full(pairs, v))
+    src, dst = np.concatenate(src).astype(np.int32), np.concatenate(dst).astype(np.int32)
+    _say("mid pivot items", nxt)
+    ref = native.o2_paper(src, dst, nxt)
+    g = tclib.Graph.from_edges(src, dst, nxt)
+    g.compute({"algorithm": tclib.TC_ALGO_MID_PIVOT})
+    r = g.results()
+    g.close()
+    for k, want in (("support", ref.sup), ("tri", ref.tri), ("num", ref.num)):
+        np.testing.assert_array_equal(r[k], want)
