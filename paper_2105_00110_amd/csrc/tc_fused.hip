@@ -403,7 +403,8 @@ __device__ __forceinline__ void fused_small(const FusedArgs &a, const GraphRef q
 // count, offset, rank and sum that the edges gather or add to is in LDS.  Bound
 // by the memory latency of one workgroup's 16 wavefronts, so loads in flight
 // count: a loop over single elements waits a round trip for each (4096 BA
-// graphs: 25.8 ms before, 14.9 ms so, of which the merge's random rows take 8.4).
+// graphs: 25.8 ms before, 14.9 ms so, of which the merge's random rows took 8.4;
+// 10.65 ms with the highest rows and their counts in LDS).
 // ---------------------------------------------------------------------------
 template <int BLOCK>
 struct Medium {
@@ -411,6 +412,7 @@ struct Medium {
     static constexpr uint32_t PMAX = 1u << 20;
     static constexpr uint32_t LT = 8 * BLOCK;   // elements per tile of the loops
     static constexpr uint32_t ST = 16 * BLOCK;  // of the sort
+    static constexpr uint32_t CT = 4 * BLOCK;   // of the merge (8: 10.71 ms, 2: 10.72)
     // longest oriented row: d+ neighbours of degree >= d+ each, so d+^2 <= 2m
     static constexpr uint32_t HALO = 1536;
     // bytes: per-vertex words and the row sort's tile with its halo, or a rank
@@ -418,8 +420,12 @@ struct Medium {
     static constexpr size_t ROWS = 4 * (size_t)NMAX + 4 * (LT + 2 * HALO);
     static constexpr size_t ORIENT = 6 * (size_t)NMAX;
     static constexpr size_t SORT = 4 * (size_t)ST + 4 * (size_t)(BLOCK / TC_WAVE) * tc_small::RADIX;
-    static constexpr size_t BYTES = ROWS > ORIENT ? (ROWS > SORT ? ROWS : SORT)
-                                                  : (ORIENT > SORT ? ORIENT : SORT);
+    // what is left of a workgroup's share of LDS: the merge's cache
+    static constexpr size_t COUNT = 150 * (size_t)BLOCK;
+    static constexpr size_t max2(size_t x, size_t y) { return x > y ? x : y; }
+    static constexpr size_t BYTES = max2(max2(ROWS, ORIENT), max2(SORT, COUNT));
+    static constexpr uint32_t PAD = 8;  // a window of the merge past its row
+    static_assert(BYTES / 4 - NMAX >= CT + HALO + PAD, "a tile of the merge fits after the row ends");
 };
 
 // Digit counts of up to 4 passes, running bases during a pass; scan words.
@@ -532,7 +538,7 @@ template <int BLOCK>
 __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef q, unsigned char *raw,
                              MediumTail<BLOCK> &T) {
     using namespace tc_small;
-    constexpr uint32_t NMAX = Medium<BLOCK>::NMAX, LT = Medium<BLOCK>::LT, HALO = Medium<BLOCK>::HALO;
+    constexpr uint32_t NMAX = Medium<BLOCK>::NMAX, LT = Medium<BLOCK>::LT, CT = Medium<BLOCK>::CT, HALO = Medium<BLOCK>::HALO;
     constexpr int U = 8;  // elements per thread of a tile
     const uint32_t n = q.n, P = q.P;
     const int tid = threadIdx.x;
@@ -641,6 +647,7 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
     // its row as (lower rank << 16 | higher rank, edge), any order: one 8-byte
     // store per edge (A and B), since each store of the scatter is a sector
     Entry *const entry = reinterpret_cast<Entry *>(q.A);
+    uint32_t longest = 0;  // row
     for (int pass = 0; pass < 2; ++pass) {
         for (uint32_t t0 = 0; t0 < m; t0 += LT) {
             uint32_t key[U];
@@ -667,7 +674,12 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
             constexpr int PER = (int)(NMAX / BLOCK);
             uint32_t sum = 0, all;
             const uint32_t r0 = tid * PER;
-            for (int j = 0; j < PER; ++j) sum += r0 + j < n ? words[r0 + j] : 0u;
+            for (int j = 0; j < PER; ++j) {
+                const uint32_t d = r0 + j < n ? words[r0 + j] : 0u;
+                sum += d;
+                longest = d > longest ? d : longest;
+            }
+            longest = wg_max<BLOCK>(longest, T.wsum);
             uint32_t off = wg_scan<BLOCK>(sum, &all, T.wsum);
             for (int j = 0; j < PER; ++j)
                 if (r0 + j < n) {
@@ -711,20 +723,37 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
     // count: the tail of N_H(r) after c merged with N_H(c), supports added to
     // the canonical edges (so that they leave in order).  A lane goes on to its
     // next slot as soon as its merge ends, without waiting for the longest
-    // merge of the wavefront
+    // merge of the wavefront.  The last slots, whose rows are of the highest
+    // ranks and merged most, lie in LDS with their counts (column | count << 16;
+    // a support is below n < 2^16), the others are taken in tiles that do while
+    // they are a merge's own row: what is left to device memory are the rows
+    // N_H(c) of lower ranks and their hits
     uint32_t *const esup = q.A;  // the entries are no longer needed
     for (uint32_t e = tid; e < m; e += BLOCK) at(esup, e) = 0;
+    uint32_t *const top = words + n;
+    const uint32_t room = (uint32_t)(Medium<BLOCK>::BYTES / 4) - n - Medium<BLOCK>::PAD;
+    const uint32_t kept = m <= room ? m : room - (CT + longest), top0 = m - kept;
+    uint32_t *const run = top + kept;
+    for (uint32_t i = tid; i < kept; i += BLOCK) top[i] = at(ocol, top0 + i) & 0xFFFFu;
     __syncthreads();
-    {
-        uint32_t s = tid, t = 0, i = 0, ie = 0, j = 0, je = 0;
-        uint32_t w = s < m ? at(ocol, s) : 0u;
+    for (uint32_t t0 = 0; t0 < m; t0 = t0 < top0 ? (top0 - t0 > CT ? t0 + CT : top0) : m) {
+        const bool tile = t0 < top0;
+        const uint32_t end = tile ? (top0 - t0 > CT ? t0 + CT : top0) : m;
+        uint32_t *const own = tile ? run : top;  // slot t0 on
+        const uint32_t len = (m - end > longest && tile ? end + longest : m) - t0;
+        if (tile) {
+            for (uint32_t i = tid; i < len; i += BLOCK) own[i] = at(ocol, t0 + i) & 0xFFFFu;
+            __syncthreads();
+        }
+        uint32_t s = t0 + tid, t = 0, i = 0, ie = 0, j = 0, je = 0;
+        uint32_t w = s < end ? at(ocol, s) : 0u;
         bool open = false;  // slot s is being merged
         for (;;) {
-            while (s < m && !(open && i < ie && j < je)) {
+            while (s < end && !(open && i < ie && j < je)) {
                 if (open) {
-                    if (t) wg_add(&at(esup, at(o2e, s)), t);
+                    if (t) atomicAdd(&own[s - t0], t << 16);
                     s += BLOCK;
-                    if (s >= m) break;
+                    if (s >= end) break;
                     w = at(ocol, s);
                 }
                 const uint32_t c = w & 0xFFFFu;
@@ -735,12 +764,19 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
                 t = 0;
                 open = true;
             }
-            if (s >= m) break;
-            // windows may reach past their row, and past the last one into the
-            // array that follows
+            if (s >= end) break;
+            // windows may reach past their row, and past the last one into
+            // what follows
             uint32_t x[8], y[8], na, nb, hits, where;
-            load8(&at(ocol, i), x);
-            load8(&at(ocol, j), y);
+            const bool in_top = j >= top0;
+            if (in_top) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[e] = top[j - top0 + e];
+            } else {
+                load8(&at(ocol, j), y);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = own[i - t0 + e];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 x[e] &= 0xFFFFu;
@@ -750,15 +786,22 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
             t += (uint32_t)__popc(hits);
             while (hits) {
                 const uint32_t e = (uint32_t)__ffs((int)hits) - 1u;
+                const uint32_t f = j + ((where >> (4 * e)) & 15u);
                 hits &= hits - 1u;
-                wg_add(&at(esup, at(o2e, i + e)), 1u);
-                wg_add(&at(esup, at(o2e, j + ((where >> (4 * e)) & 15u))), 1u);
+                atomicAdd(&own[i - t0 + e], 1u << 16);
+                if (in_top) atomicAdd(&top[f - top0], 1u << 16);
+                else wg_add(&at(esup, at(o2e, f)), 1u);
             }
             i += na;
             j += nb;
         }
+        __syncthreads();
+        for (uint32_t i = tid; i < len; i += BLOCK) {
+            const uint32_t c = own[i] >> 16;
+            if (c) wg_add(&at(esup, at(o2e, t0 + i)), c);
+        }
+        __syncthreads();
     }
-    __syncthreads();
     // twice the triangles per rank, in LDS (at most 2^20 edges make at most
     // 5.1e8 triangles: every sum here is below 2^32), with the supports out
     for (uint32_t v = tid; v < n; v += BLOCK) {

@@ -243,6 +243,20 @@ def _pairs_over(n, P, seed):
     return src, dst, n
 
 
+def _edges_over(n, m, seed):
+    """m distinct edges over n vertices, a clique on the top ids among them."""
+    rng = np.random.default_rng(seed)
+    s, d, _ = gg.clique(60)
+    k = np.unique(np.concatenate([(s + n - 60) * n + d + n - 60, rng.integers(0, n * n, 3 * m)]))
+    a, b = k // n, k % n
+    k = np.unique(np.minimum(a, b) * n + np.maximum(a, b))
+    k = k[k // n < k % n]
+    top = k[k // n >= n - 60]
+    k = np.concatenate([top, rng.permutation(k[k // n < n - 60])])[:m]
+    assert k.shape[0] == m
+    return (k // n).astype(np.int32), (k % n).astype(np.int32), n
+
+
 # the tiers of the fused launch at 1024 threads: LDS (16384 pairs, 4096
 # vertices), LDS for vertices only (2^20 pairs, 21504 vertices), workspace
 FUSED_TIERS = {
@@ -258,6 +272,9 @@ FUSED_TIERS = {
     "most_pairs": lambda: gg.rmat(14, 64, seed=9),
     "pairs_past": lambda: gg.rmat(14, 64, seed=9, num_pairs=(1 << 20) + 1),
     "longest_rows": lambda: gg.clique(1440),
+    # the merge's LDS cache: every slot of the graph, and one more
+    "cache_full": lambda: _edges_over(5000, 153_600 // 4 - 8 - 5000, 10),
+    "cache_past": lambda: _edges_over(5000, 153_600 // 4 - 8 - 5000 + 1, 11),
 }
 
 
