@@ -37,7 +37,9 @@
 // products where those are faster (tc_core.hip): a pivot's pairs end at
 // tc_pairs_end, and the fold leaves such rows out.
 //
-// Work mapping.  A work item is a pivot with a slice of its pairs.  A
+// Work mapping.  A work item is a pivot with a slice of its pairs.  The lists are
+// in rank order and are taken from the end, where the slices are full and the
+// rows long (R-MAT scale 20: 5842 us from the front, 5718 so).  A
 // wavefront takes 64 pairs at a time and flattens their bit rows: a prefix
 // sum of the row lengths in words places word x of the group, and the lane
 // that owns word x scans its 32 candidates and stores the word, so short
@@ -489,8 +491,8 @@ __global__ __launch_bounds__(1024) void k_mid_wave(const int64_t *__restrict__ o
     int32_t *gt = reinterpret_cast<int32_t *>(gb + 64);
     unsigned long long found = 0;
     for (int64_t it = (int64_t)blockIdx.x * wpb + wv; it < nitems; it += (int64_t)gridDim.x * wpb) {
-        const int32_t v = item_v[it];
-        const int64_t first = item_first[it];
+        const int32_t v = item_v[nitems - 1 - it];
+        const int64_t first = item_first[nitems - 1 - it];
         const int64_t pend = min(first + (int64_t)item_pairs, tc_pairs_end(in_ptr, core, v));
         const int64_t vstart = orp[v];
         const int d = (int)(orp[v + 1] - vstart);
@@ -569,8 +571,8 @@ __global__ __launch_bounds__(256, 4) void k_mid_groups(const int64_t *__restrict
     int32_t *gt = reinterpret_cast<int32_t *>(gb + GL);
     unsigned long long found = 0;
     for (int64_t it = (int64_t)blockIdx.x * gpb + gi; it < nitems; it += (int64_t)gridDim.x * gpb) {
-        const int32_t v = item_v[it];
-        const int64_t first = item_first[it];
+        const int32_t v = item_v[nitems - 1 - it];
+        const int64_t first = item_first[nitems - 1 - it];
         const int64_t pend = min(first + (int64_t)item_pairs, tc_pairs_end(in_ptr, core, v));
         const int64_t vstart = orp[v];
         const int d = (int)(orp[v + 1] - vstart);
@@ -639,8 +641,8 @@ __global__ __launch_bounds__(1024) void k_mid_block(const int64_t *__restrict__ 
     int32_t *gt = reinterpret_cast<int32_t *>(gb + 64);
     unsigned long long found = 0;
     for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
-        const int32_t v = item_v[it];
-        const int64_t first = item_first[it];
+        const int32_t v = item_v[nitems - 1 - it];
+        const int64_t first = item_first[nitems - 1 - it];
         const int64_t pend = min(first + (int64_t)item_pairs, tc_pairs_end(in_ptr, core, v));
         const int64_t vstart = orp[v];
         const int d = (int)(orp[v + 1] - vstart);
@@ -721,8 +723,8 @@ __global__ __launch_bounds__(1024, 6) void k_mid_block16(
     const int lane = __lane_id();
     unsigned long long found = 0;
     for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
-        const int32_t v = item_v[it];
-        const int64_t first = item_first[it];
+        const int32_t v = item_v[nitems - 1 - it];
+        const int64_t first = item_first[nitems - 1 - it];
         const int64_t pend = min(first + (int64_t)item_pairs, tc_pairs_end(in_ptr, core, v));
         const int64_t vstart = orp[v];
         const int d = (int)(orp[v + 1] - vstart);
