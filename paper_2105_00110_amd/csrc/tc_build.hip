@@ -34,38 +34,73 @@ static inline unsigned grid_for(int64_t n, int block = BK) {
 #define GRID_STRIDE(i, n) \
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (n); i += (int64_t)gridDim.x * blockDim.x)
 
-// Pair -> packed canonical key.  For a batch, pair i belongs to the graph g
-// with pair_off[g] <= i < pair_off[g+1]; its ids are local and get the
-// graph's first global vertex id added.
-__global__ void k_make_keys(const int32_t *__restrict__ src, const int32_t *__restrict__ dst,
-                            int64_t P, int32_t n, int bits, const int64_t *__restrict__ pair_off,
-                            const int64_t *__restrict__ vtx_off, int32_t G,
-                            uint64_t *__restrict__ keys, uint32_t *__restrict__ err) {
-    const uint64_t sentinel = (bits >= 32) ? ~0ull : ((1ull << (2 * bits)) - 1);
-    GRID_STRIDE(i, P) {
-        int64_t a = src[i], b = dst[i];
+// The last index g in [lo, hi] with off[g] <= x.
+__device__ __forceinline__ int32_t last_at_or_below(const int64_t *__restrict__ off, int32_t lo,
+                                                    int32_t hi, int64_t x) {
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (off[mid] <= x) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
+// The graphs of a workgroup's first and last element (x0 <= x1), found once, so
+// that its elements search between them: a step or none, where each had searched
+// all graphs (1.8e7 pairs of 512 graphs: 126 us, 57 so with 8 pairs per thread).  Every thread calls.
+__device__ __forceinline__ void graph_range(const int64_t *__restrict__ off, int32_t G, int64_t x0,
+                                            int64_t x1, int32_t (&lds)[2], int32_t &lo, int32_t &hi) {
+    if (threadIdx.x == 0) lds[0] = last_at_or_below(off, 0, G - 1, x0);
+    if (threadIdx.x == TC_WAVE) lds[1] = last_at_or_below(off, 0, G - 1, x1);
+    __syncthreads();
+    lo = lds[0];
+    hi = lds[1];
+}
+
+// Pair -> packed canonical key (lower id << vbits | higher id).  For a batch, pair
+// i belongs to the graph g with pair_off[g] <= i < pair_off[g+1]; its ids are
+// local; the lower one gets the graph's first global vertex id added and the
+// higher one stays local, whose vbits are fewer.
+constexpr int64_t KEYS_MANY = (int64_t)1 << 20;  // from here on 8 pairs per thread
+
+template <int ITEMS>
+__global__ __launch_bounds__(BK) void k_make_keys(const int32_t *__restrict__ src,
+                                                  const int32_t *__restrict__ dst, int64_t P,
+                                                  int32_t n, int vbits, uint64_t sentinel,
+                                                  const int64_t *__restrict__ pair_off,
+                                                  const int64_t *__restrict__ vtx_off, int32_t G,
+                                                  uint64_t *__restrict__ keys,
+                                                  uint32_t *__restrict__ err) {
+    __shared__ int32_t range[2];
+    const int64_t i0 = (int64_t)blockIdx.x * (BK * ITEMS);
+    int32_t x[ITEMS], y[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t i = i0 + it * BK + threadIdx.x;
+        x[it] = i < P ? src[i] : 0;
+        y[it] = i < P ? dst[i] : 0;
+    }
+    int32_t g0 = 0, g1 = 0;
+    if (pair_off != nullptr)
+        graph_range(pair_off, G, i0, i0 + BK * ITEMS < P ? i0 + BK * ITEMS - 1 : P - 1, range, g0, g1);
+    bool bad = false;
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t i = i0 + it * BK + threadIdx.x;
+        if (i >= P) break;
         int64_t lim = n, base = 0;
         if (pair_off != nullptr) {
-            int32_t lo = 0, hi = G - 1;  // last g with pair_off[g] <= i
-            while (lo < hi) {
-                int32_t mid = (lo + hi + 1) >> 1;
-                if (pair_off[mid] <= i) lo = mid; else hi = mid - 1;
-            }
-            base = vtx_off[lo];
-            lim = vtx_off[lo + 1] - base;
+            const int32_t g = last_at_or_below(pair_off, g0, g1, i);
+            base = vtx_off[g];
+            lim = vtx_off[g + 1] - base;
         }
-        uint64_t key;
-        if (a < 0 || a >= lim || b < 0 || b >= lim) {
-            atomicOr(err, 1u);
-            key = sentinel;
-        } else if (a == b) {
-            key = sentinel;
-        } else {
-            uint64_t lo = (uint64_t)((a < b ? a : b) + base), hi = (uint64_t)((a < b ? b : a) + base);
-            key = (lo << bits) | hi;
-        }
+        const int64_t a = x[it], b = y[it];
+        uint64_t key = sentinel;
+        if (a < 0 || a >= lim || b < 0 || b >= lim) bad = true;
+        else if (a != b)
+            key = (uint64_t)((a < b ? a : b) + base) << vbits | (uint64_t)(a < b ? b : a);
         keys[i] = key;
     }
+    if (bad) atomicOr(err, 1u);
 }
 
 // Deduplication as a two-pass compaction over tiles of UQ_TILE sorted keys:
@@ -109,7 +144,9 @@ __global__ __launch_bounds__(UQ_BLOCK) void k_unique_count(const uint64_t *__res
 // come sorted by it).  us and ue start zeroed; the end of the last run is set
 // by k_last_run.
 __global__ __launch_bounds__(UQ_BLOCK) void k_unique_emit(const uint64_t *__restrict__ keys,
-                                                          int64_t P, uint64_t sentinel, int bits,
+                                                          int64_t P, uint64_t sentinel, int vbits,
+                                                          const int64_t *__restrict__ vtx_off,
+                                                          int32_t G,
                                                           const uint32_t *__restrict__ tile_off,
                                                           int32_t *__restrict__ eu,
                                                           int32_t *__restrict__ ev,
@@ -119,7 +156,9 @@ __global__ __launch_bounds__(UQ_BLOCK) void k_unique_emit(const uint64_t *__rest
     __shared__ int32_t su[UQ_TILE], sv[UQ_TILE];
     __shared__ uint32_t cnt[UQ_ITEMS * W];  // flags per (item, wavefront), then their prefix
     __shared__ uint32_t total;
-    const uint64_t mask = (1ull << bits) - 1;
+    __shared__ int32_t range[2];
+    static_assert(UQ_ITEMS * W == TC_WAVE, "a wavefront scans the counts");
+    const uint64_t mask = (1ull << vbits) - 1;
     const int64_t base = (int64_t)blockIdx.x * UQ_TILE;
     const int w = threadIdx.x / TC_WAVE;
     const int lane = __lane_id();
@@ -136,14 +175,16 @@ __global__ __launch_bounds__(UQ_BLOCK) void k_unique_emit(const uint64_t *__rest
         if (lane == 0) cnt[it * W + w] = (uint32_t)__popcll(fl[it]);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int q = 0; q < UQ_ITEMS * W; ++q) {
-            const uint32_t c = cnt[q];
-            cnt[q] = run;
-            run += c;
-        }
-        total = run;
+    if (w == 0) {
+        const uint32_t c = cnt[lane], incl = tc_wave_incl_scan(c);
+        cnt[lane] = incl - c;
+        if (lane == TC_WAVE - 1) total = incl;
+    }
+    int32_t g0 = 0, g1 = 0;
+    if (vtx_off != nullptr) {
+        const int64_t last = base + UQ_TILE < P ? base + UQ_TILE - 1 : P - 1;
+        graph_range(vtx_off, G, (int64_t)(keys[base] >> vbits), (int64_t)(keys[last] >> vbits), range,
+                    g0, g1);
     }
     __syncthreads();
     const uint32_t p0 = tile_off[blockIdx.x];
@@ -151,11 +192,13 @@ __global__ __launch_bounds__(UQ_BLOCK) void k_unique_emit(const uint64_t *__rest
     for (int it = 0; it < UQ_ITEMS; ++it) {
         if ((fl[it] >> lane) & 1ull) {
             const uint32_t lp = cnt[it * W + w] + (uint32_t)__popcll(fl[it] & lt);
-            const uint32_t u = (uint32_t)(k[it] >> bits), v = (uint32_t)(k[it] & mask);
+            const uint32_t u = (uint32_t)(k[it] >> vbits);
+            int64_t v = (int64_t)(k[it] & mask);
+            if (vtx_off != nullptr) v += vtx_off[last_at_or_below(vtx_off, g0, g1, u)];
             su[lp] = (int32_t)u;
             sv[lp] = (int32_t)v;
             // prev is the previous distinct key (sentinels sort last)
-            const uint32_t pu = (uint32_t)(prev[it] >> bits);
+            const uint32_t pu = (uint32_t)(prev[it] >> vbits);
             if (base + it * UQ_BLOCK + threadIdx.x == 0) {
                 us[u] = 0;
             } else if (pu != u) {
@@ -1027,7 +1070,20 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
                               const int32_t *simple_col) {
     const int32_t n = g->n;
     const int bits = g->bits;
-    const uint64_t sentinel = (bits >= 32) ? ~0ull : ((1ull << (2 * bits)) - 1);
+    // of a batch, the most vertices of a graph: the range of its local ids and
+    // degrees
+    int64_t most = n;
+    if (d_vtx_off) {
+        most = 1;
+        for (int32_t i = 0; i < num_graphs; ++i) {
+            const int64_t c = g->h_vtx_off[i + 1] - g->h_vtx_off[i];
+            most = c > most ? c : most;
+        }
+    }
+    // bits of a packed key's higher id (local in a batch: one pass less of the
+    // sort for 1.8e7 pairs of 512 graphs)
+    const int vbits = d_vtx_off ? tc_bits_for(most > 1 ? (uint64_t)(most - 1) : 1) : bits;
+    const uint64_t sentinel = bits + vbits >= 64 ? ~0ull : (1ull << (bits + vbits)) - 1;
     tc_scratch tmp(s);
 
     TC_TRY(tc_graph_alloc(g, &g->err, 4, s));
@@ -1076,10 +1132,15 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
         TC_TRY(tmp.get(&keys2, P));
         // an id out of range makes a sentinel key (dropped like a self
         // loop) and sets err, which is read back with the edge count
-        k_make_keys<<<grid_for(P), BK, 0, s>>>(d_src, d_dst, P, n, bits, d_pair_off, d_vtx_off,
-                                               num_graphs, keys, g->err);
+        if (P < KEYS_MANY)
+            k_make_keys<1><<<grid_for(P), BK, 0, s>>>(d_src, d_dst, P, n, vbits, sentinel, d_pair_off,
+                                                      d_vtx_off, num_graphs, keys, g->err);
+        else
+            k_make_keys<8><<<grid_for(tc_div_up(P, 8)), BK, 0, s>>>(d_src, d_dst, P, n, vbits, sentinel,
+                                                                   d_pair_off, d_vtx_off, num_graphs,
+                                                                   keys, g->err);
         TC_LAUNCHED();
-        TC_TRY(tc_sort_u64(&keys, &keys2, P, 2 * bits, s));
+        TC_TRY(tc_sort_u64(&keys, &keys2, P, bits + vbits, s));
         const int64_t tiles = tc_div_up(P, UQ_TILE);
         uint32_t *tcnt = nullptr, *d_m = nullptr;
         TC_TRY(tmp.get(&tcnt, tiles));
@@ -1094,8 +1155,8 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
         TC_TRY(tc_graph_alloc(g, &g->eu, m, s));
         TC_TRY(tc_graph_alloc(g, &g->ev, m, s));
         if (m > 0) {
-            k_unique_emit<<<(unsigned)tiles, UQ_BLOCK, 0, s>>>(keys, P, sentinel, bits, tcnt, g->eu,
-                                                               g->ev, us, ue);
+            k_unique_emit<<<(unsigned)tiles, UQ_BLOCK, 0, s>>>(keys, P, sentinel, vbits, d_vtx_off,
+                                                               num_graphs, tcnt, g->eu, g->ev, us, ue);
             TC_LAUNCHED();
             k_last_run<<<1, 64, 0, s>>>(m, g->eu, ue);
             TC_LAUNCHED();
@@ -1119,12 +1180,7 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
     // degree, which is below the vertices of its graph
     int dbits = bits;
     bool &by_graph = g->rank_by_graph;
-    if (num_graphs > 1 && g->h_vtx_off) {
-        int64_t most = 1;
-        for (int32_t i = 0; i < num_graphs; ++i) {
-            const int64_t c = g->h_vtx_off[i + 1] - g->h_vtx_off[i];
-            most = c > most ? c : most;
-        }
+    if (num_graphs > 1 && d_vtx_off) {
         dbits = tc_bits_for((uint64_t)most);
         by_graph = dbits + tc_bits_for((uint64_t)num_graphs) <= 32;
     }

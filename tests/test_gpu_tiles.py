@@ -208,6 +208,9 @@ def test_slot_merge_batch(tclib):
 BATCH_RANKS = {
     "uneven": [gg.ba(9000, 12, seed=1), gg.clique(9), (np.zeros(0, np.int32), np.zeros(0, np.int32), 0),
                gg.ba(700, 3, seed=2), gg.ba(20_000, 7, seed=3), gg.clique(2), gg.ba(60, 16, seed=4)],
+    # from 2^20 pairs on a thread takes eight, of workgroups that span many graphs
+    "many_pairs": [gg.ba(40_000, 16, seed=5), gg.clique(3), gg.ba(36_000, 15, seed=6)]
+                  + [gg.clique(2 + i % 11) for i in range(700)],
     "wide_keys": [(np.array([5, 5, 1 << 20], np.int32), np.array([1 << 20, 77, 77], np.int32),
                    (1 << 20) + 1)] + [gg.clique(3 + i % 7) for i in range(4095)],
 }
