@@ -462,7 +462,7 @@ tc_status tc_aggregate(tc_graph *g, hipStream_t s) {
     if (!g->num) TC_TRY(tc_graph_alloc(g, &g->num, nn, s));
     if (!g->tcv) TC_TRY(tc_graph_alloc(g, &g->tcv, nn, s));
     const int64_t *voff = G > 1 ? g->vtx_off : nullptr;
-    TC_HIP(hipMemsetAsync(g->triG, 0, sizeof(uint64_t) * G, s));
+    TC_TRY(tc_zero({{g->triG, 2 * (int64_t)G}}, s));
     if (n == 0) {
         tc_prof_mark(g, 10, s);
         tc_prof_mark(g, 11, s);
@@ -525,8 +525,8 @@ static tc_status aggregate_rank_space(tc_graph *g, hipStream_t s) {
     if (!g->num) TC_TRY(tc_graph_alloc(g, &g->num, nn, s));
     if (!g->tcv) TC_TRY(tc_graph_alloc(g, &g->tcv, nn, s));
     const int64_t *voff = G > 1 ? g->vtx_off : nullptr;
-    TC_HIP(hipMemsetAsync(g->triG, 0, sizeof(uint64_t) * G, s));
     if (n == 0) {
+        TC_TRY(tc_zero({{g->triG, 2 * (int64_t)G}}, s));
         tc_prof_mark(g, 10, s);
         tc_prof_mark(g, 11, s);
         return TC_OK;
@@ -545,7 +545,9 @@ static tc_status aggregate_rank_space(tc_graph *g, hipStream_t s) {
         TC_TRY(tmp.get(&chunks, 1));
         TC_TRY(tmp.get(&chunk, cap));
         TC_TRY(tmp.get(&part, cap));
-        TC_HIP(hipMemsetAsync(chunks, 0, 4, s));
+    }
+    TC_TRY(tc_zero({{g->triG, 2 * (int64_t)G}, {chunks, 1}}, s));
+    if (any_chunk) {
         k_rank_chunk_list<<<(unsigned)tc_div_up(n, RC_TILE), BK, 0, s>>>(n, g->orp, g->in_ptr, chunks,
                                                                         chunk);
         TC_LAUNCHED();

@@ -141,14 +141,13 @@ __global__ __launch_bounds__(UQ_BLOCK) void k_unique_count(const uint64_t *__res
 
 // Writes the canonical edges of each tile at tile_off[tile] and, in the same
 // pass, the run [us[u], ue[u]) of the edges whose smaller end is u (edges
-// come sorted by it).  us and ue start zeroed; the end of the last run is set
-// by k_last_run.
+// come sorted by it).  us and ue start zeroed.  m: all edges.
 __global__ __launch_bounds__(UQ_BLOCK) void k_unique_emit(const uint64_t *__restrict__ keys,
                                                           int64_t P, uint64_t sentinel, int vbits,
                                                           const int64_t *__restrict__ vtx_off,
                                                           int32_t G,
                                                           const uint32_t *__restrict__ tile_off,
-                                                          int32_t *__restrict__ eu,
+                                                          int64_t m, int32_t *__restrict__ eu,
                                                           int32_t *__restrict__ ev,
                                                           uint32_t *__restrict__ us,
                                                           uint32_t *__restrict__ ue) {
@@ -205,6 +204,7 @@ __global__ __launch_bounds__(UQ_BLOCK) void k_unique_emit(const uint64_t *__rest
                 us[u] = p0 + lp;
                 ue[pu] = p0 + lp;
             }
+            if (p0 + lp + 1 == m) ue[u] = (uint32_t)m;  // the last run
         }
     }
     __syncthreads();
@@ -350,10 +350,6 @@ __global__ __launch_bounds__(CT_BLOCK) void k_csr_upper(
             }
         }
     }
-}
-
-__global__ void k_last_run(int64_t m, const int32_t *__restrict__ eu, uint32_t *__restrict__ ue) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) ue[eu[m - 1]] = (uint32_t)m;
 }
 
 // Run boundaries of a sorted id sequence: start/end of each present id.
@@ -999,8 +995,7 @@ tc_status tc_orient(tc_graph *g, hipStream_t s) {
     TC_TRY(tmp.get(&info, INFO));
     TC_TRY(tmp.get(&list_mid, nn));
     TC_TRY(tmp.get(&list_big, nn));
-    TC_HIP(hipMemsetAsync(info, 0, INFO * sizeof(uint32_t), s));
-    TC_HIP(hipMemsetAsync(cursor, 0, sizeof(uint32_t) * nn, s));
+    TC_TRY(tc_zero({{info, INFO}, {cursor, nn}}, s));
     // pass A: buckets of the lower-ordered endpoints
     {
         uint32_t *rank_u = nullptr;
@@ -1087,17 +1082,17 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
     tc_scratch tmp(s);
 
     TC_TRY(tc_graph_alloc(g, &g->err, 4, s));
-    TC_HIP(hipMemsetAsync(g->err, 0, 16, s));
 
     // runs of the edges by smaller end, filled while the canonical edges are
-    // written
+    // written, and by larger end
     int64_t nn = n > 0 ? n : 1;
-    uint32_t *ue = nullptr;
+    uint32_t *ue = nullptr, *ls = nullptr, *le = nullptr;
     TC_TRY(tc_graph_alloc(g, &g->run_us, nn, s));
     uint32_t *us = g->run_us;
     TC_TRY(tmp.get(&ue, nn));
-    TC_HIP(hipMemsetAsync(us, 0, sizeof(uint32_t) * nn, s));
-    TC_HIP(hipMemsetAsync(ue, 0, sizeof(uint32_t) * nn, s));
+    TC_TRY(tmp.get(&ls, nn));
+    TC_TRY(tmp.get(&le, nn));
+    TC_TRY(tc_zero({{g->err, 4}, {us, nn}, {ue, nn}, {ls, nn}, {le, nn}}, s));
 
     // -- 1. canonical edges ---------------------------------------------------
     int64_t m = 0;
@@ -1156,9 +1151,8 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
         TC_TRY(tc_graph_alloc(g, &g->ev, m, s));
         if (m > 0) {
             k_unique_emit<<<(unsigned)tiles, UQ_BLOCK, 0, s>>>(keys, P, sentinel, vbits, d_vtx_off,
-                                                               num_graphs, tcnt, g->eu, g->ev, us, ue);
-            TC_LAUNCHED();
-            k_last_run<<<1, 64, 0, s>>>(m, g->eu, ue);
+                                                               num_graphs, tcnt, m, g->eu, g->ev, us,
+                                                               ue);
             TC_LAUNCHED();
         }
     } else {
@@ -1173,7 +1167,7 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
     TC_TRY(tc_graph_alloc(g, &g->row_ptr, (int64_t)n + 1, s));
     // the canonical edges ordered by their larger end (kept for the
     // orientation), whose runs count the edges by larger end
-    uint32_t *key = nullptr, *ls = nullptr, *le = nullptr;
+    uint32_t *key = nullptr;
     int64_t *deg64 = nullptr;
     TC_TRY(tmp.get(&key, nn));
     // the rank order's key: (graph, degree) where 32 bits hold both, else the
@@ -1186,10 +1180,6 @@ tc_status tc_build_from_pairs(tc_graph *g, const int32_t *d_src, const int32_t *
     }
     const int key_bits = by_graph ? dbits + tc_bits_for((uint64_t)num_graphs) : dbits;
     TC_TRY(tmp.get(&deg64, nn));
-    TC_TRY(tmp.get(&ls, nn));
-    TC_TRY(tmp.get(&le, nn));
-    TC_HIP(hipMemsetAsync(ls, 0, sizeof(uint32_t) * nn, s));
-    TC_HIP(hipMemsetAsync(le, 0, sizeof(uint32_t) * nn, s));
     if (m > 0) {
         uint32_t *lk2 = nullptr, *lv2 = nullptr;
         TC_TRY(tc_graph_alloc(g, &g->lt_key, m, s));
@@ -1265,9 +1255,7 @@ static tc_status orient_sorted(tc_graph *g, hipStream_t s) {
     TC_TRY(tmp.get(&re, nn));
     TC_TRY(tmp.get(&dplus, nn));
     TC_TRY(tmp.get(&d_max, 1));
-    TC_HIP(hipMemsetAsync(rs, 0, sizeof(uint32_t) * nn, s));
-    TC_HIP(hipMemsetAsync(re, 0, sizeof(uint32_t) * nn, s));
-    TC_HIP(hipMemsetAsync(d_max, 0, sizeof(uint32_t), s));
+    TC_TRY(tc_zero({{rs, nn}, {re, nn}, {d_max, 1}}, s));
     k_runs<<<grid_for(m), BK, 0, s>>>(GetHigh{okey, bits}, m, rs, re);
     TC_LAUNCHED();
     k_run_len64<<<grid_for(n), BK, 0, s>>>(n, rs, re, dplus, d_max);
@@ -1302,8 +1290,7 @@ tc_status tc_ensure_symmetric(tc_graph *g, hipStream_t s) {
     }
     TC_TRY(tmp.get(&ls, nn));
     TC_TRY(tmp.get(&le, nn));
-    TC_HIP(hipMemsetAsync(ls, 0, sizeof(uint32_t) * nn, s));
-    TC_HIP(hipMemsetAsync(le, 0, sizeof(uint32_t) * nn, s));
+    TC_TRY(tc_zero({{ls, nn}, {le, nn}}, s));
     k_runs<<<grid_for(m), BK, 0, s>>>(GetU32{tkey}, m, ls, le);
     TC_LAUNCHED();
     k_fill_lower<<<grid_for(m), BK, 0, s>>>(m, tkey, tval, ls, g->row_ptr, g->eu, g->col, g->sym2e);

@@ -301,7 +301,7 @@ tc_status tc_core_count(const tc_graph *g, int32_t N, const uint4 *mat, unsigned
     tc_scratch tmp(s);
     unsigned long long *sum = nullptr;
     TC_TRY(tmp.get(&sum, 1));
-    TC_HIP(hipMemsetAsync(sum, 0, sizeof(*sum), s));
+    TC_TRY(tc_zero({{sum, 2}}, s));
     const int64_t T = N / CT, ntiles = T * (T + 1) / 2;
     k_core_count<<<(unsigned)((ntiles + 7) / 8 * 8), CBLOCK, 0, s>>>(
         g->n - N, N, ntiles, reinterpret_cast<const v4i *>(mat), g->orp, g->ocol, g->osup, sum);

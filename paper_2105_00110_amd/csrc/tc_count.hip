@@ -352,8 +352,7 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
         for (int k = 6; k <= 9; ++k) tc_prof_mark(g, k, s);
         return TC_OK;
     }
-    TC_HIP(hipMemsetAsync(g->osup, 0, sizeof(uint32_t) * (m > 0 ? m : 1), s));
-    TC_HIP(hipMemsetAsync(found, 0, sizeof(uint64_t), s));
+    TC_TRY(tc_zero({{g->osup, m > 0 ? m : 1}, {found, 2}}, s));
     if (m == 0 || g->max_dplus < 2) {
         g->light_max = t.light_max_dplus;
         g->huge_min = 0x7FFFFFFF;
@@ -398,7 +397,7 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     TC_TRY(tmp.get(&heavy, any_heavy ? g->n : 1));
     TC_TRY(tmp.get(&huge, any_huge ? g->n : 1));
     TC_TRY(tmp.get(&cnt, 3));
-    TC_HIP(hipMemsetAsync(cnt, 0, 12, s));
+    TC_TRY(tc_zero({{cnt, 3}}, s));
     k_bin_rows<<<(unsigned)tc_div_up(g->n, BR_TILE), BK, 0, s>>>(g->n, g->orp, light_max, huge_min,
                                                                 rows, heavy, huge, cnt);
     TC_LAUNCHED();

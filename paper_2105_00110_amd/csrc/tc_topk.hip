@@ -173,7 +173,7 @@ tc_status tc_topk_select(const double *tcv, int32_t n, int32_t k, int32_t *h_ver
     uint32_t *count = hist + 2 * BINS;
     double *d_vals = reinterpret_cast<double *>(out);
     int32_t *d_verts = reinterpret_cast<int32_t *>(d_vals + k);
-    TC_HIP(hipMemsetAsync(hist, 0, sizeof(uint32_t) * (2 * BINS + 1), s));
+    TC_TRY(tc_zero({{hist, 2 * BINS + 1}}, s));
     // four keys per thread, at most two workgroups per CU
     const int64_t want = tc_div_up(n, 4 * HB);
     const unsigned grid = (unsigned)(want < 512 ? want : 512);
