@@ -143,11 +143,11 @@ COUNTER_KERNELS = [
     ("__amd_rocclr_copyBuffer", None, "copy_calibration"),
 ]
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
-COUNTER_REGEX = "k_mid_block|k_mid_wave|k_mid_groups|k_fold|copyBuffer|k_place_by|k_orient_small|" \
+COUNTER_REGEX = "k_mid_block|k_mid_wave|k_mid_groups|k_core|k_fold|copyBuffer|k_place_by|k_orient_small|" \
                 "k_orient_mid|k_unique_emit|k_rank_rows|k_rank_chunks"
 COUNTER_ARGS = "--steps 1 --warmup 0 --no-batched --no-serve --no-er --no-ingest " \
                "--no-cpu-baseline --copy-calibration 1"
-COUNT_SOURCES = ["tc_count.hip", "tc_count_mid.hip", "tc_table.h", "tc_internal.h"]
+COUNT_SOURCES = ["tc_count.hip", "tc_count_mid.hip", "tc_core.hip", "tc_table.h", "tc_internal.h"]
 
 
 def _short_kernel(name):

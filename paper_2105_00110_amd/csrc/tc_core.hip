@@ -267,10 +267,11 @@ __global__ void k_core_found(const unsigned long long *__restrict__ sum,
 
 // The size that saves most.  Measured on R-MAT graphs, in ps: the scan and the
 // fold take 1.0 (scale 20) to 0.6 (scale 24) per wedge whose lowest end is in
-// the core; the products 0.00025 N^3 (3.9 PFLOP/s at N = 16384: 1.12 ms) with
-// about 40 us more for the launches, the searches and the tiles' ends, and the
-// matrix 0.55 N^2 (144 us at 16384).  At scale 20 a core of 6144 takes 173 us
-// and saves 441 of 2640 us, one of 16384 takes 1259 us and saves 800.
+// the core; the products 0.00025 N^3 (3.9 PFLOP/s at N = 16384: 1.12 ms; 1.28
+// in scale 24's denser core) with about 40 us more for the launches, the
+// searches and the tiles' ends, and the matrix 0.55 N^2 (144 us at 16384).  At
+// scale 20 a core of 6144 takes 173 us and saves 441 of 2640 us, one of 16384
+// takes 1259 us and saves 800.
 int32_t tc_core_size(const tc_graph *g) {
     int32_t best = 0;
     double gain = 2e7;

@@ -1339,11 +1339,12 @@ __global__ void k_row_words_total(int32_t n, const int64_t *__restrict__ orp,
     if (__lane_id() == 0 && acc) atomicAdd(total, acc);
 }
 
-// Work per bin for the statistics: scan lengths of every pair, binned by
-// the pivot's |N_H| (those of the core included, which no scan reads).
+// Work per bin for the statistics: scan lengths of every pair that the last
+// count scanned (those of its core, from rank r0 on, it did not), binned by the
+// pivot's |N_H|.
 __global__ void k_mid_stats(int64_t m, const int64_t *__restrict__ orp,
                             const int32_t *__restrict__ ocol, const uint64_t *__restrict__ in_pair,
-                            int light_max, int huge_min, int32_t r16,
+                            int light_max, int huge_min, int32_t r16, int32_t r0,
                             unsigned long long *__restrict__ acc) {
     // cand per bin, pairs per bin, heavy cand and pairs of pivots among the
     // top 2^16 ranks
@@ -1355,7 +1356,7 @@ __global__ void k_mid_stats(int64_t m, const int64_t *__restrict__ orp,
         const int32_t v = ocol[k];
         const int64_t d = orp[v + 1] - orp[v];
         const int64_t len = orp[u + 1] - (int64_t)k - 1;
-        if (d < 1) continue;
+        if (d < 1 || u >= r0) continue;
         const int bin = d <= light_max ? 0 : (d < huge_min ? 1 : 2);
         sums[bin] += (unsigned long long)len;
         sums[3 + bin] += 1ull;
@@ -1514,6 +1515,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
             core_n = 0;
         }
     }
+    g->core_n = core_n;
     // workgroup pivots whose rank span fits the LDS bitmap use it; the
     // others hash (or, above huge_min, search device memory).  Wavefront
     // pivots with at least light_bitmap_pairs pairs and a span that fits go
@@ -1708,7 +1710,7 @@ tc_status tc_mid_stats(tc_graph *g, unsigned long long *acc, hipStream_t s) {
     // a bounded grid: each wavefront adds its sums to the same few words
     const unsigned sg = grid_for(g->m) < 4096u ? grid_for(g->m) : 4096u;
     k_mid_stats<<<sg, BK, 0, s>>>(g->m, g->orp, g->ocol, g->in_pair, light_max,
-                                             huge_min, r16, acc);
+                                             huge_min, r16, g->n - g->core_n, acc);
     TC_LAUNCHED();
     const unsigned pg = grid_for(g->n) < 4096u ? grid_for(g->n) : 4096u;
     k_mid_pivots<<<pg, BK, 0, s>>>(g->n, g->orp, g->in_ptr, light_max, huge_min, r16, acc);

@@ -232,6 +232,7 @@ struct tc_graph {
     // oriented wedges of the rows of the tc_core_ranks(j) highest ranks, the
     // sizes of the core that tc_core.hip takes
     unsigned long long core_wedges[TC_CORE_SIZES] = {};
+    int32_t core_n = 0;  // the last count's core
     uint32_t *err = nullptr;  // device words: error bits, largest degree, 2 unused
 
     size_t bytes = 0;  // device bytes held

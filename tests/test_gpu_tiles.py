@@ -356,7 +356,11 @@ def test_core_products(tclib, name):
     g.compute({"algorithm": tclib.TC_ALGO_LOW_PIVOT})
     a = g.results()
     g.compute()
-    assert g.work_stats()["algorithm"] == tclib.TC_ALGO_MID_PIVOT
+    ws = g.work_stats()
+    assert ws["algorithm"] == tclib.TC_ALGO_MID_PIVOT
+    # the candidates scanned: all oriented wedges but the core's
+    scanned = ws["cand_light"] + ws["cand_heavy"] + ws["cand_huge"]
+    assert scanned == 0 if name == "whole" else scanned <= ws["wedges"]
     b = g.results()
     for k in ("tri", "support", "triG", "num"):
         np.testing.assert_array_equal(a[k], b[k])
