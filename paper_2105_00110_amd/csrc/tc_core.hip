@@ -297,11 +297,8 @@ tc_status tc_core_fill(const tc_graph *g, int32_t N, int64_t *end, uint4 *mat, h
     return TC_OK;
 }
 
-tc_status tc_core_count(const tc_graph *g, int32_t N, const uint4 *mat, unsigned long long *found,
-                        hipStream_t s) {
-    tc_scratch tmp(s);
-    unsigned long long *sum = nullptr;
-    TC_TRY(tmp.get(&sum, 1));
+tc_status tc_core_count(const tc_graph *g, int32_t N, const uint4 *mat, unsigned long long *sum,
+                        unsigned long long *found, hipStream_t s) {
     TC_TRY(tc_zero({{sum, 2}}, s));
     const int64_t T = N / CT, ntiles = T * (T + 1) / 2;
     k_core_count<<<(unsigned)((ntiles + 7) / 8 * 8), CBLOCK, 0, s>>>(

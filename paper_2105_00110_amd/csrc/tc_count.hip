@@ -371,7 +371,7 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     // AUTO, above the slot merge: the middle pivot streams fewer candidates
     // (the oriented wedges), but its transposition, work items and fold cost a
     // fixed number of launches and a host round trip.
-    const int algo = choose_algo(g, t);
+    int algo = choose_algo(g, t);
     g->algo_used = algo;
     if (use_slots(g, t)) {
         g->slots_used = true;
@@ -382,7 +382,13 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
         for (int k = 6; k <= 9; ++k) tc_prof_mark(g, k, s);
         return TC_OK;
     }
-    if (algo == TC_ALGO_MID_PIVOT) return tc_count_mid(g, t, lds_limit, max_entries, found, s);
+    if (algo == TC_ALGO_MID_PIVOT) {
+        const tc_status st = tc_count_mid(g, t, lds_limit, max_entries, found, s);
+        if (!tc_no_memory(st) || t.algorithm != TC_ALGO_AUTO || g->m >= TC_LOW_FITS_EDGES) return st;
+        // its bit matrices do not fit: the low pivot does without
+        tc_mid_release(g, s);
+        g->algo_used = algo = TC_ALGO_LOW_PIVOT;
+    }
     const int light_max = t.light_max_dplus;
     // heavy rows: light_max < d+ < huge_min (table at most half full); the
     // three bins must not overlap, whatever the knobs

@@ -1398,10 +1398,10 @@ __global__ void k_mid_pivots(int32_t n, const int64_t *__restrict__ orp,
 }  // namespace
 
 // Builds in_ptr / in_pair (the transposed orientation) once per handle.
-tc_status tc_mid_prepare(tc_graph *g, hipStream_t s) {
+tc_status tc_mid_prepare(tc_graph *g, hipStream_t s, bool keep_order) {
     // the order by larger id is not needed from here on (the symmetric
     // fill sorts again if it is ever asked for)
-    tc_release_transposition(g, s);
+    if (!keep_order) tc_release_transposition(g, s);
     if (g->in_pair) return TC_OK;
     const int32_t n = g->n;
     const int64_t m = g->m;
@@ -1465,10 +1465,10 @@ static tc_status bit_rows_alloc(tc_graph *g, int64_t words, hipStream_t s) {
     // 4 words of padding: the fold's row sums read up to 3 words past a
     // row's end
     if (!g->hitbits) TC_TRY(tc_graph_alloc(g, &g->hitbits, words + 4, s));
+    g->bit_words = words;
     TC_TRY(tc_graph_alloc(g, &g->rowinfo, g->n, s));
     k_row_info<<<grid_for(g->n), BK, 0, s>>>(g->n, g->orp, g->rowbase, g->rowinfo);
     TC_LAUNCHED();
-    g->bit_words = words;
     return TC_OK;
 }
 
@@ -1486,9 +1486,26 @@ static tc_status ocol16_prepare(tc_graph *g, hipStream_t s) {
     return TC_OK;
 }
 
-tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
-                       unsigned long long *found, hipStream_t s) {
-    TC_TRY(tc_mid_prepare(g, s));
+void tc_mid_release(tc_graph *g, hipStream_t s) {
+    const auto drop = [&](auto *&p, int64_t count) {
+        if (!p) return;
+        tc_dev_free(p, s);
+        p = nullptr;
+        g->bytes -= (size_t)(count > 0 ? count : 1) * sizeof(*p);
+    };
+    drop(g->in_ptr, (int64_t)(g->n > 0 ? g->n : 1) + 1);
+    drop(g->in_pair, g->m);
+    drop(g->rowbase, (int64_t)g->n + 1);
+    drop(g->hitbits, g->bit_words + 4);
+    drop(g->rowinfo, g->n);
+    drop(g->ocol16, (g->m + TC_OCOL_PAD + 1) & ~(int64_t)1);
+    g->bit_words = 0;
+}
+
+static tc_status count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
+                           bool use_core, unsigned long long *found, hipStream_t s) {
+    g->core_n = 0;
+    TC_TRY(tc_mid_prepare(g, s, t.algorithm == TC_ALGO_AUTO && g->m < TC_LOW_FITS_EDGES));
     TC_TRY(ocol16_prepare(g, s));
     const int light_max = t.light_max_dplus;
     int huge_min = max_entries / 2 + 1;
@@ -1503,19 +1520,17 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
     // the triangles inside the core come from matrix products
     tc_core core;
     uint4 *core_mat = nullptr;
-    int32_t core_n = tc_core_size(g);
+    unsigned long long *core_sum = nullptr;
+    const int32_t core_n = use_core ? tc_core_size(g) : 0;
+    g->core_n = core_n;
     if (core_n > 0) {
         int64_t *end = nullptr;
         TC_TRY(items.get(&end, core_n));
-        // no memory for the matrix: the scan takes every pair
-        if (items.get(&core_mat, (int64_t)core_n * core_n / 32) == TC_OK) {
-            TC_TRY(tc_core_fill(g, core_n, end, core_mat, s));
-            core = {g->n - core_n, end};
-        } else {
-            core_n = 0;
-        }
+        TC_TRY(items.get(&core_sum, 1));
+        TC_TRY(items.get(&core_mat, (int64_t)core_n * core_n / 32));
+        TC_TRY(tc_core_fill(g, core_n, end, core_mat, s));
+        core = {g->n - core_n, end};
     }
-    g->core_n = core_n;
     // workgroup pivots whose rank span fits the LDS bitmap use it; the
     // others hash (or, above huge_min, search device memory).  Wavefront
     // pivots with at least light_bitmap_pairs pairs and a span that fits go
@@ -1567,6 +1582,7 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
     TC_TRY(items.get(&item_v, n_items));
     TC_TRY(items.get(&item_first, n_items));
     TC_TRY(items.get(&fold_rows, n_rows));
+    tc_release_transposition(g, s);  // everything is there
     k_plan_write<<<(unsigned)plan_tiles, BK, 0, s>>>(rules, g->n, flags, g->in_ptr, core, tile_cnt, item_v,
                                                      item_first, fold_rows);
     TC_LAUNCHED();
@@ -1697,9 +1713,18 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
             }
         }
     }
-    if (core_n > 0) TC_TRY(tc_core_count(g, core_n, core_mat, found, s));
+    if (core_n > 0) TC_TRY(tc_core_count(g, core_n, core_mat, core_sum, found, s));
     tc_prof_mark(g, 9, s);
     return TC_OK;
+}
+
+tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
+                       unsigned long long *found, hipStream_t s) {
+    const tc_status st = count_mid(g, t, lds_limit, max_entries, true, found, s);
+    // no memory beside the core's matrix: the scan takes every pair
+    if (tc_no_memory(st) && g->core_n > 0)
+        return count_mid(g, t, lds_limit, max_entries, false, found, s);
+    return st;
 }
 
 tc_status tc_mid_stats(tc_graph *g, unsigned long long *acc, hipStream_t s) {

@@ -281,16 +281,26 @@ constexpr int32_t TOPK_SELECT_MAX = 1024;
 tc_status tc_topk_select(const double *tcv, int32_t n, int32_t k, int32_t *h_verts, double *h_vals,
                          bool *found, hipStream_t s);
 tc_status tc_work_stats(tc_graph *g, int64_t *stats, hipStream_t s);
-tc_status tc_mid_prepare(tc_graph *g, hipStream_t s);
+tc_status tc_mid_prepare(tc_graph *g, hipStream_t s, bool keep_order = false);
+// Takes all its memory before it counts: after TC_ERR_BUDGET or TC_ERR_OOM
+// g->osup and *found are as they were.
 tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
                        unsigned long long *found, hipStream_t s);
+// Below this many edges AUTO counts with the low pivot where a memory limit
+// leaves no room for the middle pivot's arrays (a dense graph's bit matrices take
+// several times the low pivot's), so the order by larger end, which it needs, is
+// kept until they are all there; a larger graph gets the limit's error.
+constexpr int64_t TC_LOW_FITS_EDGES = 600000;
+// Frees what the middle pivot keeps on the handle.
+void tc_mid_release(tc_graph *g, hipStream_t s);
+static inline bool tc_no_memory(tc_status st) { return st == TC_ERR_BUDGET || st == TC_ERR_OOM; }
 // tc_core.hip: the core's size for this graph (0: none); its matrix
 // (N * N / 32 words of 16 bytes) and the ends of its pairs; its products added
-// to g->osup and its triangles to *found.
+// to g->osup and its triangles to *found (sum: a scratch word).
 int32_t tc_core_size(const tc_graph *g);
 tc_status tc_core_fill(const tc_graph *g, int32_t N, int64_t *end, uint4 *mat, hipStream_t s);
-tc_status tc_core_count(const tc_graph *g, int32_t N, const uint4 *mat, unsigned long long *found,
-                        hipStream_t s);
+tc_status tc_core_count(const tc_graph *g, int32_t N, const uint4 *mat, unsigned long long *sum,
+                        unsigned long long *found, hipStream_t s);
 // One small graph by one workgroup (tc_single.hip): everything that
 // tc_build_from_pairs and tc_orient leave but the order by larger ends (made
 // again where a consumer needs it), and everything that tc_count and

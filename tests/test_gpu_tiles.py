@@ -410,3 +410,38 @@ def test_mid_pivot_items(tclib):
     g.close()
     for k, want in (("support", ref.sup), ("tri", ref.tri), ("num", ref.num)):
         np.testing.assert_array_equal(r[k], want)
+
+
+# a limit between what the low and the middle pivot take: AUTO does without the
+# core's matrix, then without the middle pivot, before it gives the limit's error
+@pytest.mark.parametrize("name", ["whole", "clique_900"])
+def test_counts_under_a_limit(tclib, name):
+    src, dst, n = CORE_GRAPHS["whole"]() if name == "whole" else gg.clique(900)
+    ref = native.o2_paper(src, dst, n)
+    done = {"low": [], "auto": []}
+    try:
+        for part in range(2, 22, 2):
+            for algo in done:
+                tclib.tc_set_memory_limit(0)
+                g = tclib.Graph.from_edges(src, dst, n)
+                room = g.compute_bytes() * part // 20
+                tclib.tc_trim_memory()
+                tclib.tc_set_memory_limit(tclib.tc_memory_stats()["in_use"] + room)
+                _say("counts under a limit", name, algo, part)
+                try:
+                    g.compute({"algorithm": tclib.TC_ALGO_LOW_PIVOT} if algo == "low" else None)
+                    done[algo].append(part)
+                except tclib.TCError as e:
+                    assert e.status == tclib.TC_ERR_BUDGET
+                tclib.tc_set_memory_limit(0)
+                if done[algo] and done[algo][-1] == part:
+                    r = g.results()
+                    np.testing.assert_array_equal(r["support"], ref.sup)
+                    np.testing.assert_array_equal(r["num"], ref.num)
+                g.close()
+    finally:
+        tclib.tc_set_memory_limit(0)
+        tclib.tc_trim_memory()
+    assert 20 in done["auto"] and 20 in done["low"], done
+    if ref.m < 600_000:  # there, whatever the low pivot fits into is enough
+        assert set(done["low"]) <= set(done["auto"]), done
