@@ -355,7 +355,6 @@ __device__ __forceinline__ void fused_small(const FusedArgs &a, const GraphRef q
     }
     if (wg_any(bad)) {
         fused_fail<BLOCK>(a, q.g, q.va, n, TC_ERR_VERTEX_RANGE);
-        __syncthreads();
         return;
     }
     Edges E;
@@ -393,7 +392,6 @@ __device__ __forceinline__ void fused_small(const FusedArgs &a, const GraphRef q
         if (a.triG) a.triG[q.g] = tg;
         a.status[q.g] = odd ? TC_ERR_DEVICE : (tg == 0 ? TC_TRIANGLE_FREE : TC_OK);
     }
-    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -577,7 +575,6 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
     }
     if (wg_any(bad)) {
         fused_fail<BLOCK>(a, q.g, q.va, n, TC_ERR_VERTEX_RANGE);
-        __syncthreads();
         return;
     }
     uint32_t *k = q.A, *kt = q.B;
@@ -879,7 +876,6 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
         if (a.triG) a.triG[q.g] = tg;
         a.status[q.g] = odd ? TC_ERR_DEVICE : (tg == 0 ? TC_TRIANGLE_FREE : TC_OK);
     }
-    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -912,7 +908,6 @@ __device__ __forceinline__ void fused_large(const FusedArgs &a, const GraphRef q
     }
     if (wg_any(bad)) {
         fused_fail<BLOCK>(a, g, va, n, TC_ERR_VERTEX_RANGE);
-        __syncthreads();
         return;
     }
     // canonical edges
@@ -1110,10 +1105,9 @@ __device__ __forceinline__ void fused_large(const FusedArgs &a, const GraphRef q
         if (a.triG) a.triG[g] = tg;
         a.status[g] = odd ? TC_ERR_DEVICE : (tg == 0 ? TC_TRIANGLE_FREE : TC_OK);
     }
-    __syncthreads();
 }
 
-
+// The caller has the barrier before the next graph.
 template <int BLOCK>
 __device__ __forceinline__ void fused_one_graph(const FusedArgs &a, int32_t g, FusedArena<BLOCK> &sh) {
     const int tid = threadIdx.x;
@@ -1178,11 +1172,16 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_fused_graphs(Fu
         // the same value in every lane: keep it (and what derives from it) in
         // scalar registers
         const uint32_t slot = __builtin_amdgcn_readfirstlane(next);
-        __syncthreads();
         if (slot >= (uint32_t)a.G) break;
         const int32_t g = a.order ? __builtin_amdgcn_readfirstlane(a.order[slot]) : (int32_t)slot;
-        if (g < 0 || g >= a.G) continue;  // not a permutation: skip the entry
-        fused_one_graph<BLOCK>(a, g, sh);
+        // not a permutation: skip the entry
+        if (g >= 0 && g < a.G) fused_one_graph<BLOCK>(a, g, sh);
+        // Every way through the loop ends at this barrier.  A refused graph ends
+        // with thread 0's stores, and with nothing between them and the fetch
+        // above the compiler joins the two tests of threadIdx.x == 0: the other
+        // lanes then go round a loop of their own, in which thread 0 never
+        // fetches again, and the launch does not end.
+        __syncthreads();
     }
 }
 

@@ -136,10 +136,6 @@ def test_fused_random_tiny_graphs(tclib):
     check_all(fb, res, graphs)
 
 
-@pytest.mark.skip(reason="this batch did not finish on the GPU (stopped after 180 s without output); "
-                         "the cause is not found: a CPU emulation of the kernel on the same batch "
-                         "(one thread per lane, AddressSanitizer, uninitialised workspace) gives "
-                         "the oracle's results, so it stays off the GPU until a cause is shown")
 def test_fused_degenerate_and_invalid_graphs(tclib):
     e0 = np.zeros(0, np.int32)
     big_n = 65535
@@ -175,6 +171,22 @@ def test_fused_degenerate_and_invalid_graphs(tclib):
         assert not one["tri"].any() and not one["num"].any() and not one["tc"].any()
     assert fb.graph(res, 0)["status"] == tclib.TC_TRIANGLE_FREE
     assert fb.graph(res, 3)["status"] == tclib.TC_TRIANGLE_FREE
+
+
+def test_fused_offsets_outside_the_arrays(tclib):
+    # graphs 1 and 2 have pair offsets past the end, or decreasing: a status, and
+    # the graphs after them are computed
+    src, dst, po, vo = concat([gg.clique(3), gg.clique(3), gg.clique(3), gg.clique(5)])
+    po[2] = 9999
+    _say("fused offsets outside the arrays")
+    fb = tclib.FusedBatch(torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda(), po, vo)
+    fb.run()
+    torch.cuda.synchronize()
+    res = fb.results()
+    assert list(res["status"][1:3]) == [tclib.TC_ERR_INVALID_ARG] * 2
+    assert not res["num_edges"][1:3].any()
+    for g, k in ((0, 3), (3, 5)):
+        check_graph(fb.graph(res, g), native.o2_paper(*gg.clique(k), nthreads=1))
 
 
 def test_fused_ba_batch_4096_every_graph(tclib):
