@@ -1406,10 +1406,11 @@ tc_status tc_mid_prepare(tc_graph *g, hipStream_t s, bool keep_order) {
     const int32_t n = g->n;
     const int64_t m = g->m;
     const int64_t nn = n > 0 ? n : 1;
-    TC_TRY(tc_graph_alloc(g, &g->in_ptr, nn + 1, s));
-    TC_TRY(tc_graph_alloc(g, &g->in_pair, m, s));
     tc_scratch tmp(s);
-    int64_t *len = nullptr;
+    int64_t *len = nullptr, *ptr = nullptr;
+    uint64_t *val = nullptr;
+    TC_TRY(tmp.get(&ptr, nn + 1));
+    TC_TRY(tmp.get(&val, m));
     TC_TRY(tmp.get(&len, nn));
     if (m > 0) {
         // (row << 32 | slot) of every slot, in order of the pivot (stable:
@@ -1419,21 +1420,18 @@ tc_status tc_mid_prepare(tc_graph *g, hipStream_t s, bool keep_order) {
         TC_TRY(tmp.get(&key, m));
         TC_TRY(tmp.get(&key2, m));
         TC_TRY(tmp.get(&val2, m));
-        uint64_t *val = g->in_pair;
         TC_TRY(tc_sort_u32_index_hi((const uint32_t *)g->ocol, (const uint32_t *)g->orow, &key, &val,
                                     &key2, &val2, m, g->bits, s));
-        if (val != g->in_pair) {  // the result is in the scratch buffer: swap ownership
-            tmp.exchange(val, g->in_pair);
-            g->in_pair = val;
-        }
     }
     if (n > 0) {
         k_in_len<<<grid_for(n), BK, 0, s>>>(n, g->perm, g->row_ptr, g->orp, len);
         TC_LAUNCHED();
-        TC_TRY(tc_scan_i64(len, g->in_ptr, n, g->in_ptr + n, s));
+        TC_TRY(tc_scan_i64(len, ptr, n, ptr + n, s));
     } else {
-        TC_HIP(hipMemsetAsync(g->in_ptr, 0, sizeof(int64_t), s));
+        TC_HIP(hipMemsetAsync(ptr, 0, sizeof(int64_t), s));
     }
+    tc_graph_take(g, &g->in_ptr, ptr, nn + 1, tmp);
+    tc_graph_take(g, &g->in_pair, val, m, tmp);
     return TC_OK;
 }
 
@@ -1452,12 +1450,14 @@ __global__ void k_row_info(int32_t n, const int64_t *__restrict__ orp,
 static tc_status bit_rows_scan(tc_graph *g, hipStream_t s) {
     const int32_t n = g->n;
     tc_scratch tmp(s);
-    int64_t *len = nullptr;
+    int64_t *len = nullptr, *base = nullptr;
     TC_TRY(tmp.get(&len, n));
-    TC_TRY(tc_graph_alloc(g, &g->rowbase, (int64_t)n + 1, s));
+    TC_TRY(tmp.get(&base, (int64_t)n + 1));
     k_row_words<<<grid_for(n), BK, 0, s>>>(n, g->orp, len);
     TC_LAUNCHED();
-    return tc_scan_i64(len, g->rowbase, n, g->rowbase + n, s);
+    TC_TRY(tc_scan_i64(len, base, n, base + n, s));
+    tc_graph_take(g, &g->rowbase, base, (int64_t)n + 1, tmp);
+    return TC_OK;
 }
 
 // The matrices themselves and the per-row records, with the total known.

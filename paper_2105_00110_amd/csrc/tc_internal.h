@@ -335,6 +335,16 @@ tc_status tc_graph_alloc(tc_graph *g, T **p, int64_t count, hipStream_t s) {
     return st;
 }
 
+// The handle takes p, count entries allocated in tmp, as *slot.  For arrays that
+// are made once per handle: only when nothing can fail before they are filled, as
+// a later call takes an array that is there as filled.
+template <typename T>
+void tc_graph_take(tc_graph *g, T **slot, T *p, int64_t count, tc_scratch &tmp) {
+    tmp.exchange(p, nullptr);
+    *slot = p;
+    g->bytes += (size_t)(count > 0 ? count : 1) * sizeof(T);
+}
+
 // ---------------------------------------------------------------------------
 // Device-side helpers
 // ---------------------------------------------------------------------------

@@ -1,0 +1,76 @@
+"""GPU: a compute that runs out of memory, at each of its allocations in turn,
+leaves the handle usable: the next compute on it, without the limit, gives the
+oracle's results.
+
+The limit is narrowed down to every place where one more block is had (the
+allocator's blocks are multiples of 512 bytes), told apart by the peak of
+the bytes in use and by the bytes that the handle holds after the failure."""
+import numpy as np
+import pytest
+
+from oracle import native
+from paper_2105_00110_amd import graphgen as gg
+from tests.test_gpu_tiles import _dense_core
+
+pytestmark = pytest.mark.gpu
+
+STEP = 512
+# above 16384 vertices the scans take scratch of their own
+FORMS = {
+    "mid": (lambda: gg.ba(20_000, 4, seed=11), {"algorithm": 2}),
+    # beside the core's matrix the later arrays are what does not fit
+    "mid_core": (lambda: _dense_core(20_000, 2048, 0.35, 12, 20_000), {"algorithm": 2}),
+}
+
+
+@pytest.mark.parametrize("name", sorted(FORMS))
+def test_compute_again_after_each_failed_allocation(tclib, name):
+    graph, tuning = FORMS[name]
+    src, dst, n = graph()
+    ref = native.o2_paper(src, dst, n)
+
+    def probe(steps):
+        """Computes with room for steps * STEP bytes; how far it got."""
+        tclib.tc_set_memory_limit(0)
+        g = tclib.Graph.from_edges(src, dst, n)
+        tclib.tc_trim_memory()
+        before = tclib.tc_memory_stats(reset_peaks=True)["in_use"]
+        tclib.tc_set_memory_limit(before + steps * STEP)
+        failed = False
+        try:
+            g.compute(tuning)
+        except tclib.TCError as e:
+            assert e.status == tclib.TC_ERR_BUDGET
+            failed = True
+        tclib.tc_set_memory_limit(0)
+        got = (failed, tclib.tc_memory_stats()["peak_in_use"] - before, g.device_bytes())
+        if failed:
+            g.compute(tuning)
+        r = g.results()
+        np.testing.assert_array_equal(r["support"], ref.sup)
+        np.testing.assert_array_equal(r["num"], ref.num)
+        g.close()
+        return got
+
+    try:
+        g = tclib.Graph.from_edges(src, dst, n)
+        hi = g.compute_bytes(tuning) // STEP + 1
+        g.close()
+        ends = {0: probe(0), hi: probe(hi)}
+        assert ends[0][0] and not ends[hi][0]
+        todo, places = [(0, hi)], 0
+        while todo:
+            a, b = todo.pop()
+            if ends[a] == ends[b]:
+                continue
+            if b == a + 1:
+                places += 1
+                print("[case] memory limits", name, "place", places, "at", b * STEP, ends[b], flush=True)
+                continue
+            m = (a + b) // 2
+            ends[m] = probe(m)
+            todo += [(a, m), (m, b)]
+        assert places >= 8, places
+    finally:
+        tclib.tc_set_memory_limit(0)
+        tclib.tc_trim_memory()
