@@ -1270,13 +1270,22 @@ tc_status tc_ensure_symmetric(tc_graph *g, hipStream_t s) {
     const int32_t n = g->n;
     const int64_t m = g->m;
     const int64_t nn = n > 0 ? n : 1;
-    TC_TRY(tc_graph_alloc(g, &g->col, 2 * m, s));
-    TC_TRY(tc_graph_alloc(g, &g->sym2e, 2 * m, s));
-    if (m == 0) return TC_OK;
+    tc_scratch tmp(s);
+    int32_t *col = nullptr;
+    uint32_t *sym2e = nullptr;
+    TC_TRY(tmp.get(&col, 2 * m));
+    TC_TRY(tmp.get(&sym2e, 2 * m));
+    const auto take = [&] {
+        tc_graph_take(g, &g->col, col, 2 * m, tmp);
+        tc_graph_take(g, &g->sym2e, sym2e, 2 * m, tmp);
+    };
+    if (m == 0) {
+        take();
+        return TC_OK;
+    }
     // the transposition: canonical edges sorted by their larger end (kept
     // from the build unless the middle-pivot count released it), and the
     // run of every vertex in that order
-    tc_scratch tmp(s);
     uint32_t *tkey = g->lt_key, *tval = g->lt_val;
     uint32_t *ls = nullptr, *le = nullptr;
     if (!tkey) {
@@ -1293,11 +1302,11 @@ tc_status tc_ensure_symmetric(tc_graph *g, hipStream_t s) {
     TC_TRY(tc_zero({{ls, nn}, {le, nn}}, s));
     k_runs<<<grid_for(m), BK, 0, s>>>(GetU32{tkey}, m, ls, le);
     TC_LAUNCHED();
-    k_fill_lower<<<grid_for(m), BK, 0, s>>>(m, tkey, tval, ls, g->row_ptr, g->eu, g->col, g->sym2e);
+    k_fill_lower<<<grid_for(m), BK, 0, s>>>(m, tkey, tval, ls, g->row_ptr, g->eu, col, sym2e);
     TC_LAUNCHED();
-    k_fill_upper<<<grid_for(m), BK, 0, s>>>(m, g->eu, g->ev, g->run_us, ls, le, g->row_ptr, g->col,
-                                            g->sym2e);
+    k_fill_upper<<<grid_for(m), BK, 0, s>>>(m, g->eu, g->ev, g->run_us, ls, le, g->row_ptr, col, sym2e);
     TC_LAUNCHED();
+    take();
     tc_release_transposition(g, s);
     return TC_OK;
 }

@@ -20,6 +20,10 @@ FORMS = {
     "mid": (lambda: gg.ba(20_000, 4, seed=11), {"algorithm": 2}),
     # beside the core's matrix the later arrays are what does not fit
     "mid_core": (lambda: _dense_core(20_000, 2048, 0.35, 12, 20_000), {"algorithm": 2}),
+    # the symmetric adjacency that the low pivot aggregates over; as one small
+    # graph by one workgroup it sorts for it
+    "low": (lambda: gg.ba(20_000, 4, seed=11), {"algorithm": 1}),
+    "low_small": (lambda: gg.clique(170), {"algorithm": 1}),
 }
 
 
