@@ -355,7 +355,10 @@ tc_status tc_graph_device_bytes(const tc_graph *g, int64_t *bytes);
  * as tc_compute does).  For the middle pivot it includes the exact size of
  * the bit matrices of §3.3's Procedure 1, 4·Σ_v Σ_{t<d+(v)} ceil(t/32)
  * bytes over the oriented rows (about Σ_v C(d+(v), 2) / 8), which it reads
- * back from the device: the call waits for the stream.  A caller with a
+ * back from the device: the call waits for the stream.  Of a graph with
+ * fewer than 600000 edges (3000000 where no oriented row has 32 entries)
+ * TC_ALGO_AUTO asks for the low pivot's bytes only: it takes another form
+ * there where that stays within them.  A caller with a
  * memory budget checks it after the build, before the count, so that a
  * dense graph whose bit matrices outgrow tc_estimate_device_bytes cannot
  * overrun the budget.  *bytes is a host pointer.  TC_ERR_INVALID_ARG for a

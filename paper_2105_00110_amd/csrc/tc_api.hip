@@ -101,12 +101,6 @@ struct Pending {
 thread_local Pending t_pending;
 std::vector<Pending *> g_pending;  // those with blocks
 
-size_t round_size(size_t b) {
-    if (b < ((size_t)1 << 20)) return (b + 511) & ~(size_t)511;
-    const size_t g = (size_t)2 << 20;
-    return (b + g - 1) / g * g;
-}
-
 void unref(Fence *f, int dev) {
     if (f && --f->refs == 0) g_fences[dev].push_back(f);
 }
@@ -184,12 +178,19 @@ tc_call_scope::~tc_call_scope() {
     p.listed = false;
 }
 
+size_t tc_block_size(size_t b) {
+    if (b == 0) b = 1;
+    if (b < ((size_t)1 << 20)) return (b + 511) & ~(size_t)511;
+    const size_t g = (size_t)2 << 20;
+    return (b + g - 1) / g * g;
+}
+
 tc_status tc_dev_alloc(void **p, size_t bytes, hipStream_t s) {
     int dev = 0;
     TC_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= MAX_DEV) return TC_ERR_DEVICE;
     *p = nullptr;
-    const size_t size = round_size(bytes > 0 ? bytes : 1);
+    const size_t size = tc_block_size(bytes);
     std::lock_guard<std::mutex> lk(g_alloc_mu);
     auto &fl = g_free[dev];
     auto it = fl.lower_bound(size);

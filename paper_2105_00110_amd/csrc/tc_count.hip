@@ -296,39 +296,49 @@ static bool use_slots(const tc_graph *g, const tc_tuning &t) {
     return t.algorithm == TC_ALGO_AUTO && g->max_dplus <= TC_SLOTS_MAX_DPLUS;
 }
 
+// The low pivot's bound (the slot merge's too): what both forms need, flags,
+// symmetric adjacency with its slot map, temporaries of the bins and the
+// aggregation.
+static int64_t common_bytes(const tc_graph *g) {
+    // support per oriented slot and per edge, tri, num, tc, triG
+    return 8 * g->m + 24 * (int64_t)(g->n > 0 ? g->n : 1) + 8 * ((int64_t)g->num_graphs + 1);
+}
+// The caching allocator rounds each block up: by under 512 bytes below 1 MiB, by
+// under 2 MiB above; at most 64 blocks, each above 1 MiB taking at least 1 MiB of b.
+static int64_t with_rounding(int64_t b) {
+    const int64_t big = (b >> 20) < 64 ? (b >> 20) : 64;
+    return b + 64 * 512 + big * ((int64_t)2 << 20);
+}
+static int64_t low_bytes(const tc_graph *g) {
+    return with_rounding(common_bytes(g) + 34 * g->m + 40 * (int64_t)(g->n > 0 ? g->n : 1));
+}
+
 // The pivot form AUTO (or the tuning) takes for this graph.
 static int choose_algo(const tc_graph *g, const tc_tuning &t) {
     if (t.algorithm != TC_ALGO_AUTO) return t.algorithm;
-    if (use_slots(g, t)) return TC_ALGO_LOW_PIVOT;
-    return g->m >= AUTO_MID_MIN_EDGES ? TC_ALGO_MID_PIVOT : TC_ALGO_LOW_PIVOT;
+    if (use_slots(g, t) || g->m < AUTO_MID_MIN_EDGES) return TC_ALGO_LOW_PIVOT;
+    if (tc_low_bytes_promised(g) && tc_mid_most_bytes(g) > low_bytes(g)) return TC_ALGO_LOW_PIVOT;
+    return TC_ALGO_MID_PIVOT;
 }
 
 tc_status tc_count_bytes(tc_graph *g, const tc_tuning *tin, hipStream_t s, int64_t *bytes) {
     tc_tuning t;
     if (tin) t = *tin; else tc_tuning_default(&t);
     if (!tuning_valid(&t)) return TC_ERR_INVALID_ARG;
-    const int64_t m = g->m, nn = g->n > 0 ? g->n : 1, G = g->num_graphs;
-    // both forms: support per oriented slot and per edge, tri, num, tc, triG
-    int64_t b = 8 * m + 24 * nn + 8 * (G + 1);
-    if (m > 0 && g->max_dplus >= 2 && choose_algo(g, t) == TC_ALGO_MID_PIVOT) {
-        int64_t words = 0;
-        TC_TRY(tc_mid_bit_words(g, &words, s));
-        // transposition (pair lists and offsets), bit matrices with their
-        // row records and offsets, the 16-bit columns; temporaries of the
-        // transposition sort, work-item lists, support reordering and
-        // aggregation, all counted at once
-        b += 8 * m + 8 * (nn + 1) + 4 * (words + 4) + 16 * nn + 8 * (nn + 1) + 2 * (m + 66) +
-             30 * m + 96 * nn;
-    } else {
-        // flags, symmetric adjacency with its slot map; temporaries of the
-        // bins and the aggregation
-        b += 2 * m + 16 * m + 16 * m + 40 * nn;
+    const int64_t m = g->m, nn = g->n > 0 ? g->n : 1;
+    const bool promised = t.algorithm == TC_ALGO_AUTO && tc_low_bytes_promised(g);
+    if (m == 0 || g->max_dplus < 2 || promised || choose_algo(g, t) == TC_ALGO_LOW_PIVOT) {
+        *bytes = low_bytes(g);
+        return TC_OK;
     }
-    // the caching allocator rounds each block up: by under 512 bytes below
-    // 1 MiB, by under 2 MiB above; at most 64 blocks, each above 1 MiB
-    // taking at least 1 MiB of b
-    const int64_t big = (b >> 20) < 64 ? (b >> 20) : 64;
-    *bytes = b + 64 * 512 + big * ((int64_t)2 << 20);
+    int64_t words = 0;
+    TC_TRY(tc_mid_bit_words(g, &words, s));
+    // transposition (pair lists and offsets), bit matrices with their row
+    // records and offsets, the 16-bit columns; temporaries of the
+    // transposition sort, work-item lists, support reordering and
+    // aggregation, all counted at once
+    *bytes = with_rounding(common_bytes(g) + 8 * m + 8 * (nn + 1) + 4 * (words + 4) + 16 * nn +
+                           8 * (nn + 1) + 2 * (m + 66) + 30 * m + 96 * nn);
     return TC_OK;
 }
 
@@ -384,7 +394,7 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     }
     if (algo == TC_ALGO_MID_PIVOT) {
         const tc_status st = tc_count_mid(g, t, lds_limit, max_entries, found, s);
-        if (!tc_no_memory(st) || t.algorithm != TC_ALGO_AUTO || g->m >= TC_LOW_FITS_EDGES) return st;
+        if (!tc_no_memory(st) || t.algorithm != TC_ALGO_AUTO || !tc_low_bytes_promised(g)) return st;
         // its bit matrices do not fit: the low pivot does without
         tc_mid_release(g, s);
         g->algo_used = algo = TC_ALGO_LOW_PIVOT;

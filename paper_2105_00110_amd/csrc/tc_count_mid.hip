@@ -1505,7 +1505,7 @@ void tc_mid_release(tc_graph *g, hipStream_t s) {
 static tc_status count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
                            bool use_core, unsigned long long *found, hipStream_t s) {
     g->core_n = 0;
-    TC_TRY(tc_mid_prepare(g, s, t.algorithm == TC_ALGO_AUTO && g->m < TC_LOW_FITS_EDGES));
+    TC_TRY(tc_mid_prepare(g, s, t.algorithm == TC_ALGO_AUTO && tc_low_bytes_promised(g)));
     TC_TRY(ocol16_prepare(g, s));
     const int light_max = t.light_max_dplus;
     int huge_min = max_entries / 2 + 1;
@@ -1725,6 +1725,51 @@ tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_e
     if (tc_no_memory(st) && g->core_n > 0)
         return count_mid(g, t, lds_limit, max_entries, false, found, s);
     return st;
+}
+
+int64_t tc_mid_most_bytes(const tc_graph *g) {
+    const int64_t n = g->n, m = g->m;
+    int64_t all = 0;
+    const auto add = [&](int64_t bytes) { all += (int64_t)tc_block_size((size_t)bytes); };
+    const auto scan = [&](int64_t len) { add(8 * tc_div_up(len, 4096)); };
+    // results: osup, esup, triG, tri, num, tc
+    for (int i = 0; i < 2; ++i) add(4 * m);
+    add(8 * ((int64_t)g->num_graphs + 1));
+    for (int i = 0; i < 3; ++i) add(8 * n);
+    // tc_mid_prepare: offsets, pairs, the sort's other buffers and tile counts
+    for (int i = 0; i < 2; ++i) add(8 * (n + 1));
+    for (int i = 0; i < 2; ++i) add(8 * m);
+    for (int i = 0; i < 2; ++i) add(4 * m);
+    add(1024 * (tc_div_up(m, 2048) + 1));
+    scan(n);
+    add(2 * (m + TC_OCOL_PAD + 1));
+    // count_mid: the core, the lists (every pivot has one item and one more per
+    // GROUP_PAIRS_FEW pairs at most), the bit matrices with their offsets
+    if (const int64_t N = tc_core_size(g)) {
+        add(8 * N);
+        add(8);
+        add(N * N / 2);
+    }
+    const int64_t cnts = NLISTS * tc_div_up(n, PLAN_TILE) + 1, items = n + m / GROUP_PAIRS_FEW;
+    add(8 * cnts);
+    scan(cnts);
+    add(n);
+    for (int i = 0; i < 2; ++i) add(8 * (n + 1));
+    scan(n);
+    // a row of d entries has at most C(d, 2) / 32 + d words
+    const int64_t wedges = n <= tc_core_ranks(TC_CORE_SIZES - 1)
+                               ? (int64_t)g->core_wedges[TC_CORE_SIZES - 1]
+                               : m * (g->max_dplus - 1) / 2;
+    add(4 * (wedges / 32 + m + 4));
+    add(16 * n);
+    for (int i = 0; i < 2; ++i) add(4 * items);
+    add(4 * n);
+    // the aggregation by rank (and, of many edges, the supports' grouping)
+    add(4 * m);
+    add(8 * n);
+    add(4);
+    for (int i = 0; i < 2; ++i) add(8 * (2 * m / 2048 + 2 * m / 257 + 1));
+    return all;
 }
 
 tc_status tc_mid_stats(tc_graph *g, unsigned long long *acc, hipStream_t s) {

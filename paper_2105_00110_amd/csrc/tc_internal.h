@@ -48,6 +48,8 @@ static inline int tc_bits_for(uint64_t max_value) {
 // device bytes the library holds past it fails with TC_ERR_BUDGET.
 // ---------------------------------------------------------------------------
 tc_status tc_dev_alloc(void **p, size_t bytes, hipStream_t s);
+// the size of the block that holds bytes
+size_t tc_block_size(size_t bytes);
 // idle: no work that uses the block is pending on any stream
 void tc_dev_free(void *p, hipStream_t s, bool idle = false);
 
@@ -286,11 +288,17 @@ tc_status tc_mid_prepare(tc_graph *g, hipStream_t s, bool keep_order = false);
 // g->osup and *found are as they were.
 tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
                        unsigned long long *found, hipStream_t s);
-// Below this many edges AUTO counts with the low pivot where a memory limit
-// leaves no room for the middle pivot's arrays (a dense graph's bit matrices take
-// several times the low pivot's), so the order by larger end, which it needs, is
-// kept until they are all there; a larger graph gets the limit's error.
-constexpr int64_t TC_LOW_FITS_EDGES = 600000;
+// Graphs for which tc_compute_bytes promises that AUTO stays within the low
+// pivot's bound.  AUTO still takes the middle pivot there where all its arrays fit
+// into that bound (tc_mid_most_bytes); and where a memory limit leaves no room for
+// them it counts with the low pivot, so the order by larger end, which that needs,
+// is kept until they are all there.  A larger graph gets the limit's error.
+static inline bool tc_low_bytes_promised(const tc_graph *g) {
+    return g->m < 600000 || (g->m < 3000000 && g->max_dplus < 32);
+}
+// The bytes of every block that AUTO's middle pivot and its aggregation allocate,
+// as if none were used twice, up to a bound of the bit matrices' size.
+int64_t tc_mid_most_bytes(const tc_graph *g);
 // Frees what the middle pivot keeps on the handle.
 void tc_mid_release(tc_graph *g, hipStream_t s);
 static inline bool tc_no_memory(tc_status st) { return st == TC_ERR_BUDGET || st == TC_ERR_OOM; }

@@ -78,3 +78,35 @@ def test_compute_again_after_each_failed_allocation(tclib, name):
     finally:
         tclib.tc_set_memory_limit(0)
         tclib.tc_trim_memory()
+
+
+# between 200 and 600 thousand edges AUTO may take the middle pivot; what
+# tc_compute_bytes asks for there stays the low pivot's bound, and holds: with the
+# cache emptied after the build, every block of the count is new
+PROMISED = {
+    "clique_660": lambda: gg.clique(660),
+    "clique_1090": lambda: gg.clique(1090),
+    "core": lambda: _dense_core(2048, 2048, 0.28, 13, 0),
+    "flat_rows": lambda: gg.ba(3000, 150, seed=1),
+    "rmat_15": lambda: gg.rmat(15, 16, seed=1),
+    "rmat_16": lambda: gg.rmat(16, 8, seed=1),
+}
+
+
+@pytest.mark.parametrize("name", sorted(PROMISED))
+def test_compute_bytes_of_mid_sized_graphs(tclib, name):
+    src, dst, n = PROMISED[name]()
+    g = tclib.Graph.from_edges(src, dst, n)
+    assert 200_000 <= g.m < 600_000
+    tclib.tc_trim_memory()
+    need = g.compute_bytes()
+    assert need == g.compute_bytes({"algorithm": tclib.TC_ALGO_LOW_PIVOT})
+    before = tclib.tc_memory_stats(reset_peaks=True)["held"]
+    g.compute()
+    grown = tclib.tc_memory_stats()["peak_held"] - before
+    ws = g.work_stats()
+    print("[case] compute bytes", name, "edges", g.m, "longest row", ws["max_dplus"], "algorithm",
+          ws["algorithm"], "bound", need, "growth", grown, flush=True)
+    assert ws["algorithm"] == tclib.TC_ALGO_MID_PIVOT
+    assert grown <= need
+    g.close()
