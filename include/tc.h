@@ -107,7 +107,9 @@ const char *tc_status_string(int32_t status);
  *                    TC_ALGO_AUTO (0) merges the sorted rows of the low
  *                    and the middle vertex (the appendix's Procedure 2,
  *                    reported as the low pivot) while every oriented row
- *                    has at most 128 entries.  Above, it picks the middle
+ *                    has at most 128 entries and, from 200000 edges on, an
+ *                    edge has few triangles (about eight, by a sample of the
+ *                    build).  Else it picks the middle
  *                    pivot, whose streamed work is the number of oriented
  *                    wedges, for graphs of 200000 edges or more, and the
  *                    low pivot for smaller ones (fewer launches and host

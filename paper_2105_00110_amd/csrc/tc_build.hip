@@ -600,15 +600,60 @@ __device__ __forceinline__ void core_wedges(int32_t n, int64_t base, const uint3
 constexpr int SEG_MID = 1024;  // k_orient_mid's longest bucket
 constexpr int DL_TILE = 2048;
 
+// How many triangles an edge has, from TC_SAMPLES edges: each takes another edge
+// of its bucket at random and looks up whether the two close.  The workgroups of
+// the sample follow those of the lists in one launch and end before them.
+struct SampleArgs {
+    unsigned first;  // their first workgroup
+    int64_t m;
+    const int32_t *eu, *ev, *rank;
+    const int64_t *row_ptr;
+    const uint64_t *tbuf;
+    const uint32_t *run_us;
+    unsigned long long *sum;  // twice the triangles that the sampled edges see
+};
+
+__device__ void sample_triangles(const SampleArgs &a, const uint32_t *__restrict__ cursor) {
+    const uint32_t s = (blockIdx.x - a.first) * BK + threadIdx.x;
+    const int64_t e = a.m * s / TC_SAMPLES;
+    const int32_t u = a.eu[e], v = a.ev[e];
+    const int32_t x = a.rank[u] < a.rank[v] ? u : v, w = u ^ v ^ x;
+    const uint32_t d = cursor[x];
+    unsigned long long got = 0;
+    if (d >= 2) {
+        const int64_t b = a.row_ptr[x];
+        uint32_t t = (uint32_t)((uint64_t)(s * 2654435761u) * d >> 32);
+        uint32_t e2 = (uint32_t)a.tbuf[b + t];
+        if (e2 == (uint32_t)e) e2 = (uint32_t)a.tbuf[b + (t + 1 < d ? t + 1 : 0)];
+        const int32_t z = a.eu[e2] ^ a.ev[e2] ^ x;
+        // the canonical edge of w and z, if there is one: in the run of the smaller
+        const int32_t lo = w < z ? w : z, hi = w < z ? z : w;
+        int64_t i = a.run_us[lo], j = i + (a.row_ptr[lo + 1] - a.row_ptr[lo]);
+        j = j < a.m ? j : a.m;
+        while (i < j) {
+            const int64_t mid = (i + j) >> 1;
+            if (a.eu[mid] < lo || (a.eu[mid] == lo && a.ev[mid] < hi)) i = mid + 1; else j = mid;
+        }
+        if (i < a.m && a.eu[i] == lo && a.ev[i] == hi) got = d - 1;
+    }
+    got = tc_wave_sum(got);
+    if (__lane_id() == 0 && got) atomicAdd(a.sum, got);
+}
+
 __global__ __launch_bounds__(BK) void k_dplus_lists(int32_t n, const uint32_t *__restrict__ cursor,
                                                     const int32_t *__restrict__ perm,
                                                     int64_t *__restrict__ dplus,
                                                     int32_t *__restrict__ list_mid,
                                                     int32_t *__restrict__ list_big,
                                                     uint32_t *__restrict__ info,
-                                                    unsigned long long *__restrict__ wedges) {
+                                                    unsigned long long *__restrict__ wedges,
+                                                    SampleArgs sample) {
     constexpr int PER = DL_TILE / BK;
     __shared__ uint32_t lds[BK / TC_WAVE + 1];
+    if (blockIdx.x >= sample.first) {
+        sample_triangles(sample, cursor);
+        return;
+    }
     const int64_t base = (int64_t)blockIdx.x * DL_TILE;
     uint32_t d[PER], mx = 0, nmid = 0, nbig = 0;
     int32_t x[PER];
@@ -990,8 +1035,9 @@ tc_status tc_orient(tc_graph *g, hipStream_t s) {
     TC_TRY(tmp.get(&cursor, nn));
     TC_TRY(tmp.get(&tbuf, 2 * m));
     TC_TRY(tmp.get(&dplus, nn));
-    // max d+, mid-list count, big-list count; wedges of the cores (64-bit)
-    constexpr int INFO = 4 + 2 * TC_CORE_SIZES;
+    // max d+, mid-list count, big-list count; wedges of the cores and the sampled
+    // triangles (64-bit)
+    constexpr int INFO = 4 + 2 * (TC_CORE_SIZES + 1);
     TC_TRY(tmp.get(&info, INFO));
     TC_TRY(tmp.get(&list_mid, nn));
     TC_TRY(tmp.get(&list_big, nn));
@@ -1009,15 +1055,21 @@ tc_status tc_orient(tc_graph *g, hipStream_t s) {
     }
     // with the largest d+ and the lists, whose counts one read-back brings
     unsigned long long *wedges = reinterpret_cast<unsigned long long *>(info + 4);
-    k_dplus_lists<<<(unsigned)tc_div_up(n, DL_TILE), BK, 0, s>>>(n, cursor, g->perm, dplus, list_mid,
-                                                                list_big, info, wedges);
+    const unsigned tiles = (unsigned)tc_div_up(n, DL_TILE);
+    const unsigned more = m >= TC_SAMPLE_MIN_EDGES ? TC_SAMPLES / BK : 0;
+    const SampleArgs sample{tiles, m, g->eu, g->ev, g->rank, g->row_ptr, tbuf, g->run_us, wedges + TC_CORE_SIZES};
+    k_dplus_lists<<<tiles + more, BK, 0, s>>>(n, cursor, g->perm, dplus, list_mid, list_big, info, wedges,
+                                              sample);
     TC_LAUNCHED();
     uint32_t h_info[4] = {0, 0, 0, 0};
+    unsigned long long h_wedges[TC_CORE_SIZES + 1] = {};
     TC_TRY(tc_read({{h_info, info, 3},
                     {&g->max_degree, g->err + 1, 1},
-                    {g->core_wedges, wedges, 2 * TC_CORE_SIZES}},
+                    {h_wedges, wedges, 2 * (TC_CORE_SIZES + 1)}},
                    s));
-    for (int j = 1; j < TC_CORE_SIZES; ++j) g->core_wedges[j] += g->core_wedges[j - 1];
+    unsigned long long sum = 0;
+    for (int j = 0; j < TC_CORE_SIZES; ++j) g->core_wedges[j] = sum += h_wedges[j];
+    g->tri_per_edge = (double)h_wedges[TC_CORE_SIZES] / (2.0 * TC_SAMPLES);
     const uint32_t h_max = h_info[0];
     const int64_t nmid = h_info[1], nblk = h_info[2];
     g->max_dplus = (int32_t)h_max;

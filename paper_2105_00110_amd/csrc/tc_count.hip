@@ -290,11 +290,8 @@ static bool tuning_valid(const tc_tuning *t) {
            t->light_bitmap_pairs >= 0;
 }
 
-// AUTO merges slots (tc_slots.hip, a low-pivot form without tables) where every
-// oriented row is short.
-static bool use_slots(const tc_graph *g, const tc_tuning &t) {
-    return t.algorithm == TC_ALGO_AUTO && g->max_dplus <= TC_SLOTS_MAX_DPLUS;
-}
+// The forms that AUTO chooses between.
+enum class Form { SLOTS, LOW, MID };
 
 // The low pivot's bound (the slot merge's too): what both forms need, flags,
 // symmetric adjacency with its slot map, temporaries of the bins and the
@@ -313,12 +310,27 @@ static int64_t low_bytes(const tc_graph *g) {
     return with_rounding(common_bytes(g) + 34 * g->m + 40 * (int64_t)(g->n > 0 ? g->n : 1));
 }
 
-// The pivot form AUTO (or the tuning) takes for this graph.
-static int choose_algo(const tc_graph *g, const tc_tuning &t) {
-    if (t.algorithm != TC_ALGO_AUTO) return t.algorithm;
-    if (use_slots(g, t) || g->m < AUTO_MID_MIN_EDGES) return TC_ALGO_LOW_PIVOT;
-    if (tc_low_bytes_promised(g) && tc_mid_most_bytes(g) > low_bytes(g)) return TC_ALGO_LOW_PIVOT;
-    return TC_ALGO_MID_PIVOT;
+// Where rows are short enough for the slot merge: whether its hits, an atomic add
+// to a row of another workgroup each, cost more than the middle pivot.  Device time
+// in ns per edge, merge and middle pivot, by triangles per edge: 0.6 0.06 / 0.30;
+// 5.8 0.35 / 0.37; 7.2 0.30 / 0.36; 10 (R-MAT scale 12, 256 times) 0.45 / 0.31; 19
+// (K_60) 0.83 / 0.31; 33 (K_100) 1.34 / 0.45; that is about 0.06 + 0.038 t against
+// 0.34, and the middle pivot's launches take 70 us more.
+static bool merge_hits_dear(const tc_graph *g) {
+    return (double)g->m * (0.038 * g->tri_per_edge - 0.28) > 70e3;
+}
+
+// The form that AUTO (or the tuning) takes for this graph.
+static Form choose_form(const tc_graph *g, const tc_tuning &t) {
+    if (t.algorithm != TC_ALGO_AUTO)
+        return t.algorithm == TC_ALGO_MID_PIVOT ? Form::MID : Form::LOW;
+    // the slot merge (tc_slots.hip, a low-pivot form without tables) where every
+    // oriented row is short
+    const bool short_rows = g->max_dplus <= TC_SLOTS_MAX_DPLUS;
+    const Form few = short_rows ? Form::SLOTS : Form::LOW;
+    if (g->m < AUTO_MID_MIN_EDGES || (short_rows && !merge_hits_dear(g))) return few;
+    if (tc_low_bytes_promised(g) && tc_mid_most_bytes(g) > low_bytes(g)) return few;
+    return Form::MID;
 }
 
 tc_status tc_count_bytes(tc_graph *g, const tc_tuning *tin, hipStream_t s, int64_t *bytes) {
@@ -327,7 +339,7 @@ tc_status tc_count_bytes(tc_graph *g, const tc_tuning *tin, hipStream_t s, int64
     if (!tuning_valid(&t)) return TC_ERR_INVALID_ARG;
     const int64_t m = g->m, nn = g->n > 0 ? g->n : 1;
     const bool promised = t.algorithm == TC_ALGO_AUTO && tc_low_bytes_promised(g);
-    if (m == 0 || g->max_dplus < 2 || promised || choose_algo(g, t) == TC_ALGO_LOW_PIVOT) {
+    if (m == 0 || g->max_dplus < 2 || promised || choose_form(g, t) != Form::MID) {
         *bytes = low_bytes(g);
         return TC_OK;
     }
@@ -352,7 +364,8 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     if (!g->triG) TC_TRY(tc_graph_alloc(g, &g->triG, g->num_graphs + 1, s));
     // triG[num_graphs] is the scratch total of triangles found by the count
     unsigned long long *found = (unsigned long long *)(g->triG + g->num_graphs);
-    if (g->single && m > 0 && use_slots(g, t)) {  // one launch, aggregation included
+    Form form = choose_form(g, t);
+    if (g->single && m > 0 && form == Form::SLOTS) {  // one launch, aggregation included
         g->algo_used = TC_ALGO_LOW_PIVOT;
         g->slots_used = true;
         g->light_max = t.light_max_dplus;
@@ -381,9 +394,19 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     // AUTO, above the slot merge: the middle pivot streams fewer candidates
     // (the oriented wedges), but its transposition, work items and fold cost a
     // fixed number of launches and a host round trip.
-    int algo = choose_algo(g, t);
-    g->algo_used = algo;
-    if (use_slots(g, t)) {
+    g->algo_used = form == Form::MID ? TC_ALGO_MID_PIVOT : TC_ALGO_LOW_PIVOT;
+    if (form == Form::MID) {
+        const tc_status st = tc_count_mid(g, t, lds_limit, max_entries, found, s);
+        const bool short_rows = g->max_dplus <= TC_SLOTS_MAX_DPLUS;
+        if (!tc_no_memory(st) || t.algorithm != TC_ALGO_AUTO ||
+            !(short_rows || tc_low_bytes_promised(g)))
+            return st;
+        // its bit matrices do not fit: the other forms do without
+        tc_mid_release(g, s);
+        g->algo_used = TC_ALGO_LOW_PIVOT;
+        form = short_rows ? Form::SLOTS : Form::LOW;
+    }
+    if (form == Form::SLOTS) {
         g->slots_used = true;
         g->light_max = t.light_max_dplus;
         g->huge_min = 0x7FFFFFFF;
@@ -391,13 +414,6 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
         TC_TRY(tc_count_slots(g, found, s));
         for (int k = 6; k <= 9; ++k) tc_prof_mark(g, k, s);
         return TC_OK;
-    }
-    if (algo == TC_ALGO_MID_PIVOT) {
-        const tc_status st = tc_count_mid(g, t, lds_limit, max_entries, found, s);
-        if (!tc_no_memory(st) || t.algorithm != TC_ALGO_AUTO || !tc_low_bytes_promised(g)) return st;
-        // its bit matrices do not fit: the low pivot does without
-        tc_mid_release(g, s);
-        g->algo_used = algo = TC_ALGO_LOW_PIVOT;
     }
     const int light_max = t.light_max_dplus;
     // heavy rows: light_max < d+ < huge_min (table at most half full); the

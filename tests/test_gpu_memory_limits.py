@@ -23,6 +23,8 @@ FORMS = {
     # the symmetric adjacency that the low pivot aggregates over; as one small
     # graph by one workgroup it sorts for it
     "low": (lambda: gg.ba(20_000, 4, seed=11), {"algorithm": 1}),
+    # AUTO: the middle pivot, and the slot merge where it does not fit
+    "short_rows": (lambda: gg.disjoint_cliques(80, 100), None),
     "low_small": (lambda: gg.clique(170), {"algorithm": 1}),
 }
 

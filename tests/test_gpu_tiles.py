@@ -179,6 +179,35 @@ def test_slot_merge_edges(tclib, name):
     g.close()
 
 
+# short rows whose edges have many triangles (as many as half their entries) cost
+# the merge an atomic add each: the middle pivot takes them, the merge the others
+@pytest.mark.parametrize("name,mid", [("cliques", True), ("batch_rmat", True), ("flat", False),
+                                      ("few_cliques", False)])
+def test_slot_merge_or_middle_pivot(tclib, name, mid):
+    if name == "batch_rmat":
+        graphs = [gg.rmat(12, 16, seed=40 + i % 4) for i in range(40)]
+        po = np.cumsum([0] + [len(x[0]) for x in graphs])
+        vo = np.cumsum([0] + [x[2] for x in graphs])
+        src, dst = (np.concatenate([x[k] for x in graphs]).astype(np.int32) for k in (0, 1))
+        g = tclib.Graph.batch(src, dst, po, vo)
+        off = np.repeat(vo[:-1], np.diff(po)).astype(np.int32)
+        src, dst, n = src + off, dst + off, int(vo[-1])
+    else:
+        src, dst, n = {"cliques": lambda: gg.disjoint_cliques(400, 100),
+                       "flat": lambda: gg.ba(100_000, 16, seed=2),
+                       "few_cliques": lambda: gg.disjoint_cliques(30, 100)}[name]()
+        g = tclib.Graph.from_edges(src, dst, n)
+    _say("slot merge or middle pivot", name)
+    g.compute()
+    r, ws = g.results(), g.work_stats()
+    g.close()
+    assert ws["max_dplus"] <= 128
+    assert ws["algorithm"] == (tclib.TC_ALGO_MID_PIVOT if mid else tclib.TC_ALGO_LOW_PIVOT)
+    ref = native.o2_paper(src, dst, n)
+    for k, want in (("support", ref.sup), ("tri", ref.tri), ("num", ref.num)):
+        np.testing.assert_array_equal(r[k], want)
+
+
 def test_slot_merge_batch(tclib):
     # graphs that end inside wavefronts, with and without triangles
     graphs = [gg.clique(3 + i % 9) if i % 3 else (np.arange(5, dtype=np.int32),
