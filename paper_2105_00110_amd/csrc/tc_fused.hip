@@ -992,16 +992,29 @@ __device__ __forceinline__ void fused_large(const FusedArgs &a, const GraphRef q
         osup[s] = 0;
     }
     __syncthreads();
-    // row offsets: every entry of orp[0..n] is written once
-    for (uint32_t s = tid; s < m; s += BLOCK) {
-        const uint32_t r = orow[s];
-        const uint32_t from = s == 0 ? 0u : orow[s - 1] + 1u;
-        for (uint32_t q = from; q <= r; ++q) orp[q] = s;
-        if (s == m - 1)
-            for (uint32_t q = r + 1; q <= n; ++q) orp[q] = m;
+    // row offsets: every entry of orp[0..n] is written once.  A slot opens its row
+    // and the empty ones before it; where these are many (the isolated vertices
+    // come first) its wavefront writes them together.  256 graphs of 65000 vertices
+    // and 1000 pairs: 2.7 to 3.4 ms with a thread for all of a slot's, by how that
+    // loop came out of the compiler, 0.95 ms so
+    for (uint32_t s0 = 0; s0 < m; s0 += BLOCK) {
+        const uint32_t s = s0 + tid;
+        uint32_t from = 0, end = 0;
+        if (s < m) {
+            from = s == 0 ? 0u : orow[s - 1] + 1u;
+            end = orow[s] + 1u;
+        }
+        uint64_t wide = __ballot(end > from + TC_WAVE);
+        if (end <= from + TC_WAVE)
+            for (uint32_t q = from; q < end; ++q) orp[q] = s;
+        while (wide) {
+            const int l = __ffsll((unsigned long long)wide) - 1;
+            wide &= wide - 1;
+            const uint32_t e = __shfl(end, l, TC_WAVE), x = __shfl(s, l, TC_WAVE);
+            for (uint32_t q = __shfl(from, l, TC_WAVE) + __lane_id(); q < e; q += TC_WAVE) orp[q] = x;
+        }
     }
-    if (m == 0)
-        for (uint32_t q = tid; q <= n; q += BLOCK) orp[q] = 0;
+    for (uint32_t q = (m > 0 ? orow[m - 1] + 1u : 0u) + tid; q <= n; q += BLOCK) orp[q] = m;
     __syncthreads();
 
     // count: the tail of N_H(r) after c against N_H(c), merged four entries

@@ -173,6 +173,23 @@ def test_fused_degenerate_and_invalid_graphs(tclib):
     assert fb.graph(res, 3)["status"] == tclib.TC_TRIANGLE_FREE
 
 
+@pytest.mark.parametrize("block", [256, 512, 1024])
+def test_fused_rows_after_many_empty_ones(tclib, block):
+    # ranks of isolated vertices come first, and vertices without higher
+    # neighbours lie between the others: gaps of rows up to a wavefront and above
+    rng = np.random.default_rng(17)
+    graphs = [gg.clique(5)]
+    for n, hubs in ((22000, 1), (30000, 70), (65535, 3)):
+        leaves = np.arange(100, 100 + 90 * hubs, dtype=np.int32)
+        far = rng.integers(n - 400, n, (2, 700)).astype(np.int32)
+        graphs.append((np.concatenate([np.repeat(np.arange(hubs, dtype=np.int32), 90), far[0]]),
+                       np.concatenate([leaves, far[1]]), n))
+    graphs.append((np.array([3], np.int32), np.array([60000], np.int32), 65535))
+    _say("fused rows after empty ones", block)
+    fb, res = run_fused(tclib, graphs, tuning={"block": block, "wg_per_cu": 1})
+    check_all(fb, res, graphs)
+
+
 def test_fused_offsets_outside_the_arrays(tclib):
     # graphs 1 and 2 have pair offsets past the end, or decreasing: a status, and
     # the graphs after them are computed
