@@ -1172,10 +1172,17 @@ __global__ void k_fused_init(unsigned char *ws) {
     if (threadIdx.x == 0) reinterpret_cast<uint32_t *>(ws)[0] = 0;
 }
 
-// 512-thread workgroups ask for 4 wavefronts per SIMD (at most 128 VGPRs),
-// so that two of them fit on a compute unit
+// Wavefronts per SIMD that a workgroup size asks for.  512 threads: 4 (at most
+// 128 VGPRs), so that two workgroups fit on a compute unit.  256: 3 (168), for the
+// three that LDS holds; with the 212 that the tiers take if left alone it is two,
+// and 600 graphs of 30000 vertices and 120000 pairs take 18.9 ms (16.3 so), 3000
+// BA graphs of 60 to 260 vertices 0.19 (0.15), but 4096 BA graphs of up to 20000
+// vertices 32.1 (34.7); before the tiers, with 4 per SIMD, the three took 16.2,
+// 0.43 and 38.3 ms.
+constexpr int fused_waves(int block) { return block == 512 ? 4 : block == 256 ? 3 : 1; }
+
 template <int BLOCK>
-__global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_fused_graphs(FusedArgs a) {
+__global__ __launch_bounds__(BLOCK, fused_waves(BLOCK)) void k_fused_graphs(FusedArgs a) {
     __shared__ FusedArena<BLOCK> sh;
     __shared__ uint32_t next;
     uint32_t *head = reinterpret_cast<uint32_t *>(a.ws);
