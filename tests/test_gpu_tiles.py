@@ -320,6 +320,27 @@ def test_fused_tiers(tclib):
 
 
 
+# the same limits at 256 and 512 threads, with the merge's cache (bytes of LDS)
+FUSED_CACHE = {256: 41_984, 512: 76_800}
+
+
+@pytest.mark.parametrize("block", sorted(FUSED_CACHE))
+def test_fused_tiers_of_smaller_workgroups(tclib, block):
+    b, words = block, FUSED_CACHE[block] // 4 - 8
+    graphs = [_pairs_over(4 * b, 16 * b, 1), _pairs_over(4 * b, 16 * b + 1, 2),
+              _pairs_over(4 * b + 1, 16 * b - 100, 3), _pairs_over(6 * b, 24 * b, 4),
+              _pairs_over(6 * b, 24 * b + 1, 5), _pairs_over(21 * b, 70, 6),
+              _pairs_over(21 * b, 100 * b, 7), _pairs_over(21 * b + 1, 100 * b, 8), gg.clique(400),
+              gg.rmat(12, 256, seed=9), gg.rmat(12, 256, seed=9, num_pairs=(1 << 20) + 1),
+              gg.clique(1440), _edges_over(5 * b, words - 5 * b, 10),
+              _edges_over(5 * b, words - 5 * b + 1, 11)]
+    refs = [native.o2_paper(*g) for g in graphs]
+    for wg in (1, 4):
+        _say("fused tiers", block, "threads", wg, "per CU")
+        fb, res = run_fused(tclib, graphs, tuning={"block": block, "wg_per_cu": wg})
+        check_all(fb, res, graphs, refs)
+
+
 # one small graph by one workgroup: its largest size and one more of each, and
 # rows above the slot merge's limit (the general count on such a build)
 SINGLE_GRAPHS = {
