@@ -1312,8 +1312,8 @@ extern "C" {
 tc_status tc_fused_tuning_default(tc_fused_tuning *t) {
     if (!t) return TC_ERR_INVALID_ARG;
     // measured on MI355X, the 4096-graph BA batch (ms) and five ER graphs of 10 k
-    // pairs (us): 1024 threads x 1 per compute unit 10.6, 85; 512 x 1 20.6, 171;
-    // 512 x 2 23.1, 171; 256 x 4 35.3, 290.  Thousands of graphs of a few hundred
+    // pairs (us): 1024 threads x 1 per compute unit 10.6, 103; 512 x 1 20.6, 186;
+    // 512 x 2 23.1, 188; 256 x 4 35.3, 307.  Thousands of graphs of a few hundred
     // vertices go faster with more workgroups: 3000 of 60 to 260 vertices 343 us at
     // 1024 x 1, 195 at 512 x 2, 152 at 256 x 4.
     t->block = 1024;
