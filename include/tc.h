@@ -119,6 +119,8 @@ const char *tc_status_string(int32_t status);
  *   item_pairs       middle pivot only: lower neighbours of one pivot per
  *                    work item of a wavefront (a workgroup item takes this
  *                    many per wavefront); 64..65536, a multiple of 64.
+ *                    Pivots of at most 128 entries, four to a wavefront, take
+ *                    16 (from 2^23 edges on 32) whatever this says.
  *   bitmap_words     middle pivot only: workgroup pivots whose N_H(v)
  *                    spans at most 32*bitmap_words ranks are looked up in
  *                    an LDS bitmap of the span (8 bytes per 32 ranks: the
@@ -129,7 +131,10 @@ const char *tc_status_string(int32_t status);
  *                    light_max_dplus) with at least this many lower
  *                    neighbours and a span that fits the bitmap are
  *                    counted by the workgroup bitmap kernel instead;
- *                    0 keeps all of them on the wavefront kernel.
+ *                    0 keeps all of them on the wavefront kernel.  64, the
+ *                    default, leaves the number to the library below 2^23
+ *                    edges: pivots of more than 128 entries move there with
+ *                    any; every other value holds for all of them.
  * ---------------------------------------------------------------------- */
 #define TC_ALGO_AUTO 0
 #define TC_ALGO_LOW_PIVOT 1

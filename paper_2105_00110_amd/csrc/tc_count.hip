@@ -273,7 +273,7 @@ tc_status tc_tuning_default(tc_tuning *t) {
     t->algorithm = TC_ALGO_AUTO;
     t->item_pairs = 512;
     t->bitmap_words = 4096;
-    t->light_bitmap_pairs = 64;
+    t->light_bitmap_pairs = TC_LIGHT_BITMAP_PAIRS;
     return TC_OK;
 }
 

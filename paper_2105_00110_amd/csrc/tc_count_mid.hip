@@ -1551,8 +1551,10 @@ static tc_status count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int m
     // hash
     const int32_t r16s = bw >= BITMAP16_WORDS ? g->rank16_base : 0x7FFFFFFF;
     // few edges: not a launch of k_mid_wave for a handful of pivots (26 us at
-    // R-MAT scale 16, of 850), which the bitmaps take as well
-    const int64_t wide_min = g->m < FEW_EDGES ? 1 : t.light_bitmap_pairs;
+    // R-MAT scale 16, of 850), which the bitmaps take as well, unless the caller
+    // chose a number of pairs
+    const bool chosen = t.light_bitmap_pairs != TC_LIGHT_BITMAP_PAIRS;
+    const int64_t wide_min = g->m < FEW_EDGES && !chosen ? 1 : t.light_bitmap_pairs;
     PlanRules rules = {gmax, light_max, huge_min, split, lsplit, span_max, t.light_bitmap_pairs, wide_min,
                        r16s, {}};
     for (int i = 0; i < NPLANS; ++i) rules.S[i] = block_pairs;

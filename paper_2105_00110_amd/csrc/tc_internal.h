@@ -291,6 +291,8 @@ constexpr int32_t TOPK_SELECT_MAX = 1024;
 tc_status tc_topk_select(const double *tcv, int32_t n, int32_t k, int32_t *h_verts, double *h_vals,
                          bool *found, hipStream_t s);
 tc_status tc_work_stats(tc_graph *g, int64_t *stats, hipStream_t s);
+// tc_tuning's default of light_bitmap_pairs, which stands for no choice
+constexpr int32_t TC_LIGHT_BITMAP_PAIRS = 64;
 tc_status tc_mid_prepare(tc_graph *g, hipStream_t s, bool keep_order = false);
 // Takes all its memory before it counts: after TC_ERR_BUDGET or TC_ERR_OOM
 // g->osup and *found are as they were.

@@ -462,6 +462,28 @@ def test_mid_pivot_items(tclib):
         np.testing.assert_array_equal(r[k], want)
 
 
+# a caller's number of pairs holds, the default's is the library's below 2^23 edges:
+# which of the two launches has the work of the pivots of 129 to 512 entries
+def test_light_bitmap_pairs_as_chosen(tclib):
+    src, dst, n = gg.rmat(15, 16, seed=5)
+    tclib.tc_set_profiling(True)
+    try:
+        g = tclib.Graph.from_edges(src, dst, n)
+        ms = {}
+        for pairs in (64, 1_000_000):
+            t = {"algorithm": tclib.TC_ALGO_MID_PIVOT, "light_bitmap_pairs": pairs}
+            for _ in range(2):
+                g.compute(t)
+            ms[pairs] = g.stage_ms()
+        g.close()
+    finally:
+        tclib.tc_set_profiling(False)
+    _say("light bitmap pairs", {k: (v["count_light_wave"], v["count_light_bitmap"]) for k, v in ms.items()})
+    # no pivot has a million pairs: the wavefront launch has all of the work
+    assert ms[1_000_000]["count_light_wave"] > 2 * ms[1_000_000]["count_light_bitmap"]
+    assert ms[64]["count_light_bitmap"] > 2 * ms[64]["count_light_wave"]
+
+
 # a limit between what the low and the middle pivot take: AUTO does without the
 # core's matrix, then without the middle pivot, before it gives the limit's error
 @pytest.mark.parametrize("name", ["whole", "clique_900"])
