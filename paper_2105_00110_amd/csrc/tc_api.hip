@@ -828,10 +828,13 @@ tc_status tc_top_k(const tc_graph *g, int32_t k, int32_t *vertices, double *valu
     // three times where the sort of all of them moves them eight times (k = 10
     // of 2^20: 346 against 90 us a call).  The selection decides on the host
     // whether it succeeded, so device outputs, which must not wait, take the
-    // sort, and so does k above what one workgroup sorts.
+    // sort, and so does k above what one workgroup sorts.  On a few vertices the
+    // sort takes less memory than the selection, whose histograms and lists do not
+    // depend on n.
     if (mem_kind == TC_MEM_HOST && k <= TOPK_SELECT_MAX) {
         bool found = false;
-        TC_TRY(tc_topk_select(g->tcv, n, k, vertices, values, &found, s));
+        const tc_status st = tc_topk_select(g->tcv, n, k, vertices, values, &found, s);
+        if (st < 0 && !tc_no_memory(st)) return st;
         if (found) return TC_OK;
     }
     tc_scratch tmp(s);

@@ -112,3 +112,21 @@ def test_compute_bytes_of_mid_sized_graphs(tclib, name):
     assert ws["algorithm"] == tclib.TC_ALGO_MID_PIVOT
     assert grown <= need
     g.close()
+
+
+def test_top_k_of_few_vertices_under_a_limit(tclib):
+    # room for a sort of 40 vertices (under 10 KB), not for the selection's
+    # histograms (64 KB)
+    src, dst, n = gg.clique(40)
+    ref = native.o2_paper(src, dst, n)
+    g = tclib.Graph.from_edges(src, dst, n)
+    g.compute()
+    try:
+        tclib.tc_trim_memory()
+        tclib.tc_set_memory_limit(tclib.tc_memory_stats()["in_use"] + (32 << 10))
+        verts, vals = g.top_k(10)
+    finally:
+        tclib.tc_set_memory_limit(0)
+    np.testing.assert_array_equal(verts, np.arange(10))
+    np.testing.assert_array_equal(vals.view(np.uint64), ref.tc[:10].view(np.uint64))
+    g.close()
