@@ -447,6 +447,18 @@ __global__ void k_edge_offsets(const int32_t *__restrict__ eu, int64_t m,
     }
 }
 
+// A kernel may store to p: memory of the current device (or none).  A copy reaches
+// other memory too.  0.1 us a pointer.
+bool stores_reach(const void *p, int dev) {
+    if (!p) return true;
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == dev;
+}
+
 tc_status copy_out(void *dst, const void *src, size_t bytes, int32_t mem_kind, hipStream_t s) {
     if (bytes == 0) return TC_OK;
     TC_HIP(hipMemcpyAsync(dst, src, bytes,
@@ -753,9 +765,13 @@ tc_status tc_get_results(const tc_graph *g, uint64_t *tri, uint64_t *support, ui
     hipStream_t s = (hipStream_t)stream;
     tc_call_scope scope(s);
     // the buffers may lie at any address that their types allow, and G <= n but
-    // for graphs without vertices
+    // for graphs without vertices; buffers elsewhere than on this device are copied to
     const int64_t most = g->m > g->n ? g->m : g->n;
-    if (mem_kind == TC_MEM_DEVICE && most >= g->num_graphs) {
+    int dev = 0;
+    TC_HIP(hipGetDevice(&dev));
+    if (mem_kind == TC_MEM_DEVICE && most >= g->num_graphs && stores_reach(tri, dev) &&
+        stores_reach(support, dev) && stores_reach(triG, dev) && stores_reach(num, dev) &&
+        stores_reach(tc, dev)) {
         const ResultArgs a{g->tri, g->num, g->triG, g->tcv, g->esup, tri, num, triG, support, tc};
         k_results<<<grid_for(most), BK, 0, s>>>(a, g->n, g->m, g->num_graphs);
         TC_LAUNCHED();

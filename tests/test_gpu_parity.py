@@ -609,3 +609,23 @@ def test_cached_memory_across_streams_and_trim(tclib):
         assert_parity(r, ref)
         if rep == 2:
             tclib.tc_trim_memory()
+
+
+def test_device_results_into_pinned_memory(tclib):
+    # buffers that the device reaches but that are not its own memory take copies
+    src, dst, n = gg.ba(5000, 7, seed=6)
+    ref = native.o2_paper(src, dst, n)
+    g = tclib.Graph.from_edges(src, dst, n)
+    g.compute()
+    out = {k: torch.full((c,), -1, dtype=torch.int64, pin_memory=True)
+           for k, c in (("tri", n), ("support", g.m), ("triG", 1), ("num", n))}
+    out["tc"] = torch.full((n,), -1.0, dtype=torch.float64, pin_memory=True)
+    _say("device results into pinned memory")
+    tclib.tc_get_results(g.h, *(out[k].data_ptr() for k in ("tri", "support", "triG", "num", "tc")),
+                         tclib.TC_MEM_DEVICE, g.stream)
+    torch.cuda.synchronize()
+    g.close()
+    for k, want in (("tri", ref.tri), ("support", ref.sup), ("num", ref.num)):
+        np.testing.assert_array_equal(out[k].numpy().view(np.uint64), want)
+    assert int(out["triG"][0]) == ref.triG
+    np.testing.assert_array_equal(out["tc"].numpy().view(np.uint64), ref.tc.view(np.uint64))
