@@ -208,6 +208,53 @@ def test_slot_merge_or_middle_pivot(tclib, name, mid):
         np.testing.assert_array_equal(r[k], want)
 
 
+def _wide(graph, n):
+    """The graph with isolated vertices up to n: past the sizes of one workgroup."""
+    src, dst, _ = graph
+    return src, dst, n
+
+
+def _long_rows(lows):
+    """`lows` vertices with 127 or 128 higher neighbours each, out of 128 hubs of
+    which three are linked: rows that end at and across the runs of a workgroup,
+    with a triangle here and there."""
+    keep = np.ones((lows, 128), bool)
+    keep[::3, 5] = False
+    v, h = np.nonzero(keep)
+    hubs = np.array([[9, 70], [70, 127], [9, 127]])
+    return (np.concatenate([128 + v, hubs[:, 0]]).astype(np.int32),
+            np.concatenate([h, hubs[:, 1]]).astype(np.int32), 128 + max(lows, 4500))
+
+
+# as above, on builds that take the slot merge's own kernels: rows at its window,
+# the longest row, and graphs of as many vertices as the sums keep in LDS (8192)
+# and one more; runs of 256 slots a workgroup and of 2048
+SLOT_KERNEL_GRAPHS = {
+    **{f"K{k}": (lambda k=k: _wide(gg.clique(k), 5000)) for k in (3, 8, 9, 10, 17, 18, 129)},
+    "window": lambda: _hub_and_clique(8192),
+    "window_past": lambda: _hub_and_clique(8193),
+    "triangle_free": lambda: _wide(gg.single_triangle_with_pendants((0, 4000, 1)), 6000),
+    "long_rows": lambda: _long_rows(700),
+    "long_rows_long_runs": lambda: _long_rows(64_000),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SLOT_KERNEL_GRAPHS))
+def test_slot_merge_kernels(tclib, name):
+    src, dst, n = SLOT_KERNEL_GRAPHS[name]()
+    _say("slot merge kernels", name, "n", n)
+    assert n > 4096  # not one workgroup's
+    ref = native.o2_paper(src, dst, n)
+    assert_parity(run_gpu(tclib, src, dst, n), ref)
+    g = tclib.Graph.from_edges(src, dst, n)
+    g.compute()
+    ws = g.work_stats()
+    g.close()
+    assert ws["max_dplus"] <= 128 and ws["algorithm"] == tclib.TC_ALGO_LOW_PIVOT
+    if name.startswith("long"):
+        assert ws["max_dplus"] == 128
+
+
 def test_slot_merge_batch(tclib):
     # graphs that end inside wavefronts, with and without triangles
     graphs = [gg.clique(3 + i % 9) if i % 3 else (np.arange(5, dtype=np.int32),
@@ -415,6 +462,26 @@ def test_core_products(tclib, name):
     for k in ("tri", "support", "triG", "num"):
         np.testing.assert_array_equal(a[k], b[k])
     g.close()
+
+
+# the scan leaves out at least the wedges of the smallest core, the 2048 highest ranks
+@pytest.mark.parametrize("name", sorted(set(CORE_GRAPHS) - {"skewed"}))
+def test_core_products_are_taken(tclib, name):
+    src, dst, n = CORE_GRAPHS[name]()
+    k = np.unique(np.minimum(src, dst).astype(np.int64) * n + np.maximum(src, dst))
+    u, v = k // n, k % n
+    u, v = u[u != v], v[u != v]
+    rank = np.empty(n, np.int64)
+    rank[np.lexsort((np.arange(n), np.bincount(np.concatenate([u, v]), minlength=n)))] = np.arange(n)
+    d = np.bincount(np.minimum(rank[u], rank[v]), minlength=n)
+    core = int((d * (d - 1) // 2)[-2048:].sum())
+    g = tclib.Graph.from_edges(src, dst, n)
+    g.compute()
+    ws = g.work_stats()
+    g.close()
+    _say("core products taken", name, "wedges", ws["wedges"], "of the smallest core", core)
+    assert core > 0 and ws["wedges"] == int((d * (d - 1) // 2).sum())
+    assert ws["cand_light"] + ws["cand_heavy"] + ws["cand_huge"] <= ws["wedges"] - core
 
 
 # orientation buckets at the edges of the size classes (8, 16, 32, 64, 128, 256
