@@ -310,10 +310,12 @@ tc_status tc_aggregate_slots(tc_graph *g, hipStream_t s) {
     if (!g->tcv) TC_TRY(tc_graph_alloc(g, &g->tcv, n, s));
     const int64_t *voff = G > 1 ? g->vtx_off : nullptr;
     tc_scratch tmp(s);
-    ull *acc = nullptr;  // twice the triangles by rank, the numerators by rank, sums
-    TC_TRY(tmp.get(&acc, 2 * (int64_t)n + G));
-    ull *num2 = acc + n, *sums = num2 + n;
-    TC_TRY(tc_zero({{acc, 2 * (2 * (int64_t)n + G)}}, s));
+    // twice the triangles by rank, in num until that is written at the end; the
+    // numerators by rank, sums
+    ull *acc = reinterpret_cast<ull *>(g->num), *num2 = nullptr;
+    TC_TRY(tmp.get(&num2, (int64_t)n + G));
+    ull *sums = num2 + n;
+    TC_TRY(tc_zero({{acc, 2 * (int64_t)n}, {num2, 2 * ((int64_t)n + G)}}, s));
     const int64_t run = run_for(m, g->rank_by_graph ? SUM_RUNS_GRAPHS : SUM_RUNS, SUM_BLOCK);
     const int64_t *span = g->rank_by_graph ? voff : nullptr;
     k_slot_sums<1><<<runs_grid(m, run), SUM_BLOCK, 0, s>>>(m, run, n, g->ocol, g->orow, g->osup, g->o2e,

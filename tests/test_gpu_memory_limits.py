@@ -130,3 +130,25 @@ def test_top_k_of_few_vertices_under_a_limit(tclib):
     np.testing.assert_array_equal(verts, np.arange(10))
     np.testing.assert_array_equal(vals.view(np.uint64), ref.tc[:10].view(np.uint64))
     g.close()
+
+
+def test_estimate_holds_for_many_isolated_vertices(tclib):
+    # a triangle among 24 million vertices: what counts is the bytes per vertex
+    n = 24_000_000
+    src, dst = np.array([5, 1000, n - 1], np.int32), np.array([1000, n - 1, 5], np.int32)
+    est = tclib.tc_estimate_device_bytes(src.shape[0], n)
+    try:
+        tclib.tc_trim_memory()
+        before = tclib.tc_memory_stats(reset_peaks=True)["in_use"]
+        tclib.tc_set_memory_limit(tclib.tc_memory_stats()["held"] + est)
+        g = tclib.Graph.from_edges(src, dst, n)
+        g.compute()
+        used = tclib.tc_memory_stats()["peak_in_use"] - before
+        verts, _ = g.top_k(3)
+        g.close()
+    finally:
+        tclib.tc_set_memory_limit(0)
+        tclib.tc_trim_memory()
+    print("[case] estimate", est, "used", used, flush=True)
+    assert list(verts) == [5, 1000, n - 1]
+    assert used <= est
