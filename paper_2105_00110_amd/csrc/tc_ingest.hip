@@ -354,7 +354,7 @@ tc_status tc_relabel_ids(const int64_t *src, const int64_t *dst, int64_t num_pai
     k_ids_keys<<<grid_for(P), BK, 0, s>>>(d_src, d_dst, P, base, keys);
     TC_LAUNCHED();
     TC_TRY(tc_sort_u64(&keys, &keys2, N2, bits, s));
-    uint32_t *cnt = nullptr, *tot = nullptr, *start = nullptr;
+    uint32_t *cnt = nullptr, *tot = nullptr;
     int64_t *uniq = nullptr;
     const int64_t tiles = tc_div_up(N2, UQ_TILE);
     TC_TRY(tmp.get(&cnt, tiles));
@@ -368,12 +368,14 @@ tc_status tc_relabel_ids(const int64_t *src, const int64_t *dst, int64_t num_pai
     TC_TRY(tmp.get(&uniq, hn));
     k_ids_unique<true><<<(unsigned)tiles, BK, 0, s>>>(keys, N2, base, nullptr, cnt, uniq);
     TC_LAUNCHED();
-    // buckets: one to two per distinct id, at most 2^22 (16 MB)
+    // buckets: one to two per distinct id, at most 2^22 (16 MB), and no more than
+    // fit the sort's other buffer, which is free
     int bbits = tc_bits_for(hn) < 22 ? tc_bits_for(hn) : 22;
     if (bbits > bits) bbits = bits;
+    while (((int64_t)1 << bbits) + 1 > 2 * N2) --bbits;
     const int shift = bits - bbits;
     const uint32_t nb = 1u << bbits;
-    TC_TRY(tmp.get(&start, (int64_t)nb + 1));
+    uint32_t *const start = reinterpret_cast<uint32_t *>(keys2);
     k_ids_buckets<<<grid_for((int64_t)nb + 1), BK, 0, s>>>(uniq, hn, base, shift, nb, start);
     TC_LAUNCHED();
     int32_t *o_s = src32, *o_d = dst32;

@@ -14,6 +14,8 @@ from tests.test_gpu_tiles import _dense_core
 
 pytestmark = pytest.mark.gpu
 
+torch = pytest.importorskip("torch")
+
 STEP = 512
 # above 16384 vertices the scans take scratch of their own
 FORMS = {
@@ -152,3 +154,31 @@ def test_estimate_holds_for_many_isolated_vertices(tclib):
     print("[case] estimate", est, "used", used, flush=True)
     assert list(verts) == [5, 1000, n - 1]
     assert used <= est
+
+
+# all ids distinct, a power of two of them and not: keys, the sort's other buffer and
+# its counts, the ids; what the lookup needs beside the map lies in those
+@pytest.mark.parametrize("pairs", [1, 2, 1 << 16, 100_000])
+def test_relabel_within_the_sorts_memory(tclib, pairs):
+    ids = np.random.default_rng(3).permutation(8 * pairs)[:2 * pairs].astype(np.int64) << 20
+    src, dst = torch.from_numpy(ids[:pairs]).cuda(), torch.from_numpy(ids[pairs:]).cuda()
+    s32, d32 = (torch.empty(pairs, dtype=torch.int32, device="cuda") for _ in range(2))
+    tclib.tc_trim_memory()
+    before = tclib.tc_memory_stats(reset_peaks=True)["in_use"]
+    n = tclib.tc_relabel_ids(src.data_ptr(), dst.data_ptr(), pairs, s32.data_ptr(), d32.data_ptr(), None,
+                             tclib.TC_MEM_DEVICE, None)
+    used = tclib.tc_memory_stats()["peak_in_use"] - before
+    want = np.sort(ids)
+    assert n == 2 * pairs
+    np.testing.assert_array_equal(s32.cpu().numpy(), np.searchsorted(want, ids[:pairs]))
+    np.testing.assert_array_equal(d32.cpu().numpy(), np.searchsorted(want, ids[pairs:]))
+    # three arrays of 8 bytes an id, 1 KB of counts per 2048 ids and two more, blocks
+    # rounded up to 512 bytes (2 MiB from 1 MiB on)
+    n2 = 2 * pairs
+    def block(b):
+        unit = 512 if b < 1 << 20 else 2 << 20
+        return (b + unit - 1) // unit * unit
+
+    rounded = [8 * n2] * 3 + [1024 * (n2 // 2048 + 2), 4 * (n2 // 4096 + 1), 4, 16]
+    print("[case] relabel", pairs, "used", used, flush=True)
+    assert used <= sum(block(b) for b in rounded)
