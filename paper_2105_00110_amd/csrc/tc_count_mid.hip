@@ -1200,15 +1200,13 @@ __global__ __launch_bounds__(256, 4) void k_fold_big(const int32_t *__restrict__
     }
 }
 
-// Per vertex its flag byte, the class in the low four bits (15: none) and the
-// fold list, less L_FOLD, above them (15: none); per (list, tile) the number
-// of entries.
-__global__ void k_dplus_flags(PlanRules q, int32_t n,
-                                                    const int64_t *__restrict__ orp,
-                                                    const int32_t *__restrict__ ocol,
-                                                    const int64_t *__restrict__ in_ptr, tc_core core,
-                                                    uint8_t *__restrict__ flags,
-                                                    int64_t *__restrict__ tile_cnt) {
+// Per vertex its flag byte, by d+ and what else places it: the class of its items
+// in the low four bits (15: none) and the fold list, less L_FOLD, above them
+// (15: none); per (list, tile) the number of entries.
+__global__ void k_dplus_flags(PlanRules q, int32_t n, const int64_t *__restrict__ orp,
+                              const int32_t *__restrict__ ocol, const int64_t *__restrict__ in_ptr,
+                              tc_core core, uint8_t *__restrict__ flags,
+                              int64_t *__restrict__ tile_cnt) {
     __shared__ uint32_t red[NLISTS][BK / TC_WAVE];
     const int64_t base = (int64_t)blockIdx.x * PLAN_TILE;
     uint32_t c[NLISTS] = {};

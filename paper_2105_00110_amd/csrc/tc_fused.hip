@@ -466,8 +466,6 @@ __device__ __forceinline__ void medium_hist(const SortPlan &sp, uint32_t key, Me
             atomicAdd(&T.hist[p][(key >> sp.at(p)) & ((1u << sp.bits_at(p)) - 1u)], 1u);
 }
 
-// Stable sort of k[0..n) (result in k, kt the other buffer) with the digit
-// counts of every pass already in T.hist.
 // Element i of a slice of under 2^32 bytes: a scalar base and a 32-bit offset
 // (64-bit addresses for every load in flight cost the tiles their registers).
 template <typename T>
@@ -475,6 +473,8 @@ __device__ __forceinline__ T &at(T *base, uint32_t i) {
     return *reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(base) + (uintptr_t)(i * (uint32_t)sizeof(T)));
 }
 
+// Stable sort of k[0..n) (result in k, kt the other buffer) with the digit
+// counts of every pass already in T.hist.
 template <int BLOCK>
 __device__ __forceinline__ void medium_sort(uint32_t *&k, uint32_t *&kt, uint32_t n,
                                             const SortPlan &sp, unsigned char *raw,
@@ -799,8 +799,12 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
         }
         __syncthreads();
     }
-    // twice the triangles per rank, in LDS (at most 2^20 edges make at most
-    // 5.1e8 triangles: every sum here is below 2^32), with the supports out
+    // twice the triangles per rank, in LDS, with the supports out.  32 bits hold
+    // every sum here: at most 2^20 edges make at most T = 5.1e8 triangles, and a
+    // vertex's weighted sum is at most 3 T as well.  Its neighbours of weight 3 are
+    // adjacent to none of its other neighbours (that would be a triangle), so a
+    // triangle with one of them has no second neighbour among its vertices and
+    // counts 3; the others have at most three neighbours of weight 1
     for (uint32_t v = tid; v < n; v += BLOCK) {
         words[v] = 0;
         rank[v] = (uint16_t)at(q.rank, v);
@@ -1017,12 +1021,12 @@ __device__ __forceinline__ void fused_large(const FusedArgs &a, const GraphRef q
     for (uint32_t q = (m > 0 ? orow[m - 1] + 1u : 0u) + tid; q <= n; q += BLOCK) orp[q] = m;
     __syncthreads();
 
-    // count: the tail of N_H(r) after c against N_H(c), merged four entries
-    // of each list at a time: the eight loads of a round are independent
-    // (one memory latency per round instead of one per step), all sixteen
-    // pairs are compared, and every entry up to the smaller of the two
-    // windows' last entries is then settled (an entry above it can equal
-    // nothing in the other window)
+    // count: the tail of N_H(r) after c against N_H(c), merged eight entries of
+    // each list at a time: the sixteen loads of a round are independent (one
+    // memory latency per round instead of one per step), all 64 pairs are
+    // compared, and every entry up to the smaller of the two windows' last
+    // entries is then settled (an entry above it can equal nothing in the other
+    // window)
     for (uint32_t s = tid; s < m; s += BLOCK) {
         const uint32_t r = orow[s], c = ocol[s];
         uint32_t i = s + 1, j = orp[c];

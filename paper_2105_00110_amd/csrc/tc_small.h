@@ -96,9 +96,10 @@ __device__ __forceinline__ uint32_t elem(int it, int itn) {
            (uint32_t)__lane_id();
 }
 
-// One stable pass over the width-bit digit at shift: place[it] is the element's
-// position in the digit order of the tile (IN_TILE) plus, otherwise, base[d]
-// less the digit's start in the tile.  The caller has a barrier before.
+// Ranks of a stable pass over the width-bit digit at shift: place[it] is the number
+// of elements with the same digit that come before in the wavefront's own, and
+// wcnt[w][d] the wavefront's count of digit d.  The caller has a barrier before
+// and after.
 //
 // Ranks come from ballots: the lanes with the same digit form a mask, the rank
 // is the count of lower lanes in it plus the wavefront's count so far.
