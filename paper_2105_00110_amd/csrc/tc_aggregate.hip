@@ -421,22 +421,31 @@ static tc_status aggregate_rank_space(tc_graph *g, hipStream_t s);
 // graphs first group the (edge, support) pairs by the top 8 bits of the
 // edge id with one stable radix pass, so the stores then land in windows of
 // about m / 256 edges instead of all over esup.
+struct SupportPairs {
+    uint32_t *edge = nullptr, *sup = nullptr;
+};
+
+static tc_status support_pairs(const tc_graph *g, SupportPairs &p, tc_scratch &tmp) {
+    if (g->m < ((int64_t)1 << 22)) return TC_OK;
+    TC_TRY(tmp.get(&p.edge, g->m));
+    return tmp.get(&p.sup, g->m);
+}
+
 static tc_status support_to_edge_order(tc_graph *g, hipStream_t s) {
     const int64_t m = g->m;
     if (m == 0) return TC_OK;
-    if (m < ((int64_t)1 << 22)) {
+    tc_scratch tmp(s);
+    SupportPairs p;
+    TC_TRY(support_pairs(g, p, tmp));
+    if (!p.edge) {
         k_scatter_sup<<<grid_for(m), BK, 0, s>>>(m, g->o2e, g->osup, g->esup);
         TC_LAUNCHED();
         return TC_OK;
     }
     int ebits = 0;
     while (((int64_t)1 << ebits) < m) ++ebits;
-    tc_scratch tmp(s);
-    uint32_t *e2 = nullptr, *s2 = nullptr;
-    TC_TRY(tmp.get(&e2, m));
-    TC_TRY(tmp.get(&s2, m));
-    TC_TRY(tc_partition_u32_u32(g->o2e, g->osup, e2, s2, m, ebits - 8, s));
-    k_store_pairs<<<grid_for(m), BK, 0, s>>>(m, e2, s2, g->esup);
+    TC_TRY(tc_partition_u32_u32(g->o2e, g->osup, p.edge, p.sup, m, ebits - 8, s));
+    k_store_pairs<<<grid_for(m), BK, 0, s>>>(m, p.edge, p.sup, g->esup);
     TC_LAUNCHED();
     return TC_OK;
 }
@@ -515,15 +524,51 @@ tc_status tc_aggregate(tc_graph *g, hipStream_t s) {
     return TC_OK;
 }
 
+// What the aggregation in rank space allocates: results on the handle, and scratch.
+static tc_status rank_results(tc_graph *g, hipStream_t s) {
+    const int64_t nn = g->n > 0 ? g->n : 1;
+    if (!g->esup) TC_TRY(tc_graph_alloc(g, &g->esup, g->m, s));
+    if (!g->tri) TC_TRY(tc_graph_alloc(g, &g->tri, nn, s));
+    if (!g->num) TC_TRY(tc_graph_alloc(g, &g->num, nn, s));
+    if (!g->tcv) TC_TRY(tc_graph_alloc(g, &g->tcv, nn, s));
+    return TC_OK;
+}
+
+struct RankScratch {
+    uint32_t *in_uw = nullptr, *chunks = nullptr;
+    uint64_t *tri_r = nullptr, *chunk = nullptr, *part = nullptr;
+    int64_t cap = 0;  // chunks at most
+};
+
+static tc_status rank_scratch(const tc_graph *g, RankScratch &r, tc_scratch &tmp) {
+    const int64_t m = g->m;
+    TC_TRY(tmp.get(&r.in_uw, m > 0 ? m : 1));
+    TC_TRY(tmp.get(&r.tri_r, g->n > 0 ? g->n : 1));
+    // a row's entries are its degree: none above RANK_SMALL, no chunks; else
+    // at most this many, the number itself staying on the device
+    r.cap = g->max_degree > RANK_SMALL ? 2 * m / RANK_CHUNK + 2 * m / (RANK_SMALL + 1) + 1 : 0;
+    if (r.cap > 0) {
+        TC_TRY(tmp.get(&r.chunks, 1));
+        TC_TRY(tmp.get(&r.chunk, r.cap));
+        TC_TRY(tmp.get(&r.part, r.cap));
+    }
+    return TC_OK;
+}
+
+tc_status tc_rank_room(tc_graph *g, hipStream_t s) {
+    TC_TRY(rank_results(g, s));
+    tc_scratch tmp(s);
+    RankScratch r;
+    TC_TRY(rank_scratch(g, r, tmp));
+    SupportPairs p;
+    return support_pairs(g, p, tmp);
+}
+
 static tc_status aggregate_rank_space(tc_graph *g, hipStream_t s) {
     const int32_t n = g->n;
     const int64_t m = g->m;
     const int32_t G = g->num_graphs;
-    const int64_t nn = n > 0 ? n : 1;
-    if (!g->esup) TC_TRY(tc_graph_alloc(g, &g->esup, m, s));
-    if (!g->tri) TC_TRY(tc_graph_alloc(g, &g->tri, nn, s));
-    if (!g->num) TC_TRY(tc_graph_alloc(g, &g->num, nn, s));
-    if (!g->tcv) TC_TRY(tc_graph_alloc(g, &g->tcv, nn, s));
+    TC_TRY(rank_results(g, s));
     const int64_t *voff = G > 1 ? g->vtx_off : nullptr;
     if (n == 0) {
         TC_TRY(tc_zero({{g->triG, 2 * (int64_t)G}}, s));
@@ -532,20 +577,12 @@ static tc_status aggregate_rank_space(tc_graph *g, hipStream_t s) {
         return TC_OK;
     }
     tc_scratch tmp(s);
-    uint32_t *in_uw = nullptr, *chunks = nullptr;
-    uint64_t *tri_r = nullptr, *chunk = nullptr, *part = nullptr;
-    TC_TRY(tmp.get(&in_uw, m > 0 ? m : 1));
-    TC_TRY(tmp.get(&tri_r, nn));
-    // a row's entries are its degree: none above RANK_SMALL, no chunks; else
-    // at most this many, the number itself staying on the device
-    const bool any_chunk = g->max_degree > RANK_SMALL;
-    const int64_t cap =
-        any_chunk ? 2 * m / RANK_CHUNK + 2 * m / (RANK_SMALL + 1) + 1 : 0;
-    if (any_chunk) {
-        TC_TRY(tmp.get(&chunks, 1));
-        TC_TRY(tmp.get(&chunk, cap));
-        TC_TRY(tmp.get(&part, cap));
-    }
+    RankScratch r;
+    TC_TRY(rank_scratch(g, r, tmp));
+    uint32_t *const in_uw = r.in_uw, *const chunks = r.chunks;
+    uint64_t *const tri_r = r.tri_r, *const chunk = r.chunk, *const part = r.part;
+    const int64_t cap = r.cap;
+    const bool any_chunk = cap > 0;
     TC_TRY(tc_zero({{g->triG, 2 * (int64_t)G}, {chunks, 1}}, s));
     if (any_chunk) {
         k_rank_chunk_list<<<(unsigned)tc_div_up(n, RC_TILE), BK, 0, s>>>(n, g->orp, g->in_ptr, chunks,

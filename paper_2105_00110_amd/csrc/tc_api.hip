@@ -185,6 +185,11 @@ size_t tc_block_size(size_t b) {
     return (b + g - 1) / g * g;
 }
 
+bool tc_memory_limited() {
+    std::lock_guard<std::mutex> lk(g_alloc_mu);
+    return g_limit > 0;
+}
+
 tc_status tc_dev_alloc(void **p, size_t bytes, hipStream_t s) {
     int dev = 0;
     TC_HIP(hipGetDevice(&dev));

@@ -32,8 +32,10 @@ namespace {
 constexpr int BK = 256;
 constexpr int UNROLL = 4;  // independent candidate loads in flight per lane
 // Above the slot merge TC_ALGO_AUTO takes the middle pivot from this many
-// edges (whole calls, low / middle, us: 161 k edges 980 / 1264, 205 k 936 / 880,
-// 308 k 1098 / 909 and 954 / 973, 442 k 948 / 878, 910 k 1263 / 970).
+// edges (whole calls, low / middle, us: R-MAT scale 13, 183 k edges 852 / 661, scale
+// 14, 213 k 871 / 736 and 389 k 1060 / 744, scale 15, 441 k 902 / 686; K_660, 217 k
+// 1605 / 811, K_1000 2003 / 1099; half of all pairs of 1000 vertices, 250 k 1435 /
+// 646; a tenth of those of 3000, 450 k 1040 / 664; BA attach 150, 441 k 842 / 603).
 constexpr int64_t AUTO_MID_MIN_EDGES = 200000;
 using namespace tc_tab;
 
@@ -397,14 +399,11 @@ tc_status tc_count(tc_graph *g, const tc_tuning *tin, hipStream_t s) {
     g->algo_used = form == Form::MID ? TC_ALGO_MID_PIVOT : TC_ALGO_LOW_PIVOT;
     if (form == Form::MID) {
         const tc_status st = tc_count_mid(g, t, lds_limit, max_entries, found, s);
-        const bool short_rows = g->max_dplus <= TC_SLOTS_MAX_DPLUS;
-        if (!tc_no_memory(st) || t.algorithm != TC_ALGO_AUTO ||
-            !(short_rows || tc_low_bytes_promised(g)))
-            return st;
-        // its bit matrices do not fit: the other forms do without
+        if (!tc_no_memory(st) || !tc_mid_may_yield(g, t)) return st;
+        // its arrays do not fit: the other forms do without
         tc_mid_release(g, s);
         g->algo_used = TC_ALGO_LOW_PIVOT;
-        form = short_rows ? Form::SLOTS : Form::LOW;
+        form = g->max_dplus <= TC_SLOTS_MAX_DPLUS ? Form::SLOTS : Form::LOW;
     }
     if (form == Form::SLOTS) {
         g->slots_used = true;

@@ -1503,7 +1503,7 @@ void tc_mid_release(tc_graph *g, hipStream_t s) {
 static tc_status count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
                            bool use_core, unsigned long long *found, hipStream_t s) {
     g->core_n = 0;
-    TC_TRY(tc_mid_prepare(g, s, t.algorithm == TC_ALGO_AUTO && tc_low_bytes_promised(g)));
+    TC_TRY(tc_mid_prepare(g, s, tc_mid_may_yield(g, t)));
     TC_TRY(ocol16_prepare(g, s));
     const int light_max = t.light_max_dplus;
     int huge_min = max_entries / 2 + 1;
@@ -1582,6 +1582,9 @@ static tc_status count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int m
     TC_TRY(items.get(&item_v, n_items));
     TC_TRY(items.get(&item_first, n_items));
     TC_TRY(items.get(&fold_rows, n_rows));
+    // what comes after the count has to fit a limit as well, while the other forms
+    // can still be taken (10 us of allocations, the device idle)
+    if (tc_memory_limited() && tc_mid_may_yield(g, t)) TC_TRY(tc_rank_room(g, s));
     tc_release_transposition(g, s);  // everything is there
     k_plan_write<<<(unsigned)plan_tiles, BK, 0, s>>>(rules, g->n, flags, g->in_ptr, core, tile_cnt, item_v,
                                                      item_first, fold_rows);

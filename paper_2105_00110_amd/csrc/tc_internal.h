@@ -50,6 +50,8 @@ static inline int tc_bits_for(uint64_t max_value) {
 tc_status tc_dev_alloc(void **p, size_t bytes, hipStream_t s);
 // the size of the block that holds bytes
 size_t tc_block_size(size_t bytes);
+// whether tc_set_memory_limit holds one
+bool tc_memory_limited();
 // idle: no work that uses the block is pending on any stream
 void tc_dev_free(void *p, hipStream_t s, bool idle = false);
 
@@ -298,6 +300,13 @@ tc_status tc_mid_prepare(tc_graph *g, hipStream_t s, bool keep_order = false);
 // g->osup and *found are as they were.
 tc_status tc_count_mid(tc_graph *g, const tc_tuning &t, int lds_limit, int max_entries,
                        unsigned long long *found, hipStream_t s);
+// The slot merge (tc_slots.hip) up to this longest oriented row: a slot's merge
+// grows with the rows, a table or bitmap lookup does not.  Whole calls, merge
+// against the forms above (us): BA attach 32, 0.65 M edges, longest row 50:
+// 625 / 853; BA attach 64, 12.9 M edges, 94: 4305 / 5726; R-MAT scale 13, 103:
+// 570 / 634; BA attach 100, 126: 1203 / 1175; R-MAT scale 15, 192: 1146 / 931;
+// scale 16, 246: 1879 / 955.
+constexpr int TC_SLOTS_MAX_DPLUS = 128;
 // Graphs for which tc_compute_bytes promises that AUTO stays within the low
 // pivot's bound.  AUTO still takes the middle pivot there where all its arrays fit
 // into that bound (tc_mid_most_bytes); and where a memory limit leaves no room for
@@ -311,6 +320,14 @@ static inline bool tc_low_bytes_promised(const tc_graph *g) {
 int64_t tc_mid_most_bytes(const tc_graph *g);
 // Frees what the middle pivot keeps on the handle.
 void tc_mid_release(tc_graph *g, hipStream_t s);
+// Has what the aggregation after it will allocate: the results on the handle, the
+// scratch given back at once for it to take again (tc_aggregate.hip).
+tc_status tc_rank_room(tc_graph *g, hipStream_t s);
+// Whether AUTO counts in another form where the middle pivot finds no memory.
+static inline bool tc_mid_may_yield(const tc_graph *g, const tc_tuning &t) {
+    return t.algorithm == TC_ALGO_AUTO &&
+           (g->max_dplus <= TC_SLOTS_MAX_DPLUS || tc_low_bytes_promised(g));
+}
 static inline bool tc_no_memory(tc_status st) { return st == TC_ERR_BUDGET || st == TC_ERR_OOM; }
 // tc_core.hip: the core's size for this graph (0: none); its matrix
 // (N * N / 32 words of 16 bytes) and the ends of its pairs; its products added
@@ -327,13 +344,6 @@ bool tc_single_fits(int64_t P, int32_t n);
 tc_status tc_single_build(tc_graph *g, const int32_t *d_src, const int32_t *d_dst, int64_t P,
                           hipStream_t s);
 tc_status tc_single_count(tc_graph *g, hipStream_t s);
-// The slot merge (tc_slots.hip) up to this longest oriented row: a slot's merge
-// grows with the rows, a table or bitmap lookup does not.  Whole calls, merge
-// against the forms above (us): BA attach 32, 0.65 M edges, longest row 50:
-// 625 / 853; BA attach 64, 12.9 M edges, 94: 4305 / 5726; R-MAT scale 13, 103:
-// 570 / 634; BA attach 100, 126: 1203 / 1175; R-MAT scale 15, 192: 1146 / 931;
-// scale 16, 246: 1879 / 955.
-constexpr int TC_SLOTS_MAX_DPLUS = 128;
 // Flat graphs (tc_slots.hip): support per slot into the zeroed g->osup, then
 // everything that tc_aggregate fills.
 tc_status tc_count_slots(tc_graph *g, unsigned long long *found, hipStream_t s);

@@ -116,6 +116,59 @@ def test_compute_bytes_of_mid_sized_graphs(tclib, name):
     g.close()
 
 
+def _sparse_with_cliques(n, m, size):
+    """A sparse random graph with a clique on its first vertices: many vertices per
+    edge, and rows that the slot merge does not take."""
+    rng = np.random.default_rng(21)
+    s, d, _ = gg.clique(size)
+    a, b = rng.integers(0, n, (2, m)).astype(np.int32)
+    return np.concatenate([s, a]), np.concatenate([d, b]), n
+
+
+# whatever the low pivot fits into is enough for AUTO, also where the middle pivot's
+# count fits and its aggregation does not
+@pytest.mark.parametrize("name", ["sparse", "dense"])
+def test_auto_fits_where_the_low_pivot_does(tclib, name):
+    src, dst, n = _sparse_with_cliques(200_000, 210_000, 220) if name == "sparse" else gg.clique(700)
+    ref = native.o2_paper(src, dst, n)
+
+    def fits(steps, tuning):
+        tclib.tc_set_memory_limit(0)
+        g = tclib.Graph.from_edges(src, dst, n)
+        assert 200_000 <= g.m < 600_000
+        tclib.tc_trim_memory()
+        tclib.tc_set_memory_limit(tclib.tc_memory_stats()["in_use"] + steps * 4096)
+        try:
+            g.compute(tuning)
+            tclib.tc_set_memory_limit(0)
+            np.testing.assert_array_equal(g.results()["num"], ref.num)
+            return g.work_stats()["algorithm"]
+        except tclib.TCError as e:
+            assert e.status == tclib.TC_ERR_BUDGET
+            return 0
+        finally:
+            tclib.tc_set_memory_limit(0)
+            g.close()
+
+    low = {"algorithm": tclib.TC_ALGO_LOW_PIVOT}
+    try:
+        g = tclib.Graph.from_edges(src, dst, n)
+        hi = g.compute_bytes() // 4096 + 1
+        g.close()
+        a, b = 0, hi  # the least room for the low pivot
+        assert fits(hi, low)
+        while a + 1 < b:
+            m = (a + b) // 2
+            a, b = (a, m) if fits(m, low) else (m, b)
+        used = [fits(b + (hi - b) * i // 60, None) for i in range(61)]
+        print("[case] least room", b * 4096, "of", hi * 4096, "forms", used, flush=True)
+        assert all(used), used
+        assert used[-1] == tclib.TC_ALGO_MID_PIVOT
+    finally:
+        tclib.tc_set_memory_limit(0)
+        tclib.tc_trim_memory()
+
+
 def test_top_k_of_few_vertices_under_a_limit(tclib):
     # room for a sort of 40 vertices (under 10 KB), not for the selection's
     # histograms (64 KB)
