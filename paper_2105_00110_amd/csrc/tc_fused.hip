@@ -718,15 +718,23 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
         __syncthreads();
     }
     // count: the tail of N_H(r) after c merged with N_H(c), supports added to
-    // the canonical edges (so that they leave in order).  A lane goes on to its
-    // next slot as soon as its merge ends, without waiting for the longest
-    // merge of the wavefront.  The last slots, whose rows are of the highest
-    // ranks and merged most, lie in LDS with their counts (column | count << 16;
-    // a support is below n < 2^16), the others are taken in tiles that do while
-    // they are a merge's own row: what is left to device memory are the rows
-    // N_H(c) of lower ranks and their hits
-    uint32_t *const esup = q.A;  // the entries are no longer needed
-    for (uint32_t e = tid; e < m; e += BLOCK) at(esup, e) = 0;
+    // the slots.  Added to the canonical edges, every hit outside LDS waits for
+    // its slot's edge first: 16 complete graphs of 1000 vertices took 480 / 574 /
+    // 701 ms at 1024 / 512 / 256 threads so, 318 / 373 / 478 now; with no graph in
+    // LDS (fused_large) 427 / 407 / 384.  A lane goes on to its next slot as soon as
+    // its merge ends, without waiting for the longest merge of the wavefront.  The
+    // last slots, whose rows are of the highest ranks and merged most, lie in LDS
+    // with their counts (column | count << 16; a support is below n < 2^16), the
+    // others are taken in tiles that do while they are a merge's own row: what is
+    // left to device memory are the rows N_H(c) of lower ranks and their hits.  The
+    // edges' supports are cleared in order first and only those above 0 scattered
+    // afterwards (each such store is a sector: all of them scattered made the batch
+    // of 4096 BA graphs 11.1 ms, 10.1 so, 10.6 with supports on the edges)
+    uint32_t *const osup = q.A;  // the entries are no longer needed
+    for (uint32_t s = tid; s < m; s += BLOCK) {
+        at(osup, s) = 0;
+        if (a.sup) at(a.sup + q.pa, s) = 0;
+    }
     uint32_t *const top = words + n;
     const uint32_t room = (uint32_t)(Medium<BLOCK>::BYTES / 4) - n - Medium<BLOCK>::PAD;
     const uint32_t kept = m <= room ? m : room - (CT + longest), top0 = m - kept;
@@ -787,7 +795,7 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
                 hits &= hits - 1u;
                 atomicAdd(&own[i - t0 + e], 1u << 16);
                 if (in_top) atomicAdd(&top[f - top0], 1u << 16);
-                else wg_add(&at(esup, at(o2e, f)), 1u);
+                else wg_add(&at(osup, f), 1u);
             }
             i += na;
             j += nb;
@@ -795,7 +803,7 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
         __syncthreads();
         for (uint32_t i = tid; i < len; i += BLOCK) {
             const uint32_t c = own[i] >> 16;
-            if (c) wg_add(&at(esup, at(o2e, t0 + i)), c);
+            if (c) wg_add(&at(osup, t0 + i), c);
         }
         __syncthreads();
     }
@@ -805,27 +813,24 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
     // adjacent to none of its other neighbours (that would be a triangle), so a
     // triangle with one of them has no second neighbour among its vertices and
     // counts 3; the others have at most three neighbours of weight 1
-    for (uint32_t v = tid; v < n; v += BLOCK) {
-        words[v] = 0;
-        rank[v] = (uint16_t)at(q.rank, v);
-    }
+    for (uint32_t r = tid; r < n; r += BLOCK) words[r] = 0;
     __syncthreads();
     uint32_t local = 0;
     for (uint32_t t0 = 0; t0 < m; t0 += LT) {
-        uint32_t key[U], x[U];
+        uint32_t ends[U], x[U], e[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t e = t0 + u * BLOCK + tid;
-            key[u] = e < m ? at(q.C, e) : 0u;
-            x[u] = e < m ? at(esup, e) : 0u;
+            const uint32_t s = t0 + u * BLOCK + tid;
+            ends[u] = s < m ? at(ocol, s) : 0u;
+            x[u] = s < m ? at(osup, s) : 0u;
+            e[u] = s < m && a.sup ? at(o2e, s) : 0u;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t e = t0 + u * BLOCK + tid;
-            if (e < m && a.sup) at(a.sup + q.pa, e) = x[u];
             if (x[u]) {
-                atomicAdd(&words[rank[key[u] >> b]], x[u]);
-                atomicAdd(&words[rank[key[u] & vm]], x[u]);
+                if (a.sup) at(a.sup + q.pa, e[u]) = x[u];
+                atomicAdd(&words[ends[u] >> 16], x[u]);
+                atomicAdd(&words[ends[u] & 0xFFFFu], x[u]);
                 local += x[u];
             }
         }
@@ -842,26 +847,25 @@ __device__ __forceinline__ void fused_medium(const FusedArgs &a, const GraphRef 
     __syncthreads();
     // numerator: weight 1 for triangle neighbours (support > 0), 3 for others
     for (uint32_t t0 = 0; t0 < m; t0 += LT) {
-        uint32_t key[U], x[U], tl[U], th[U];
+        uint32_t ends[U], x[U], tl[U], th[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t e = t0 + u * BLOCK + tid;
-            key[u] = e < m ? at(q.C, e) : 0u;
-            x[u] = e < m ? at(esup, e) : 0u;
+            const uint32_t s = t0 + u * BLOCK + tid;
+            ends[u] = s < m ? at(ocol, s) : 0u;
+            x[u] = s < m ? at(osup, s) : 0u;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            key[u] = (uint32_t)rank[key[u] >> b] << 16 | rank[key[u] & vm];
-            tl[u] = at(tri, key[u] >> 16);
-            th[u] = at(tri, key[u] & 0xFFFFu);
+            tl[u] = at(tri, ends[u] >> 16);
+            th[u] = at(tri, ends[u] & 0xFFFFu);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t e = t0 + u * BLOCK + tid;
-            if (e < m) {
+            const uint32_t s = t0 + u * BLOCK + tid;
+            if (s < m) {
                 const uint32_t f = x[u] ? 1u : 3u;
-                if (th[u]) atomicAdd(&words[key[u] >> 16], f * th[u]);
-                if (tl[u]) atomicAdd(&words[key[u] & 0xFFFFu], f * tl[u]);
+                if (th[u]) atomicAdd(&words[ends[u] >> 16], f * th[u]);
+                if (tl[u]) atomicAdd(&words[ends[u] & 0xFFFFu], f * tl[u]);
             }
         }
     }
