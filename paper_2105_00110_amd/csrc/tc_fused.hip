@@ -402,7 +402,8 @@ __device__ __forceinline__ void fused_small(const FusedArgs &a, const GraphRef q
 // by the memory latency of one workgroup's 16 wavefronts, so loads in flight
 // count: a loop over single elements waits a round trip for each (4096 BA
 // graphs: 25.8 ms before, 14.9 ms so, of which the merge's random rows took 8.4;
-// 10.65 ms with the highest rows and their counts in LDS).
+// 10.65 ms with the highest rows and their counts in LDS, 10.1 with the supports
+// of the others on their slots).
 // ---------------------------------------------------------------------------
 template <int BLOCK>
 struct Medium {
@@ -1185,7 +1186,7 @@ __global__ void k_fused_init(unsigned char *ws) {
 // three that LDS holds; with the 212 that the tiers take if left alone it is two,
 // and 600 graphs of 30000 vertices and 120000 pairs take 18.9 ms (16.3 so), 3000
 // BA graphs of 60 to 260 vertices 0.19 (0.15), but 4096 BA graphs of up to 20000
-// vertices 32.1 (34.7); before the tiers, with 4 per SIMD, the three took 16.2,
+// vertices 32.6 (35.3); before the tiers, with 4 per SIMD, the three took 16.2,
 // 0.43 and 38.3 ms.
 constexpr int fused_waves(int block) { return block == 512 ? 4 : block == 256 ? 3 : 1; }
 
@@ -1320,8 +1321,8 @@ extern "C" {
 tc_status tc_fused_tuning_default(tc_fused_tuning *t) {
     if (!t) return TC_ERR_INVALID_ARG;
     // measured on MI355X, the 4096-graph BA batch (ms) and five ER graphs of 10 k
-    // pairs (us): 1024 threads x 1 per compute unit 10.6, 103; 512 x 1 20.6, 186;
-    // 512 x 2 23.1, 188; 256 x 4 35.3, 307.  Thousands of graphs of a few hundred
+    // pairs (us): 1024 threads x 1 per compute unit 10.1, 103; 512 x 1 20.4, 186;
+    // 512 x 2 22.4, 188; 256 x 4 35.3, 307.  Thousands of graphs of a few hundred
     // vertices go faster with more workgroups: 3000 of 60 to 260 vertices 343 us at
     // 1024 x 1, 195 at 512 x 2, 152 at 256 x 4.
     t->block = 1024;
